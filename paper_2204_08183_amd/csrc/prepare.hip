@@ -6,8 +6,8 @@
 //  - Fine-Gray: Kaplan-Meier estimate of the censoring survival G (Sec. 2.2)
 //    as a suffix product over runs, the competing-event weights 1/G(y) and
 //    G(y) at every position;
-//  - the CSC design re-labelled to sorted positions and sorted inside each
-//    column, the per-column chunk index and c_j = sum over events of x_ij.
+//  - (design.hip) the CSC design re-labelled to sorted positions, the
+//    per-column chunk index and c_j = sum over events of x_ij.
 // Every integer output is produced with exact integer arithmetic, so it is
 // identical from run to run.
 #include <vector>
@@ -171,7 +171,7 @@ __global__ void k_time_keys(const double *y, int64_t n, uint64_t *keys, uint64_t
 __global__ void k_after_sort(int64_t n, int model, const uint64_t *sorted_idx,
                              const double *y, const int8_t *status, int32_t *perm,
                              int32_t *inv_perm, double *y_s, int8_t *st_s,
-                             uint8_t *ev_s, uint32_t *err)
+                             uint8_t *ev_s, uint32_t *ev_bits, uint32_t *err)
 {
     for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n;
          k += (int64_t)gridDim.x * blockDim.x) {
@@ -189,7 +189,10 @@ __global__ void k_after_sort(int64_t n, int model, const uint64_t *sorted_idx,
             s = 0;
         }
         st_s[k] = s;
-        ev_s[k] = model == SS_COX ? (s != 0) : (s == 1);
+        const bool ev = model == SS_COX ? (s != 0) : (s == 1);
+        ev_s[k] = ev;
+        const uint64_t bits = __ballot(ev);  // k is a multiple of 64 at lane 0
+        if (lane_id() == 0) *reinterpret_cast<uint64_t *>(ev_bits + k / 32) = bits;
     }
 }
 
@@ -252,141 +255,12 @@ __global__ void k_fg_weights(int64_t n, const int8_t *st_s, const double *g_end,
         w_comp[k] = st_s[k] == 2 ? 1.0 / g_end[k] : 0.0;
 }
 
-// A balanced work list over the non-zeros: chunk q covers entries
-// [begin, end) of column col, with at most kEntChunk entries.
-constexpr int64_t kEntChunk = 4096;
-struct EntChunk {
-    int64_t col;
-    int64_t begin;
-    int64_t end;
-};
-
-__global__ void k_csc_keys(const EntChunk *chunks, int64_t nchunks, int64_t n,
-                           const int32_t *rows, const double *vals,
-                           const int32_t *inv_perm, int posbits, uint64_t *keys,
-                           uint64_t *kv, uint32_t *err)
-{
-    for (int64_t q = blockIdx.x; q < nchunks; q += gridDim.x) {
-        const EntChunk ch = chunks[q];
-        for (int64_t o = ch.begin + threadIdx.x; o < ch.end; o += blockDim.x) {
-            int32_t r = rows[o];
-            if (r < 0 || r >= n) {
-                atomicOr(err, 8u);
-                r = 0;
-            }
-            keys[o] = ((uint64_t)ch.col << posbits) | (uint64_t)inv_perm[r];
-            if (vals) kv[o] = (uint64_t)__double_as_longlong(vals[o]);
-        }
-    }
-}
-
-__global__ void k_csc_unpack(int64_t nnz, const uint64_t *keys, const uint64_t *kv,
-                             uint64_t posmask, int32_t *rows_sorted, double *vals_sorted)
-{
-    for (int64_t o = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; o < nnz;
-         o += (int64_t)gridDim.x * blockDim.x) {
-        rows_sorted[o] = (int32_t)(keys[o] & posmask);
-        if (vals_sorted) vals_sorted[o] = __longlong_as_double((long long)kv[o]);
-    }
-}
-
-// c_j, step 1: every chunk sums x over its event rows in a fixed order.
-__global__ __launch_bounds__(256) void k_col_c_part(const EntChunk *chunks, int64_t nchunks,
-                                                    int64_t n, const int32_t *rows_sorted,
-                                                    const double *vals_sorted,
-                                                    const uint8_t *ev_s, double *part)
-{
-    __shared__ double s_red[256 / kWave];
-    for (int64_t q = blockIdx.x; q < nchunks; q += gridDim.x) {
-        const EntChunk ch = chunks[q];
-        double acc = 0.0;
-        for (int64_t o = ch.begin + threadIdx.x; o < ch.end; o += blockDim.x) {
-            const int32_t r = rows_sorted[o];
-            if (r >= 0 && r < n && ev_s[r]) acc += vals_sorted ? vals_sorted[o] : 1.0;
-        }
-#pragma unroll
-        for (int off = kWave / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, kWave);
-        if (lane_id() == 0) s_red[threadIdx.x / kWave] = acc;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double t = 0.0;
-            for (int i = 0; i < 256 / kWave; ++i) t += s_red[i];
-            part[q] = t;
-        }
-        __syncthreads();
-    }
-}
-
-// c_j, step 2: one thread per column adds its chunks in order.
-__global__ void k_col_c_final(int64_t p, const int64_t *col_first_chunk, const double *part,
-                              double *c)
-{
-    for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < p;
-         j += (int64_t)gridDim.x * blockDim.x) {
-        double t = 0.0;
-        for (int64_t q = col_first_chunk[j]; q < col_first_chunk[j + 1]; ++q) t += part[q];
-        c[j] = t;
-    }
-}
-
-// chunk_ptr[j*(C+1)+t] = first offset in column j with position >= t*SS_CHUNK.
-// Step 1: every non-zero writes the boundaries between its predecessor's
-// chunk and its own.
-__global__ void k_chunk_ptr_entries(const EntChunk *chunks, int64_t nchunks, int64_t nchunk,
-                                    const int64_t *col_ptr, const int32_t *rows_sorted,
-                                    int32_t *chunk_ptr, uint32_t *err)
-{
-    for (int64_t q = blockIdx.x; q < nchunks; q += gridDim.x) {
-        const EntChunk ch = chunks[q];
-        const int64_t c0 = col_ptr[ch.col];
-        int32_t *cp = chunk_ptr + ch.col * (nchunk + 1);
-        for (int64_t o = ch.begin + threadIdx.x; o < ch.end; o += blockDim.x) {
-            const int32_t r = rows_sorted[o];
-            int64_t cur = r / SS_CHUNK;
-            if (r < 0 || cur >= nchunk) {
-                atomicOr(err, 256u);
-                continue;
-            }
-            int64_t prev = -1;
-            if (o > c0) {
-                const int32_t rp = rows_sorted[o - 1];
-                if (rp >= r) atomicOr(err, 16u);  // duplicate row in a column
-                prev = rp / SS_CHUNK;
-                if (rp < 0 || prev > cur) prev = cur;
-            }
-            for (int64_t t = prev + 1; t <= cur; ++t) cp[t] = (int32_t)(o - c0);
-        }
-    }
-}
-
-// Step 2: the boundaries after the last non-zero of every column.
-__global__ void k_chunk_ptr_tail(int64_t p, int64_t nchunk, const int64_t *col_ptr,
-                                 const int32_t *rows_sorted, int32_t *chunk_ptr)
-{
-    for (int64_t j = blockIdx.x; j < p; j += gridDim.x) {
-        const int64_t c0 = col_ptr[j];
-        const int64_t m = col_ptr[j + 1] - c0;
-        int64_t last = m == 0 ? -1 : rows_sorted[c0 + m - 1] / SS_CHUNK;
-        if (last < -1 || last >= nchunk) last = nchunk - 1;
-        int32_t *cp = chunk_ptr + j * (nchunk + 1);
-        for (int64_t t = last + 1 + threadIdx.x; t <= nchunk; t += blockDim.x)
-            cp[t] = (int32_t)m;
-    }
-}
-
 int grid_1d(int64_t work, int cap = 8192)
 {
     int64_t g = ceil_div(work, 256);
     if (g < 1) g = 1;
     if (g > cap) g = cap;
     return (int)g;
-}
-
-int bits_for(int64_t v)  // bits needed for values in [0, v]
-{
-    int b = 0;
-    while (b < 63 && (v >> b) != 0) ++b;
-    return b;
 }
 
 // ------------------------------------------------------------ workspace
@@ -401,17 +275,14 @@ struct PrepWs {
     int32_t *cnt_cens;
     int8_t *st_s;
     uint8_t *ev_s;
+    uint32_t *ev_bits;
     uint32_t *err;
-    EntChunk *chunks;
-    double *part;
-    int64_t *col_first;
+    void *design;
 };
 
 size_t layout(int64_t n, int64_t p, int64_t nnz, char *base, PrepWs *w)
 {
-    const int64_t max_chunks = nnz / kEntChunk + p + 1;
-    const int64_t m = n > nnz ? n : nnz;
-    const int64_t nbr = ceil_div(m, RT);
+    const int64_t nbr = ceil_div(n, RT);
     const int64_t hist_len = 256 * nbr;
     const int64_t scan_len = hist_len > n ? hist_len : n;
     const int64_t nbs = ceil_div(scan_len, ST) + 1;
@@ -422,10 +293,15 @@ size_t layout(int64_t n, int64_t p, int64_t nnz, char *base, PrepWs *w)
         return p;
     };
     PrepWs t;
-    t.keyA = (uint64_t *)take(8 * (size_t)m);
-    t.keyB = (uint64_t *)take(8 * (size_t)m);
-    t.valA = (uint64_t *)take(8 * (size_t)m);
-    t.valB = (uint64_t *)take(8 * (size_t)m);
+    t.ev_bits = (uint32_t *)take(4 * 2 * (size_t)ceil_div(n, kWave));
+    t.err = (uint32_t *)take(256);
+    // the design's scratch takes the place of the ordering's, which is done
+    t.design = base ? base + off : nullptr;
+    const size_t design_end = off + design_ws_bytes(n, p, nnz);
+    t.keyA = (uint64_t *)take(8 * (size_t)n);
+    t.keyB = (uint64_t *)take(8 * (size_t)n);
+    t.valA = (uint64_t *)take(8 * (size_t)n);
+    t.valB = (uint64_t *)take(8 * (size_t)n);
     t.hist = (uint32_t *)take(4 * (size_t)hist_len);
     t.sums = (uint64_t *)take(8 * (size_t)nbs);
     t.y_s = (double *)take(8 * (size_t)n);
@@ -435,12 +311,8 @@ size_t layout(int64_t n, int64_t p, int64_t nnz, char *base, PrepWs *w)
     t.cnt_cens = (int32_t *)take(4 * (size_t)n);
     t.st_s = (int8_t *)take((size_t)n);
     t.ev_s = (uint8_t *)take((size_t)n);
-    t.err = (uint32_t *)take(256);
-    t.chunks = (EntChunk *)take(sizeof(EntChunk) * (size_t)max_chunks);
-    t.part = (double *)take(8 * (size_t)max_chunks);
-    t.col_first = (int64_t *)take(8 * (size_t)(p + 1));
     if (w) *w = t;
-    return off;
+    return off > design_end ? off : design_end;
 }
 
 template <typename T, typename Op, bool REV, bool EXCL>
@@ -508,30 +380,16 @@ int32_t run_prepare(int32_t model, int64_t n, int64_t p, int64_t nnz, const doub
     const bool fg = model == SS_FINE_GRAY;
     int32_t rc;
 
-    // ---- the column pointers on the host: checked there, and cut into a
-    // balanced list of non-zero chunks for the design kernels
+    // ---- the column pointers, checked on the host
     std::vector<int64_t> cp_host((size_t)p + 1);
     SS_HIP_CHECK(hipMemcpyAsync(cp_host.data(), col_ptr, sizeof(int64_t) * (size_t)(p + 1),
                                 hipMemcpyDeviceToHost, s));
     SS_HIP_CHECK(hipStreamSynchronize(s));
     if (cp_host[0] != 0 || cp_host[(size_t)p] != nnz) return SS_EINVAL;
-    std::vector<EntChunk> chunks;
-    std::vector<int64_t> first((size_t)p + 1);
-    chunks.reserve((size_t)(nnz / kEntChunk + p + 1));
     for (int64_t j = 0; j < p; ++j) {
         const int64_t a = cp_host[(size_t)j], b = cp_host[(size_t)j + 1];
         if (b < a || a < 0 || b > nnz) return SS_EINVAL;
-        first[(size_t)j] = (int64_t)chunks.size();
-        for (int64_t o = a; o < b; o += kEntChunk)
-            chunks.push_back(EntChunk{j, o, o + kEntChunk < b ? o + kEntChunk : b});
     }
-    first[(size_t)p] = (int64_t)chunks.size();
-    const int64_t nchunks = (int64_t)chunks.size();
-    if (nchunks > 0)
-        SS_HIP_CHECK(hipMemcpyAsync(w.chunks, chunks.data(), sizeof(EntChunk) * chunks.size(),
-                                    hipMemcpyHostToDevice, s));
-    SS_HIP_CHECK(hipMemcpyAsync(w.col_first, first.data(), sizeof(int64_t) * first.size(),
-                                hipMemcpyHostToDevice, s));
 
     hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, s, (int32_t *)w.err, (int64_t)1, 0);
     SS_LAUNCH_CHECK();
@@ -543,7 +401,7 @@ int32_t run_prepare(int32_t model, int64_t n, int64_t p, int64_t nnz, const doub
     rc = radix_sort(n, 64, true, w, &ks, &vs, s);
     if (rc) return rc;
     hipLaunchKernelGGL(k_after_sort, dim3(grid_1d(n)), dim3(256), 0, s, n, (int)model, vs, y,
-                       status, perm, inv_perm, w.y_s, w.st_s, w.ev_s, w.err);
+                       status, perm, inv_perm, w.y_s, w.st_s, w.ev_s, w.ev_bits, w.err);
     SS_LAUNCH_CHECK();
 
     // ---- tie runs and event counts
@@ -571,37 +429,11 @@ int32_t run_prepare(int32_t model, int64_t n, int64_t p, int64_t nnz, const doub
         SS_LAUNCH_CHECK();
     }
 
-    // ---- design: re-label to sorted positions, sort inside columns
-    const int posbits = bits_for(n - 1);
-    const int colbits = bits_for(p - 1);
-    const unsigned gch = (unsigned)(nchunks < 65536 ? (nchunks > 0 ? nchunks : 1) : 65536);
-    if (nnz > 0) {
-        hipLaunchKernelGGL(k_csc_keys, dim3(gch), dim3(256), 0, s, w.chunks, nchunks, n, rows,
-                           vals, inv_perm, posbits, w.keyA, w.valA, w.err);
-        SS_LAUNCH_CHECK();
-        rc = radix_sort(nnz, posbits + colbits, vals != nullptr, w, &ks, &vs, s);
-        if (rc) return rc;
-        const uint64_t posmask = posbits >= 64 ? ~0ull : ((1ull << posbits) - 1);
-        hipLaunchKernelGGL(k_csc_unpack, dim3(grid_1d(nnz)), dim3(256), 0, s, nnz, ks, vs,
-                           posmask, rows_sorted, vals ? vals_sorted : (double *)nullptr);
-        SS_LAUNCH_CHECK();
-        hipLaunchKernelGGL(k_col_c_part, dim3(gch), dim3(256), 0, s, w.chunks, nchunks, n,
-                           rows_sorted, vals ? vals_sorted : (const double *)nullptr, w.ev_s,
-                           w.part);
-        SS_LAUNCH_CHECK();
-    }
-    hipLaunchKernelGGL(k_col_c_final, dim3(grid_1d(p)), dim3(256), 0, s, p, w.col_first,
-                       w.part, c);
-    SS_LAUNCH_CHECK();
-    const int64_t nchunk = ceil_div(n, SS_CHUNK);
-    if (nnz > 0) {
-        hipLaunchKernelGGL(k_chunk_ptr_entries, dim3(gch), dim3(256), 0, s, w.chunks, nchunks,
-                           nchunk, col_ptr, rows_sorted, chunk_ptr, w.err);
-        SS_LAUNCH_CHECK();
-    }
-    hipLaunchKernelGGL(k_chunk_ptr_tail, dim3((unsigned)(p < 8192 ? p : 8192)), dim3(256), 0, s,
-                       p, nchunk, col_ptr, rows_sorted, chunk_ptr);
-    SS_LAUNCH_CHECK();
+    // ---- design: re-labelled to sorted positions, ascending inside columns
+    std::vector<int64_t> host_list;
+    rc = run_design(n, p, nnz, cp_host.data(), col_ptr, rows, vals, inv_perm, w.ev_bits,
+                    rows_sorted, vals_sorted, chunk_ptr, c, w.err, w.design, host_list, s);
+    if (rc) return rc;
 
     // ---- data errors found on the device
     uint32_t err = 0;
@@ -620,6 +452,12 @@ int32_t scan_add_f64(const double *in, double *out, int64_t m, bool rev, bool ex
     }
     return excl ? device_scan<double, OpAdd<double>, false, true>(in, out, m, w, s)
                 : device_scan<double, OpAdd<double>, false, false>(in, out, m, w, s);
+}
+
+int32_t scan_add_u32_excl(const uint32_t *in, uint32_t *out, int64_t m, void *sums, hipStream_t s)
+{
+    return device_scan<uint32_t, OpAdd<uint32_t>, false, true>(
+        in, out, m, reinterpret_cast<uint64_t *>(sums), s);
 }
 
 size_t scan_sums_bytes(int64_t m) { return 8 * (size_t)ceil_div(m, ST); }

@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <vector>
+
 #include "survscan.h"
 
 namespace ss {
@@ -322,6 +324,8 @@ int32_t launch_ccd_scalar(int32_t penalty, double lambda, int32_t j,
 int32_t scan_add_f64(const double *in, double *out, int64_t m, bool rev, bool excl,
                      void *sums, hipStream_t s);
 size_t scan_sums_bytes(int64_t m);
+// Exclusive prefix sums of 32-bit counts (same scratch).
+int32_t scan_add_u32_excl(const uint32_t *in, uint32_t *out, int64_t m, void *sums, hipStream_t s);
 // The first two passes of scan_add_f64 alone: sums[t] = the exclusive carry
 // of scan tile t (tiles of 2048 items, in scan order), for a kernel that
 // finishes the scan itself.
@@ -378,6 +382,17 @@ int32_t launch_gather(int64_t n, const int32_t *perm, const double *src,
 int32_t launch_ws_init(void *ws, size_t bytes, hipStream_t stream);
 
 // a0
+// The design part of the preparation (design.hip); cp_host: the checked
+// column pointers on the host, ev_bits: one bit per sorted position,
+// host_list: filled with a list that the stream reads, so the caller keeps it
+// until the stream has synchronised.
+size_t design_ws_bytes(int64_t n, int64_t p, int64_t nnz);
+int32_t run_design(int64_t n, int64_t p, int64_t nnz, const int64_t *cp_host,
+                   const int64_t *col_ptr, const int32_t *rows, const double *vals,
+                   const int32_t *inv_perm, const uint32_t *ev_bits, int32_t *rows_sorted,
+                   double *vals_sorted, int32_t *chunk_ptr, double *c, uint32_t *err, void *ws,
+                   std::vector<int64_t> &host_list, hipStream_t s);
+
 size_t prepare_ws_bytes(int64_t n, int64_t p, int64_t nnz);
 int32_t run_prepare(int32_t model, int64_t n, int64_t p, int64_t nnz,
                     const double *y, const int8_t *status,

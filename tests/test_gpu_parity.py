@@ -457,3 +457,62 @@ def test_hand_examples(name):
     ll = float(prob.loglik().cpu()[0])
     assert ll == pytest.approx(g["loglik"], rel=1e-14, abs=1e-15)
     assert n == prob.n
+
+
+# The design's ordering: a column is one LDS bitmap up to 2^20 positions, cut
+# into windows above that and where few long columns would leave the chip
+# idle; pieces with few entries for their window are sorted in LDS instead
+# (at most 1024 of them, fewer than one per 512 positions).
+DESIGN_CASES = [
+    # n, entries per column
+    (131_072, [0, 1, 255, 256, 257, 131_072]),        # the line between the two, W / 512
+    (131_073, [255, 256, 257, 131_073, 131_072]),     # the larger workgroup; a full column
+    (1_048_576, [1023, 1024, 1025, 2048, 60_000]),    # the largest single window
+    (1_048_577, [0, 1, 1024, 1025, 70_000]),          # two windows, the last one position
+    (2_100_000, [900_000, 300, 2_100_000]),           # windows cut further, nearly full
+    (40_000, [20_000, 40_000]),                       # short columns cut further
+]
+
+
+@pytest.mark.parametrize("valued", [False, True])
+@pytest.mark.parametrize("n,counts", DESIGN_CASES)
+def test_design_ordering(n, counts, valued):
+    rng = np.random.default_rng(n)
+    y = rng.random(n)
+    status = (rng.random(n) < 0.5).astype(np.int8)
+    rows = np.concatenate([rng.permutation(n)[:m] for m in counts]).astype(np.int32)
+    vals = rng.uniform(1.0, 2.0, rows.size) if valued else None
+    col_ptr = np.concatenate([[0], np.cumsum(counts)]).astype(np.int64)
+    prob = ss.Problem("cox", y, status, col_ptr, rows, vals)
+    order = np.argsort(-y, kind="stable")
+    inv = np.empty_like(order)
+    inv[order] = np.arange(n)
+    rs, vs = oprep.csc_sorted_rows(col_ptr, rows, vals, inv)
+    np.testing.assert_array_equal(prob.rows_sorted.cpu().numpy()[:rs.size], rs)
+    if valued:
+        np.testing.assert_array_equal(prob.vals_sorted.cpu().numpy()[:rs.size], vs)
+    cp = prob.chunk_ptr.cpu().numpy().reshape(len(counts), prob.nchunk + 1)
+    edges = np.arange(prob.nchunk + 1) * ss.CHUNK
+    got_c = prob.c.cpu().numpy()
+    for j in range(len(counts)):
+        a, b = col_ptr[j], col_ptr[j + 1]
+        np.testing.assert_array_equal(cp[j], np.searchsorted(rs[a:b], edges, side="left"))
+        x = np.ones(b - a) if vals is None else vals[a:b]
+        want = float(np.sum(x * status[rows[a:b]]))
+        # fixed-order sums of at most 2^21 terms in [1, 2]
+        assert abs(got_c[j] - want) <= (2.0 ** -31 * want if valued else 0.0), j
+
+
+@pytest.mark.parametrize("n,m", [(3000, 40), (300_000, 30), (300_000, 2000), (2_100_000, 50_000)])
+def test_design_errors(n, m):
+    """A duplicate row and a row out of range are still refused, on every
+    path of the ordering."""
+    rng = np.random.default_rng(m)
+    rows = rng.permutation(n)[:m].astype(np.int32)
+    y, status = rng.random(n), np.ones(n, dtype=np.int8)
+    ptr = np.array([0, m], dtype=np.int64)
+    for bad in (int(rows[0]), n, -1):
+        r = rows.copy()
+        r[m - 1] = bad
+        with pytest.raises(ss.SurvScanError):
+            ss.Problem("cox", y, status, ptr, r)

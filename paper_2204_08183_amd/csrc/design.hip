@@ -14,7 +14,9 @@
 // Bound: per non-zero one random 4-byte read of inv_perm and one LDS atomic,
 // both about one lane per clock and CU; 8 bytes of HBM traffic (20 valued)
 // against 24 per pass of the 4-5 pass LSD radix sort of (column, position)
-// keys it replaced.  N = 1e6, P = 1000, 5e7 non-zeros: see kBitsBlock.
+// keys it replaced.  N = 1e6, P = 1000, 5e7 non-zeros: 288 us against 3.3 ms
+// (without the reads of inv_perm ~220 us, without the stores ~280 us: no one
+// part bounds it, the phases of the one workgroup a CU holds add up).
 #include <algorithm>
 #include <vector>
 
@@ -81,17 +83,27 @@ __host__ __device__ __forceinline__ bool is_small(int64_t m, int64_t cnt)
     return m <= kSmallMax && m < cnt / 512;
 }
 
-// Position of entry o inside the window (an out-of-range row is reported
-// and taken as row 0; the caller keeps every store in bounds).
-__device__ __forceinline__ uint32_t entry_pos(const DesignArgs &a, int64_t o)
+// Positions of U of a piece's entries, i = first + u * stride (the last entry
+// again past the end): U independent loads, and U more through inv_perm.  An
+// out-of-range row sets `bad` and is taken as row 0.
+template <int U>
+__device__ __forceinline__ void entry_pos(const DesignArgs &a, const Piece &pc, int32_t first,
+                                          int32_t stride, uint32_t (&k)[U], bool &bad)
 {
-    if (a.nwin > 1) return a.pos[o];
-    int32_t r = a.rows[o];
-    if (r < 0 || r >= a.n) {
-        atomicOr(a.err, 8u);
-        r = 0;
+    if (a.nwin > 1) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) k[u] = a.pos[pc.lo + min(first + u * stride, pc.m - 1)];
+        return;
     }
-    return (uint32_t)a.inv_perm[r];
+    int32_t r[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) r[u] = a.rows[pc.lo + min(first + u * stride, pc.m - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const bool out = r[u] < 0 || r[u] >= a.n;
+        bad |= out;
+        k[u] = (uint32_t)a.inv_perm[out ? 0 : r[u]];
+    }
 }
 
 template <int BLOCK>
@@ -111,7 +123,7 @@ template <int BLOCK, bool VALS>
 __global__ __launch_bounds__(BLOCK) void k_design_bits(DesignArgs a, int32_t max_words)
 {
     constexpr int NW = BLOCK / kWave;
-    constexpr int U = 4;  // entries in flight per thread
+    constexpr int U = BLOCK == 1024 ? 16 : 8;  // entries in flight per thread
     extern __shared__ __attribute__((aligned(16))) uint32_t s_bits[];
     uint32_t *s_pre = s_bits + max_words;  // entries before every group of words
     __shared__ uint32_t s_w[NW];
@@ -127,20 +139,21 @@ __global__ __launch_bounds__(BLOCK) void k_design_bits(DesignArgs a, int32_t max
         __syncthreads();
 
         // ---- one bit per entry
-        auto set = [&](uint32_t k) {
-            const uint32_t bit = 1u << (k & 31u);
-            if (atomicOr(&s_bits[k >> 5], bit) & bit) atomicOr(a.err, 16u);  // a duplicate row
-        };
-        int32_t o = tid;
-        for (; o + (U - 1) * BLOCK < pc.m; o += U * BLOCK) {
+        bool bad = false, twice = false;
+        for (int32_t o = tid; o < pc.m; o += U * BLOCK) {
             uint32_t k[U];
+            entry_pos<U>(a, pc, o, BLOCK, k, bad);
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                k[u] = entry_pos(a, pc.lo + o + u * BLOCK) - (uint32_t)pc.base;
-#pragma unroll
-            for (int u = 0; u < U; ++u) set(k[u]);
+            for (int u = 0; u < U; ++u) {
+                if (o + u * BLOCK < pc.m) {
+                    k[u] -= (uint32_t)pc.base;
+                    const uint32_t bit = 1u << (k[u] & 31u);
+                    twice |= (atomicOr(&s_bits[k[u] >> 5], bit) & bit) != 0u;
+                }
+            }
         }
-        for (; o < pc.m; o += BLOCK) set(entry_pos(a, pc.lo + o) - (uint32_t)pc.base);
+        if (bad) atomicOr(a.err, 8u);
+        if (twice) atomicOr(a.err, 16u);  // a duplicate row
         __syncthreads();
 
         // ---- entries per group of words, then their exclusive prefix
@@ -183,27 +196,28 @@ __global__ __launch_bounds__(BLOCK) void k_design_bits(DesignArgs a, int32_t max
             if (pc.last && tid == 0) cp[chunks] = off + pc.m;
         }
 
-        // ---- the ascending positions, a lane per word: neighbouring lanes
-        // write neighbouring runs
+        // ---- the ascending positions, a lane per 64 of them: neighbouring
+        // lanes write neighbouring runs
         double evs = 0.0;
-        for (int wd0 = 0; wd0 < words; wd0 += BLOCK) {
-            const int wd = wd0 + tid;
-            uint32_t x = wd < words ? s_bits[wd] : 0u;
-            if (!VALS && wd < words)
-                evs += (double)__popc(x & a.ev_bits[pc.base / 32 + wd]);
-            // words before this one in its group: eight lanes share a group
-            uint32_t inc = (uint32_t)__popc(x);
+        constexpr int kPairs = kGroupWords / 2;  // lanes that share a group
+        const uint64_t *b64 = reinterpret_cast<const uint64_t *>(s_bits);
+        const uint64_t *e64 = reinterpret_cast<const uint64_t *>(a.ev_bits + pc.base / 32);
+        for (int p0 = 0; p0 < (words + 1) / 2; p0 += BLOCK) {
+            const int pr = p0 + tid;
+            const bool in = pr < (words + 1) / 2;
+            uint64_t x = in ? b64[pr] : 0u;
+            if (!VALS && in) evs += (double)__popcll(x & e64[pr]);
+            uint32_t inc = (uint32_t)__popcll(x);
             const uint32_t own = inc;
 #pragma unroll
-            for (int off = 1; off < kGroupWords; off <<= 1) {
-                const uint32_t y = __shfl_up(inc, off, kGroupWords);
-                if ((lane & (kGroupWords - 1)) >= off) inc += y;
+            for (int off = 1; off < kPairs; off <<= 1) {
+                const uint32_t y = __shfl_up(inc, off, kPairs);
+                if ((lane & (kPairs - 1)) >= off) inc += y;
             }
-            int32_t at = wd < words ? (int32_t)(s_pre[wd / kGroupWords] + inc - own) : 0;
-            int32_t *dst = a.rows_sorted + pc.lo;
-            const int32_t k0 = (int32_t)(pc.base + 32 * (int64_t)wd);
+            int32_t *dst = a.rows_sorted + pc.lo + (in ? (int32_t)(s_pre[pr / kPairs] + inc - own) : 0);
+            const int32_t k0 = (int32_t)(pc.base + 64 * (int64_t)pr);
             while (x != 0u) {
-                dst[at++] = k0 + (__ffs(x) - 1);
+                *dst++ = k0 + (__ffsll((unsigned long long)x) - 1);
                 x &= x - 1u;
             }
         }
@@ -211,19 +225,29 @@ __global__ __launch_bounds__(BLOCK) void k_design_bits(DesignArgs a, int32_t max
             // ---- every value to its entry's place, then the event sum in
             // that order
             double *dst = a.vals_sorted + pc.lo;
-            for (int32_t i = tid; i < pc.m; i += BLOCK) {
-                const uint32_t k = entry_pos(a, pc.lo + i) - (uint32_t)pc.base;
-                const double v = a.nwin > 1 ? a.pv[pc.lo + i] : a.vals[pc.lo + i];
-                const uint32_t g = k / kGroupPos, wd = (k >> 5) & (kGroupWords - 1);
-                const uint4 x = b4[2 * g], y = b4[2 * g + 1];
-                const uint32_t ws[kGroupWords] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
-                uint32_t at = s_pre[g];
+            constexpr int V = 4;
+            for (int32_t o = tid; o < pc.m; o += V * BLOCK) {
+                uint32_t k[V];
+                double v[V];
+                entry_pos<V>(a, pc, o, BLOCK, k, bad);
 #pragma unroll
-                for (int u = 0; u < kGroupWords; ++u) {
-                    const uint32_t below = (1u << (k & 31u)) - 1u;
-                    at += __popc(u < (int)wd ? ws[u] : u == (int)wd ? ws[u] & below : 0u);
+                for (int u = 0; u < V; ++u) {
+                    const int64_t i = pc.lo + min(o + u * BLOCK, pc.m - 1);
+                    v[u] = a.nwin > 1 ? a.pv[i] : a.vals[i];
                 }
-                dst[at] = v;
+#pragma unroll
+                for (int u = 0; u < V; ++u) {
+                    k[u] -= (uint32_t)pc.base;
+                    const uint32_t g = k[u] / kGroupPos, wd = (k[u] >> 5) & (kGroupWords - 1);
+                    const uint4 x = b4[2 * g], y = b4[2 * g + 1];
+                    const uint32_t ws[kGroupWords] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+                    const uint32_t below = (1u << (k[u] & 31u)) - 1u;
+                    uint32_t at = s_pre[g];
+#pragma unroll
+                    for (int q = 0; q < kGroupWords; ++q)
+                        at += __popc(q < (int)wd ? ws[q] : q == (int)wd ? ws[q] & below : 0u);
+                    if (o + u * BLOCK < pc.m) dst[at] = v[u];
+                }
             }
             __syncthreads();
             for (int32_t i = tid; i < pc.m; i += BLOCK) {
@@ -253,8 +277,13 @@ __global__ __launch_bounds__(kSmallBlock) void k_design_small(DesignArgs a)
         if (!is_small(pc.m, pc.cnt)) continue;
         int size = 2;
         while (size < pc.m) size *= 2;
-        for (int i = tid; i < size; i += BLOCK)
-            s_k[i] = i < pc.m ? ((uint64_t)entry_pos(a, pc.lo + i) << 32) | (uint32_t)i : ~0ull;
+        bool bad = false;
+        for (int i = tid; i < size && pc.m > 0; i += BLOCK) {
+            uint32_t k[1];
+            entry_pos<1>(a, pc, i, 0, k, bad);
+            s_k[i] = i < pc.m ? ((uint64_t)k[0] << 32) | (uint32_t)i : ~0ull;
+        }
+        if (bad) atomicOr(a.err, 8u);
         __syncthreads();
         for (int k = 2; k <= size; k *= 2) {
             for (int d = k / 2; d > 0; d /= 2) {

@@ -234,6 +234,11 @@ int32_t ss_exp(int64_t n, const double *eta, double *e, void *stream);
 int32_t ss_gather(int64_t n, const int32_t *perm, const double *src,
                   double *dst, void *stream);
 
+/* ss_gather and ss_exp in one pass: eta[k] = src[perm[k]], e[k] = exp(eta[k])
+ * (src overlaps neither). */
+int32_t ss_gather_exp(int64_t n, const int32_t *perm, const double *src,
+                      double *eta, double *e, void *stream);
+
 /* ---------------------------------------------- FP32 storage of e
  * The paper stores the per-subject quantities in FP64 (Sec. 2.7); these two
  * calls keep e = exp(X beta) in FP32 instead, to measure what that costs in
@@ -315,8 +320,7 @@ int32_t ss_grad_hess_mixed(int32_t model, int32_t acc, int64_t n, int64_t p,
  * double.  The
  * workspace (any 256-byte-aligned device buffer of
  * ss_eta_gradient_workspace_bytes(n) bytes, caller-owned, no
- * initialisation) holds four N-vectors of partial results, the block sums
- * of l and the scan carries; it is distinct from the ss_grad_hess
+ * initialisation) holds four N-vectors of partial results and per-tile sums; it is distinct from the ss_grad_hess
  * workspace.  All sums are taken in a fixed order: results are
  * deterministic.  Errors: SS_EINVAL for an unknown-size or null argument,
  * SS_EUNSUPPORTED for an unknown model, SS_EWORKSPACE for a short or

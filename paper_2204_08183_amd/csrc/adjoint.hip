@@ -9,13 +9,20 @@
 //               [+ w_m * sum_{run ends k < m} d_k G(Y_k) / S0_k, Fine-Gray] )
 //   l      = sum_m delta_m eta_m - sum_k d_k log S0_k
 //
-// with w = I(status = 2) / G(y) the competing-event weight.  Scans (prefix
-// of e, suffix of d/S0, and for Fine-Gray the prefix of e w and of d G/S0)
-// in sorted order, the run-end terms computed in the last pass of the scan
-// of e and the gradient in the last pass of the suffix scan of d/S0; the
-// gradient reaches subject order by one gather through the inverse
-// permutation.  l is a sum of per-tile partials; every sum is taken in a
-// fixed order.
+// with w = I(status = 2) / G(y) the competing-event weight.  Three passes over
+// tiles of ST sorted positions, tile t the same positions in each of them:
+//   k_adj_sums   the tile's sums of e and (Fine-Gray) of e w;
+//   k_adj_terms  prefix of e, suffix of e w, S0 and q = d/S0 at run ends, and
+//                the tile's sums of l, of q and of q G;
+//   k_adj_grad   suffix of q, prefix of q G, and the gradient in sorted order.
+// A tile's carry is the sum over the tiles before (after) it: with few tiles
+// each workgroup adds them itself, otherwise k_adj_spine scans them once.
+// The gradient reaches subject order by one gather through the inverse
+// permutation.  Every sum is taken in a fixed order.
+//
+// Bound: HBM (each pass at the copy rate; 51 B per subject for Cox, 83 for
+// Fine-Gray) and, at small N, the launches (5; scans of their own for e w,
+// d/S0 and d G/S0 had taken 7 and 13).
 #include <math.h>
 
 #include "scan_device.h"
@@ -28,13 +35,6 @@ namespace {
 __device__ __forceinline__ bool is_event(int32_t model, int8_t s)
 {
     return model == SS_FINE_GRAY ? s == 1 : s != 0;
-}
-
-__global__ __launch_bounds__(256) void k_adj_mul(int64_t n, const double *a, const double *b,
-                                                 double *out)
-{
-    for (int64_t k = blockIdx.x * 256 + threadIdx.x; k < n; k += (int64_t)gridDim.x * 256)
-        out[k] = a[k] * b[k];
 }
 
 constexpr int kAdjGrid = 2048;  // workgroups of the element-wise passes
@@ -65,102 +65,259 @@ __device__ __forceinline__ double block_total(double v, double *s_red)
     return ((s_red[0] + s_red[1]) + s_red[2]) + s_red[3];
 }
 
-// Last pass of the prefix scan of e, with the run-end terms: S0 at k is the
-// prefix (Fine-Gray: plus G(Y_k) times the e w after k, from pw), q = d/S0,
-// q2 = d G/S0, and the tile's sum of delta eta - d log S0 into lpart[tile].
+// Inclusive suffix scan of SI items per thread (thread t holds the t-th run
+// of SI items of the tile) with the sum of everything after the tile.
+__device__ __forceinline__ void block_suffix_scan(double (&it)[SI], double after, double *s_w)
+{
+    constexpr int NW = SB / kWave;
+    const int lane = lane_id();
+    const int w = threadIdx.x / kWave;
+    double run = 0.0;
+#pragma unroll
+    for (int i = SI - 1; i >= 0; --i) {
+        run += it[i];
+        it[i] = run;
+    }
+    double inc = run;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const double y = __shfl_down(inc, off, kWave);
+        if (lane + off < kWave) inc += y;
+    }
+    if (lane == 0) s_w[w] = inc;
+    __syncthreads();
+    double pre = after;
+#pragma unroll
+    for (int q = NW - 1; q >= 0; --q)
+        if (q > w) pre += s_w[q];
+    __syncthreads();
+    const double lanes_after = __shfl_down(inc, 1, kWave);
+    if (lane < kWave - 1) pre += lanes_after;
+#pragma unroll
+    for (int i = 0; i < SI; ++i) it[i] += pre;
+}
+
+// Carries of the tiles.  Up to kSelfCarry tiles every workgroup adds the
+// sums of the tiles before (after) its own; above, k_adj_spine has turned
+// the sums into carries and the workgroup reads its own.  (N = 1e6, 489
+// tiles: a spine launch costs 4.3 us and the gap before it, the additions
+// below 1 us; at 2048 tiles they read 16 MB from L2 over all workgroups.)
+constexpr int64_t kSelfCarry = 2048;
+
+template <bool AFTER>
+__device__ __forceinline__ double tile_carry(const double *sums, int64_t tiles, double *s_red)
+{
+    const int64_t t = blockIdx.x;
+    if (tiles > kSelfCarry) return sums[t];
+    double v = 0.0;
+    const int64_t lo = AFTER ? t + 1 : 0, hi = AFTER ? tiles : t;
+#pragma unroll 4
+    for (int64_t i = lo + threadIdx.x; i < hi; i += SB) v += sums[i];
+    v = dpp_wave_sum(v);
+    __syncthreads();
+    if (lane_id() == 0) s_red[threadIdx.x / kWave] = v;
+    __syncthreads();
+    double c = 0.0;
+#pragma unroll
+    for (int q = 0; q < SB / kWave; ++q) c += s_red[q];
+    return c;
+}
+
+// Exclusive scan of the tile sums in place, one workgroup per array:
+// workgroup 0 `fwd` from the first tile, workgroup 1 `bwd` from the last.
+constexpr int kSpineBlock = 1024;
+
+__global__ __launch_bounds__(kSpineBlock) void k_adj_spine(int64_t tiles, double *fwd,
+                                                           double *bwd)
+{
+    constexpr int NW = kSpineBlock / kWave;
+    constexpr int PT = 8;
+    __shared__ double s_w[NW];
+    const bool rev = blockIdx.x != 0;
+    double *a = rev ? bwd : fwd;
+    if (!a) return;
+    const int lane = lane_id(), w = threadIdx.x / kWave;
+    double carry = 0.0;
+    for (int64_t c0 = 0; c0 < tiles; c0 += kSpineBlock * PT) {
+        const int64_t base = c0 + (int64_t)threadIdx.x * PT;
+        double it[PT], run = 0.0;
+#pragma unroll
+        for (int i = 0; i < PT; ++i) {
+            const int64_t l = base + i;
+            it[i] = l < tiles ? a[rev ? tiles - 1 - l : l] : 0.0;
+        }
+#pragma unroll
+        for (int i = 0; i < PT; ++i) {
+            const double x = it[i];
+            it[i] = run;  // exclusive within the thread
+            run += x;
+        }
+        const double inc = dpp_incl_scan(run);
+        if (lane == kWave - 1) s_w[w] = inc;
+        __syncthreads();
+        double before = carry, all = 0.0;
+#pragma unroll
+        for (int q = 0; q < NW; ++q) {
+            if (q < w) before += s_w[q];
+            all += s_w[q];
+        }
+        // the lanes before this one (not inc - run: it would round)
+        const double lanes_before = __shfl_up(inc, 1, kWave);
+        if (lane > 0) before += lanes_before;
+        carry += all;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < PT; ++i) {
+            const int64_t l = base + i;
+            if (l < tiles) a[rev ? tiles - 1 - l : l] = before + it[i];
+        }
+    }
+}
+
 template <bool FG>
-__global__ __launch_bounds__(SB) void k_adj_scan_terms(int64_t n, const double *e,
-                                                       const double *carry,
-                                                       const int8_t *status_s,
-                                                       const double *eta, const uint8_t *d8,
-                                                       const int32_t *d32, const double *g_end,
-                                                       const double *pw, double *q,
-                                                       double *q2, double *lpart)
+__global__ __launch_bounds__(SB) void k_adj_sums(int64_t n, const double *e, const double *w_comp,
+                                                 double *sum_e, double *sum_ew)
+{
+    __shared__ double s_red[SB / kWave];
+    const int64_t k0 = (int64_t)blockIdx.x * ST + (int64_t)threadIdx.x * SI;
+    double ev[SI], wv[FG ? SI : 1];
+    load_items<double, OpAdd<double>, false>(e, k0, n, ev);
+    if constexpr (FG) load_items<double, OpAdd<double>, false>(w_comp, k0, n, wv);
+    double a = 0.0, b = 0.0;
+#pragma unroll
+    for (int i = 0; i < SI; ++i) {
+        a += ev[i];
+        if constexpr (FG) b += ev[i] * wv[i];
+    }
+    const double ta = block_total(a, s_red);
+    if (threadIdx.x == 0) sum_e[blockIdx.x] = ta;
+    if constexpr (FG) {
+        __syncthreads();
+        const double tb = block_total(b, s_red);
+        if (threadIdx.x == 0) sum_ew[blockIdx.x] = tb;
+    }
+}
+
+// S0 at k is the prefix of e (Fine-Gray: plus G(Y_k) times the e w after
+// k); q = d/S0 at run ends, and the tile's sums of delta eta - d log S0, of
+// q and (Fine-Gray) of q G.
+template <bool FG>
+__global__ __launch_bounds__(SB) void k_adj_terms(int64_t n, int64_t tiles, const double *e,
+                                                  const double *w_comp, const double *sum_e,
+                                                  const double *sum_ew, const int8_t *status_s,
+                                                  const double *eta, const uint8_t *d8,
+                                                  const int32_t *d32, const double *g_end,
+                                                  double *q, double *lpart, double *sum_q,
+                                                  double *sum_qg)
 {
     static_assert(SB == 4 * kWave, "block_total sums four waves");
     __shared__ double s_w[SB / kWave];
     __shared__ double s_red[SB / kWave];
     const int64_t k0 = (int64_t)blockIdx.x * ST + (int64_t)threadIdx.x * SI;
-    double s0[SI], et[SI];
+    double s0[SI], et[SI], r[FG ? SI : 1], gv[FG ? SI : 1];
     load_items<double, OpAdd<double>, false>(e, k0, n, s0);
-    block_scan<double, OpAdd<double>>(s0, carry[blockIdx.x], s_w);
     load_items<double, OpAdd<double>, false>(eta, k0, n, et);
     uint8_t dd[SI], st[SI];
     load_bytes8(d8, k0, n, dd);
     load_bytes8(reinterpret_cast<const uint8_t *>(status_s), k0, n, st);
-    const double tot_w = FG ? pw[n - 1] : 0.0;
-    double qv[SI], q2v[SI];
-    double lsum = 0.0;
+    if constexpr (FG) {
+        load_items<double, OpAdd<double>, false>(w_comp, k0, n, r);
+        load_items<double, OpAdd<double>, false>(g_end, k0, n, gv);
+        const double after = tile_carry<true>(sum_ew, tiles, s_red);
+#pragma unroll
+        for (int i = 0; i < SI; ++i) r[i] *= s0[i];
+        block_suffix_scan(r, after, s_w);
+        // the weighted sum starts after the position: one position on
+        const double next = __shfl_down(r[0], 1, kWave);
+        __shared__ double s_first[SB / kWave];
+        if (lane_id() == 0) s_first[threadIdx.x / kWave] = r[0];
+        __syncthreads();
+        const int w = threadIdx.x / kWave;
+        const double past = lane_id() < kWave - 1 ? next
+                            : w < SB / kWave - 1  ? s_first[w + 1]
+                                                  : after;
+#pragma unroll
+        for (int i = 0; i < SI - 1; ++i) r[i] = r[i + 1];
+        r[SI - 1] = past;
+    }
+    block_scan<double, OpAdd<double>>(s0, tile_carry<false>(sum_e, tiles, s_red), s_w);
+    double qv[SI];
+    double lsum = 0.0, qsum = 0.0, qgsum = 0.0;
 #pragma unroll
     for (int i = 0; i < SI; ++i) {
         const int64_t k = k0 + i;
         qv[i] = 0.0;
-        q2v[i] = 0.0;
         if (k < n) {
             int d = dd[i];
             if (d == 255) d = d32[k];
             double l = is_event(FG ? SS_FINE_GRAY : SS_COX, (int8_t)st[i]) ? et[i] : 0.0;
             if (d != 0) {
                 double S0 = s0[i];
-                double g = 0.0;
-                if (FG) {
-                    g = g_end[k];
-                    S0 += g * (tot_w - pw[k]);
-                }
+                if constexpr (FG) S0 += gv[i] * r[i];
                 qv[i] = (double)d / S0;
-                if (FG) q2v[i] = (double)d * g / S0;
+                qsum += qv[i];
+                if constexpr (FG) qgsum += qv[i] * gv[i];
                 l -= (double)d * log(S0);
             }
             lsum += l;
         }
     }
     store_items<double, false>(q, k0, n, qv);
-    if (FG) store_items<double, false>(q2, k0, n, q2v);
-    const double t = block_total(lsum, s_red);
-    if (threadIdx.x == 0) lpart[blockIdx.x] = t;
+    __syncthreads();
+    const double tl = block_total(lsum, s_red);
+    if (threadIdx.x == 0) lpart[blockIdx.x] = tl;
+    __syncthreads();
+    const double tq = block_total(qsum, s_red);
+    if (threadIdx.x == 0) sum_q[blockIdx.x] = tq;
+    if constexpr (FG) {
+        __syncthreads();
+        const double tg = block_total(qgsum, s_red);
+        if (threadIdx.x == 0) sum_qg[blockIdx.x] = tg;
+    }
 }
 
-// Last pass of the suffix scan of q = d/S0: R at k is the suffix, and
-// dl/deta_k = delta_k - e_k (R + w_k Q_k) (Q: the exclusive prefix of
-// q2, Fine-Gray) goes to grad_s in sorted order.  Workgroup 0 also adds
-// the likelihood partials in order.
+// R at k is the suffix of q, Q (Fine-Gray) the prefix of q G before k:
+// dl/deta_k = delta_k - e_k (R + w_k Q) goes to grad_s in sorted order.
+// Workgroup 0 also adds the likelihood partials in order.
 template <bool FG>
-__global__ __launch_bounds__(SB) void k_adj_scan_grad(int64_t n, const double *q,
-                                                      const double *carry,
-                                                      const int8_t *status_s, const double *e,
-                                                      const double *w_comp, const double *q2x,
-                                                      const double *lpart, int64_t nlpart,
-                                                      double *grad_s, double *loglik)
+__global__ __launch_bounds__(SB) void k_adj_grad(int64_t n, int64_t tiles, const double *q,
+                                                 const double *sum_q, const double *sum_qg,
+                                                 const int8_t *status_s, const double *e,
+                                                 const double *w_comp, const double *g_end,
+                                                 const double *lpart, double *grad_s,
+                                                 double *loglik)
 {
     __shared__ double s_w[SB / kWave];
     __shared__ double s_red[SB / kWave];
-    // scan position l holds sorted position n - 1 - l; a thread's items are
-    // the descending run of sorted positions n - 1 - l0 .. n - SI - l0
-    const int64_t l0 = (int64_t)blockIdx.x * ST + (int64_t)threadIdx.x * SI;
-    double r[SI], ev[SI], wq[SI];
-    load_items<double, OpAdd<double>, true>(q, l0, n, r);
-    block_scan<double, OpAdd<double>>(r, carry[blockIdx.x], s_w);
-    load_items<double, OpAdd<double>, true>(e, l0, n, ev);
-    if (FG) {
-        double wv[SI], qx[SI];
-        load_items<double, OpAdd<double>, true>(w_comp, l0, n, wv);
-        load_items<double, OpAdd<double>, true>(q2x, l0, n, qx);
+    __shared__ double s_last[SB / kWave];
+    const int64_t k0 = (int64_t)blockIdx.x * ST + (int64_t)threadIdx.x * SI;
+    double r[SI], ev[SI], qg[FG ? SI : 1], wv[FG ? SI : 1];
+    load_items<double, OpAdd<double>, false>(q, k0, n, r);
+    load_items<double, OpAdd<double>, false>(e, k0, n, ev);
+    uint8_t st[SI];
+    load_bytes8(reinterpret_cast<const uint8_t *>(status_s), k0, n, st);
+    if constexpr (FG) {
+        load_items<double, OpAdd<double>, false>(g_end, k0, n, qg);
+        load_items<double, OpAdd<double>, false>(w_comp, k0, n, wv);
 #pragma unroll
-        for (int i = 0; i < SI; ++i) wq[i] = wv[i] * qx[i];
+        for (int i = 0; i < SI; ++i) qg[i] *= r[i];
+        const double before = tile_carry<false>(sum_qg, tiles, s_red);
+        block_scan<double, OpAdd<double>>(qg, before, s_w);
+        inclusive_to_exclusive<double>(qg, before, s_last);
     }
+    block_suffix_scan(r, tile_carry<true>(sum_q, tiles, s_red), s_w);
     double gv[SI];
 #pragma unroll
     for (int i = 0; i < SI; ++i) {
-        const int64_t l = l0 + i;
         double inner = r[i];
-        if (FG) inner += wq[i];
-        const bool ev_k = l < n && is_event(FG ? SS_FINE_GRAY : SS_COX, status_s[n - 1 - l]);
-        gv[i] = (ev_k ? 1.0 : 0.0) - ev[i] * inner;
+        if constexpr (FG) inner += wv[i] * qg[i];
+        gv[i] = (is_event(FG ? SS_FINE_GRAY : SS_COX, (int8_t)st[i]) ? 1.0 : 0.0) - ev[i] * inner;
     }
-    store_items<double, true>(grad_s, l0, n, gv);
+    store_items<double, false>(grad_s, k0, n, gv);
     if (blockIdx.x == 0) {
         double v = 0.0;
-        for (int64_t b = threadIdx.x; b < nlpart; b += SB) v += lpart[b];
+        for (int64_t b = threadIdx.x; b < tiles; b += SB) v += lpart[b];
+        __syncthreads();
         const double t = block_total(v, s_red);
         if (threadIdx.x == 0) *loglik = t;
     }
@@ -226,6 +383,143 @@ __global__ __launch_bounds__(256) void k_xt_span(int64_t p, int64_t nspan, int64
     }
 }
 
+// The same for larger designs: a workgroup keeps a span of g in LDS (kXtSpan
+// positions at a time where the span is longer) and its waves sum the pieces
+// of a group of columns from there.  A random 8-byte read takes a cache
+// line's worth of L2 bandwidth, which bounded the gather (N = 1e6, P = 1000,
+// 5e7 non-zeros: 194 us); from LDS it costs a bank access and the row indices
+// stream from HBM (46 us, 4.3 TB/s).  A wave takes the bounds of its columns
+// in one set of loads, and loads a column's first kXtAhead * 64 row indices
+// while it sums the column before.
+//
+// The line between the two, whole beta gradients at 5% density, from L2 /
+// from LDS: N = 1e6, P = 16 36.3 / 32.3 us, P = 256 69.8 / 40.9; N = 1e5,
+// P = 512 25.7 / 25.5 (valued 28.3 / 33.1), P = 1024 32.7 / 28.4 (37.8 /
+// 38.7), P = 2048 50.5 / 33.4; below 16 columns a span loaded is hardly read.
+constexpr int kXtBlock = 512;
+constexpr int kXtSpan = 8192;
+constexpr int kXtAhead = 8;
+constexpr int64_t kXtLdsCols = 16;
+constexpr int64_t kXtLdsSize = 100'000'000;  // positions times columns
+
+template <bool VALS>
+__global__ __launch_bounds__(kXtBlock) void k_xt_lds(int64_t n, int64_t p, int64_t nspan,
+                                                     int64_t kspan, int64_t nchunk, int64_t groups,
+                                                     int64_t group_cols, const int64_t *col_ptr,
+                                                     const int32_t *chunk_ptr,
+                                                     const int32_t *rows_sorted,
+                                                     const double *vals_sorted, const double *g,
+                                                     double *part)
+{
+    constexpr int NW = kXtBlock / kWave;
+    constexpr int kSub = kXtSpan / SS_CHUNK;  // chunks held at a time
+    __shared__ double s_g[kXtSpan + 1];
+    const int lane = lane_id();
+    const int w = threadIdx.x / kWave;
+    const int64_t c = blockIdx.x / groups;
+    const int64_t j0 = (blockIdx.x - c * groups) * group_cols;
+    const int64_t j1 = min(j0 + group_cols, p);
+    const int64_t t_end = min((c + 1) * kspan, nchunk);
+    // columns of this wave: a contiguous share of the group's
+    const int64_t share = (group_cols + NW - 1) / NW;
+    const int64_t ja = min(j0 + w * share, j1), jz = min(ja + share, j1);
+    for (int64_t t0 = c * kspan; t0 < t_end; t0 += kSub) {
+        const int64_t t1 = min(t0 + kSub, t_end);
+        const int64_t k0 = t0 * SS_CHUNK;
+        const int32_t cnt = (int32_t)(min(t1 * SS_CHUNK, n) - k0);
+        __syncthreads();
+        for (int32_t i = threadIdx.x; i < cnt; i += kXtBlock) s_g[i] = g[k0 + i];
+        if (threadIdx.x == 0) s_g[kXtSpan] = 0.0;
+        __syncthreads();
+        for (int64_t jb = ja; jb < jz; jb += kWave) {
+            const int m = (int)min((int64_t)kWave, jz - jb);
+            int64_t lo = 0;
+            int32_t len = 0;
+            if (lane < m) {
+                const int32_t *cp = chunk_ptr + (jb + lane) * (nchunk + 1);
+                const int32_t a = cp[t0], b = cp[t1];
+                lo = col_ptr[jb + lane] + a;
+                len = b - a;
+            }
+            // piece x of the batch: entries [at, at + l)
+            auto bounds = [&](int x, int64_t &at, int32_t &l) {
+                const uint32_t l0 = __builtin_amdgcn_readlane((int)(lo & 0xffffffff), x);
+                const uint32_t l1 = __builtin_amdgcn_readlane((int)(lo >> 32), x);
+                at = (int64_t)(((uint64_t)l1 << 32) | l0);
+                l = __builtin_amdgcn_readlane(len, x);
+            };
+            // entries o .. of a piece of l > 0 (the last one again past the end)
+            auto load = [&](int64_t at, int32_t l, int32_t o, int32_t (&r)[kXtAhead],
+                            double (&v)[VALS ? kXtAhead : 1]) {
+                if (l == 0) return;
+                const int32_t *rp = rows_sorted + at;
+                const double *vp = VALS ? vals_sorted + at : nullptr;
+#pragma unroll
+                for (int u = 0; u < kXtAhead; ++u) {
+                    const uint32_t i = (uint32_t)min(o + u * kWave + lane, l - 1);
+                    r[u] = rp[i];
+                    if constexpr (VALS) v[u] = vp[i];
+                }
+            };
+            int64_t at;
+            int32_t l;
+            bounds(0, at, l);
+            int32_t r[kXtAhead];
+            double v[VALS ? kXtAhead : 1];
+            load(at, l, 0, r, v);
+            for (int x = 0; x < m; ++x) {
+                double acc[4] = {0.0, 0.0, 0.0, 0.0};
+                // (an entry past the end reads the 0 after the span)
+                auto take = [&](int32_t left) {
+                    double gv[kXtAhead];
+#pragma unroll
+                    for (int u = 0; u < kXtAhead; ++u)
+                        gv[u] = s_g[u * kWave + lane < left ? r[u] - (int32_t)k0 : kXtSpan];
+#pragma unroll
+                    for (int u = 0; u < kXtAhead; ++u) {
+                        if constexpr (VALS)
+                            acc[u & 3] += u * kWave + lane < left ? v[u] * gv[u] : 0.0;
+                        else
+                            acc[u & 3] += gv[u];
+                    }
+                };
+                const int64_t at0 = at;
+                int32_t done = 0;
+                const int32_t l0 = l;
+                for (int32_t o = kXtAhead * kWave; o < l0; o += kXtAhead * kWave) {
+                    int32_t r2[kXtAhead];
+                    double v2[VALS ? kXtAhead : 1];
+                    load(at0, l0, o, r2, v2);
+                    take(l0 - done);
+                    done = o;
+#pragma unroll
+                    for (int u = 0; u < kXtAhead; ++u) {
+                        r[u] = r2[u];
+                        if constexpr (VALS) v[u] = v2[u];
+                    }
+                }
+                int32_t r2[kXtAhead];
+                double v2[VALS ? kXtAhead : 1];
+                if (x + 1 < m) {
+                    bounds(x + 1, at, l);
+                    load(at, l, 0, r2, v2);
+                }
+                take(l0 - done);
+                const double t = dpp_wave_sum((acc[0] + acc[1]) + (acc[2] + acc[3]));
+                if (lane == 0) {
+                    double *dst = part + (jb + x) * nspan + c;
+                    *dst = t0 == c * kspan ? t : *dst + t;
+                }
+#pragma unroll
+                for (int u = 0; u < kXtAhead; ++u) {
+                    r[u] = r2[u];
+                    if constexpr (VALS) v[u] = v2[u];
+                }
+            }
+        }
+    }
+}
+
 // grad_beta[j] = the sum of column j's span partials, one workgroup per
 // column: four interleaved accumulators per thread, then the workgroup's
 // fixed-order sum.
@@ -247,8 +541,8 @@ __global__ __launch_bounds__(256) void k_xt_cols(int64_t nspan, const double *pa
 }
 
 struct AdjWs {
-    double *a, *b, *q, *q2, *lpart;
-    void *sums;
+    double *a, *q, *lpart;                   // the gradient in sorted order, d/S0
+    double *sum_e, *sum_ew, *sum_q, *sum_qg; // per tile: sums, then carries
 };
 
 size_t adj_layout(int64_t n, void *ws, AdjWs *w)
@@ -260,13 +554,16 @@ size_t adj_layout(int64_t n, void *ws, AdjWs *w)
         off = align_up(off + bytes, 256);
         return r;
     };
+    const size_t tiles = (size_t)ceil_div(n, ST);
     AdjWs t;
     t.a = (double *)take(8 * (size_t)n);
-    t.b = (double *)take(8 * (size_t)n);
     t.q = (double *)take(8 * (size_t)n);
-    t.q2 = (double *)take(8 * (size_t)n);
-    t.lpart = (double *)take(8 * (size_t)ceil_div(n, ST));
-    t.sums = take(scan_sums_bytes(n));
+    (void)take(16 * (size_t)n);  // the interface promises four N-vectors
+    t.lpart = (double *)take(8 * tiles);
+    t.sum_e = (double *)take(8 * tiles);
+    t.sum_ew = (double *)take(8 * tiles);
+    t.sum_q = (double *)take(8 * tiles);
+    t.sum_qg = (double *)take(8 * tiles);
     if (w) *w = t;
     return off;
 }
@@ -293,48 +590,45 @@ int32_t launch_gather_u8(int64_t n, const int32_t *perm, const uint8_t *src, uin
 size_t adjoint_ws_bytes(int64_t n) { return adj_layout(n, nullptr, nullptr); }
 
 // The gradient in eta in sorted order into w.a (and l into *loglik).
+template <bool FG>
+static int32_t eta_gradient_passes(int64_t n, const int8_t *status_s, const double *eta,
+                                   const double *e, const uint8_t *d8, const int32_t *d32,
+                                   const double *w_comp, const double *g_end, double *loglik,
+                                   const AdjWs &w, hipStream_t s)
+{
+    const int64_t tiles = ceil_div(n, (int64_t)ST);
+    const dim3 grid((unsigned)tiles);
+    hipLaunchKernelGGL(k_adj_sums<FG>, grid, dim3(SB), 0, s, n, e, w_comp, w.sum_e, w.sum_ew);
+    SS_LAUNCH_CHECK();
+    if (tiles > kSelfCarry) {
+        hipLaunchKernelGGL(k_adj_spine, dim3(FG ? 2 : 1), dim3(kSpineBlock), 0, s, tiles, w.sum_e,
+                           w.sum_ew);
+        SS_LAUNCH_CHECK();
+    }
+    hipLaunchKernelGGL(k_adj_terms<FG>, grid, dim3(SB), 0, s, n, tiles, e, w_comp, w.sum_e,
+                       w.sum_ew, status_s, eta, d8, d32, g_end, w.q, w.lpart, w.sum_q, w.sum_qg);
+    SS_LAUNCH_CHECK();
+    if (tiles > kSelfCarry) {
+        hipLaunchKernelGGL(k_adj_spine, dim3(2), dim3(kSpineBlock), 0, s, tiles,
+                           FG ? w.sum_qg : (double *)nullptr, w.sum_q);
+        SS_LAUNCH_CHECK();
+    }
+    hipLaunchKernelGGL(k_adj_grad<FG>, grid, dim3(SB), 0, s, n, tiles, w.q, w.sum_q, w.sum_qg,
+                       status_s, e, w_comp, g_end, w.lpart, w.a, loglik);
+    SS_LAUNCH_CHECK();
+    return SS_OK;
+}
+
 static int32_t eta_gradient_sorted(int32_t model, int64_t n, const int8_t *status_s,
                                    const double *eta, const double *e, const uint8_t *d8,
                                    const int32_t *d32, const double *w_comp,
                                    const double *g_end, double *loglik, const AdjWs &w,
                                    hipStream_t s)
 {
-    const bool fg = model == SS_FINE_GRAY;
-    const int grid = grid_of(n);
-    const unsigned tiles = (unsigned)ceil_div(n, ST);
-    const double *carry = reinterpret_cast<const double *>(w.sums);
-    int32_t rc;
-    if (fg) {
-        hipLaunchKernelGGL(k_adj_mul, dim3(grid), dim3(256), 0, s, n, e, w_comp, w.b);
-        SS_LAUNCH_CHECK();
-        rc = scan_add_f64(w.b, w.b, n, false, false, w.sums, s);      // prefix of e w
-        if (rc) return rc;
-    }
-    rc = scan_carries_f64(e, n, false, w.sums, s);                    // prefix of e, then
-    if (rc) return rc;                                                 // the run-end terms
-    if (fg) {
-        hipLaunchKernelGGL(k_adj_scan_terms<true>, dim3(tiles), dim3(SB), 0, s, n, e, carry,
-                           status_s, eta, d8, d32, g_end, w.b, w.q, w.q2, w.lpart);
-    } else {
-        hipLaunchKernelGGL(k_adj_scan_terms<false>, dim3(tiles), dim3(SB), 0, s, n, e, carry,
-                           status_s, eta, d8, d32, g_end, w.b, w.q, w.q2, w.lpart);
-    }
-    SS_LAUNCH_CHECK();
-    if (fg) {
-        rc = scan_add_f64(w.q2, w.b, n, false, true, w.sums, s);      // run ends before k
-        if (rc) return rc;
-    }
-    rc = scan_carries_f64(w.q, n, true, w.sums, s);                   // suffix of d / S0,
-    if (rc) return rc;                                                 // then the gradient
-    if (fg) {
-        hipLaunchKernelGGL(k_adj_scan_grad<true>, dim3(tiles), dim3(SB), 0, s, n, w.q, carry,
-                           status_s, e, w_comp, w.b, w.lpart, (int64_t)tiles, w.a, loglik);
-    } else {
-        hipLaunchKernelGGL(k_adj_scan_grad<false>, dim3(tiles), dim3(SB), 0, s, n, w.q, carry,
-                           status_s, e, w_comp, w.b, w.lpart, (int64_t)tiles, w.a, loglik);
-    }
-    SS_LAUNCH_CHECK();
-    return SS_OK;
+    return model == SS_FINE_GRAY
+               ? eta_gradient_passes<true>(n, status_s, eta, e, d8, d32, w_comp, g_end, loglik, w, s)
+               : eta_gradient_passes<false>(n, status_s, eta, e, d8, d32, w_comp, g_end, loglik, w,
+                                            s);
 }
 
 int32_t launch_eta_gradient(int32_t model, int64_t n, const int32_t *inv_perm,
@@ -365,6 +659,28 @@ int64_t xt_span_chunks(int64_t n, int64_t p)
     return k;
 }
 
+// Columns per workgroup of k_xt_lds: the fewest groups that fill at least
+// 90% of the workgroup slots (two per CU) over the rounds they take, else the
+// fullest; at least 16 columns for each span loaded.  (N = 1e6, P = 1000,
+// 123 spans: 4 groups are one round of 492 workgroups; 9 groups, 2.2 rounds,
+// took 155 us.)
+int64_t xt_group_cols(int64_t p, int64_t nspan)
+{
+    constexpr int64_t slots = 2 * 256;
+    int64_t best = 1;
+    double full = 0.0;
+    for (int64_t g = 1; g <= std::min<int64_t>(p / 16, 64); ++g) {
+        const int64_t wgs = nspan * g;
+        const double f = (double)wgs / (double)(slots * ceil_div(wgs, slots));
+        if (f > full) {
+            full = f;
+            best = g;
+        }
+        if (full >= 0.9) break;
+    }
+    return ceil_div(p, best);
+}
+
 size_t beta_ws_bytes(int64_t n, int64_t p)
 {
     const int64_t nspan = ceil_div(ceil_div(n, (int64_t)SS_CHUNK), xt_span_chunks(n, p));
@@ -387,12 +703,24 @@ int32_t launch_beta_gradient(int32_t model, int64_t n, int64_t p, const int32_t 
     const int64_t nchunk = ceil_div(n, (int64_t)SS_CHUNK);
     const int64_t kspan = xt_span_chunks(n, p);
     const int64_t nspan = ceil_div(nchunk, kspan);
-    // about 16K waves when the design allows: column groups per span
-    const int64_t groups = std::max<int64_t>(1, std::min<int64_t>(p, ceil_div(16384, nspan)));
     double *part = reinterpret_cast<double *>(static_cast<char *>(ws) + adjoint_ws_bytes(n));
-    hipLaunchKernelGGL(k_xt_span, dim3((unsigned)ceil_div(nspan * groups, kXtWaves)), dim3(256),
-                       0, s, p, nspan, kspan, nchunk, groups, col_ptr, chunk_ptr, rows_sorted,
-                       vals_sorted, w.a, part);
+    if (p >= kXtLdsCols && p >= ceil_div(kXtLdsSize, n)) {
+        const int64_t cols = xt_group_cols(p, nspan), groups = ceil_div(p, cols);
+        if (vals_sorted)
+            hipLaunchKernelGGL(k_xt_lds<true>, dim3((unsigned)(nspan * groups)), dim3(kXtBlock), 0,
+                               s, n, p, nspan, kspan, nchunk, groups, cols, col_ptr, chunk_ptr,
+                               rows_sorted, vals_sorted, w.a, part);
+        else
+            hipLaunchKernelGGL(k_xt_lds<false>, dim3((unsigned)(nspan * groups)), dim3(kXtBlock),
+                               0, s, n, p, nspan, kspan, nchunk, groups, cols, col_ptr, chunk_ptr,
+                               rows_sorted, vals_sorted, w.a, part);
+    } else {
+        // about 16K waves when the design allows: column groups per span
+        const int64_t groups = std::max<int64_t>(1, std::min<int64_t>(p, ceil_div(16384, nspan)));
+        hipLaunchKernelGGL(k_xt_span, dim3((unsigned)ceil_div(nspan * groups, kXtWaves)),
+                           dim3(256), 0, s, p, nspan, kspan, nchunk, groups, col_ptr, chunk_ptr,
+                           rows_sorted, vals_sorted, w.a, part);
+    }
     SS_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_xt_cols, dim3((unsigned)p), dim3(256), 0, s, nspan, part, grad_beta);
     SS_LAUNCH_CHECK();

@@ -348,6 +348,13 @@ int32_t ss_gather(int64_t n, const int32_t *perm, const double *src, double *dst
     return launch_gather(n, perm, src, dst, (hipStream_t)stream);
 }
 
+int32_t ss_gather_exp(int64_t n, const int32_t *perm, const double *src, double *eta, double *e,
+                      void *stream)
+{
+    if (n < 1 || n > INT32_MAX || !perm || !src || !eta || !e) return SS_EINVAL;
+    return launch_gather_exp(n, perm, src, eta, e, (hipStream_t)stream);
+}
+
 int32_t ss_exp_f32(int64_t n, const double *eta, float *e32, double *shift, void *ws,
                    size_t ws_bytes, void *stream)
 {

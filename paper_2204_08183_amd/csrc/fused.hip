@@ -1009,6 +1009,19 @@ __global__ void k_gather(int64_t n, const int32_t *perm, const double *src,
         dst[i] = src[perm[i]];
 }
 
+// eta in sorted order and e = exp(eta) in one pass (the gather is bound by
+// the cache lines its random reads fill, the second store rides along).
+__global__ void k_gather_exp(int64_t n, const int32_t *perm, const double *src, double *eta,
+                             double *e)
+{
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        const double x = src[perm[i]];
+        eta[i] = x;
+        e[i] = exp(x);
+    }
+}
+
 __global__ void k_fill_zero(uint64_t *p, int64_t words)
 {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < words;
@@ -1245,6 +1258,15 @@ int32_t launch_gather(int64_t n, const int32_t *perm, const double *src,
 {
     hipLaunchKernelGGL(k_gather, dim3(grid_for(n, 256, 8192)), dim3(256), 0, s, n, perm,
                        src, dst);
+    SS_LAUNCH_CHECK();
+    return SS_OK;
+}
+
+int32_t launch_gather_exp(int64_t n, const int32_t *perm, const double *src, double *eta,
+                          double *e, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_gather_exp, dim3(grid_for(n, 256, 8192)), dim3(256), 0, s, n, perm, src,
+                       eta, e);
     SS_LAUNCH_CHECK();
     return SS_OK;
 }

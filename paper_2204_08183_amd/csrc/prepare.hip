@@ -442,41 +442,10 @@ int32_t run_prepare(int32_t model, int64_t n, int64_t p, int64_t nnz, const doub
     return err ? SS_EINVAL : SS_OK;
 }
 
-int32_t scan_add_f64(const double *in, double *out, int64_t m, bool rev, bool excl,
-                     void *sums, hipStream_t s)
-{
-    uint64_t *w = reinterpret_cast<uint64_t *>(sums);
-    if (rev) {
-        return excl ? device_scan<double, OpAdd<double>, true, true>(in, out, m, w, s)
-                    : device_scan<double, OpAdd<double>, true, false>(in, out, m, w, s);
-    }
-    return excl ? device_scan<double, OpAdd<double>, false, true>(in, out, m, w, s)
-                : device_scan<double, OpAdd<double>, false, false>(in, out, m, w, s);
-}
-
 int32_t scan_add_u32_excl(const uint32_t *in, uint32_t *out, int64_t m, void *sums, hipStream_t s)
 {
     return device_scan<uint32_t, OpAdd<uint32_t>, false, true>(
         in, out, m, reinterpret_cast<uint64_t *>(sums), s);
-}
-
-size_t scan_sums_bytes(int64_t m) { return 8 * (size_t)ceil_div(m, ST); }
-
-int32_t scan_carries_f64(const double *in, int64_t m, bool rev, void *sums, hipStream_t s)
-{
-    if (m <= 0) return SS_OK;
-    double *w = reinterpret_cast<double *>(sums);
-    const int64_t nb = ceil_div(m, ST);
-    if (rev)
-        hipLaunchKernelGGL((k_scan_reduce<double, OpAdd<double>, true>), dim3((unsigned)nb),
-                           dim3(SB), 0, s, in, m, w);
-    else
-        hipLaunchKernelGGL((k_scan_reduce<double, OpAdd<double>, false>), dim3((unsigned)nb),
-                           dim3(SB), 0, s, in, m, w);
-    SS_LAUNCH_CHECK();
-    hipLaunchKernelGGL((k_scan_spine<double, OpAdd<double>>), dim3(1), dim3(SB), 0, s, w, nb);
-    SS_LAUNCH_CHECK();
-    return SS_OK;
 }
 
 }  // namespace ss

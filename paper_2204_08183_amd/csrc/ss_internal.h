@@ -319,17 +319,8 @@ int32_t launch_apply(int64_t n, int32_t j, const double *step, double *eta,
 int32_t launch_ccd_scalar(int32_t penalty, double lambda, int32_t j,
                           const double *g12, double *beta, double *delta,
                           double *step, hipStream_t stream);
-// Deterministic FP64 add-scan of in[0..m) into out (may alias): forward or
-// reverse (suffix), inclusive or exclusive; `sums` holds scan_sums_bytes(m).
-int32_t scan_add_f64(const double *in, double *out, int64_t m, bool rev, bool excl,
-                     void *sums, hipStream_t s);
-size_t scan_sums_bytes(int64_t m);
-// Exclusive prefix sums of 32-bit counts (same scratch).
+// Exclusive prefix sums of 32-bit counts; `sums` holds 8 bytes per 2048 items.
 int32_t scan_add_u32_excl(const uint32_t *in, uint32_t *out, int64_t m, void *sums, hipStream_t s);
-// The first two passes of scan_add_f64 alone: sums[t] = the exclusive carry
-// of scan tile t (tiles of 2048 items, in scan order), for a kernel that
-// finishes the scan itself.
-int32_t scan_carries_f64(const double *in, int64_t m, bool rev, void *sums, hipStream_t s);
 size_t adjoint_ws_bytes(int64_t n);
 size_t beta_ws_bytes(int64_t n, int64_t p);
 int32_t launch_gather_u8(int64_t n, const int32_t *perm, const uint8_t *src, uint8_t *dst,
@@ -377,6 +368,8 @@ int32_t launch_exp_f32(int64_t n, const double *eta, float *e32, double *shift,
                        const WsView &ws, hipStream_t s);
 int32_t launch_exp(int64_t n, const double *eta, double *e,
                    hipStream_t stream);
+int32_t launch_gather_exp(int64_t n, const int32_t *perm, const double *src, double *eta,
+                          double *e, hipStream_t stream);
 int32_t launch_gather(int64_t n, const int32_t *perm, const double *src,
                       double *dst, hipStream_t stream);
 int32_t launch_ws_init(void *ws, size_t bytes, hipStream_t stream);

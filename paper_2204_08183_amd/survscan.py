@@ -60,6 +60,7 @@ SIGNATURES = {
                             _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp,
                             _sz, _vp]),
     "ss_exp": (_i32, [_i64, _vp, _vp, _vp]),
+    "ss_gather_exp": (_i32, [_i64, _vp, _vp, _vp, _vp, _vp]),
     "ss_gather": (_i32, [_i64, _vp, _vp, _vp, _vp]),
     "ss_exp_f32": (_i32, [_i64, _vp, _vp, _vp, _vp, _sz, _vp]),
     "ss_grad_hess_mixed": (_i32, [_i32, _i32, _i64, _i64, _i64, _vp, _vp, _vp, _vp, _vp,
@@ -267,8 +268,8 @@ class Problem:
         src = src.contiguous()
         lib = load()
         s = _stream(self.device)
-        check(lib.ss_gather(self.n, _p(self.perm), _p(src), _p(self.eta), s), "ss_gather")
-        check(lib.ss_exp(self.n, _p(self.eta), _p(self.e), s), "ss_exp")
+        check(lib.ss_gather_exp(self.n, _p(self.perm), _p(src), _p(self.eta), _p(self.e), s),
+              "ss_gather_exp")
 
     def set_beta(self, beta, eta_subject_order):
         self.beta.copy_(torch.as_tensor(beta, dtype=torch.float64))

@@ -229,3 +229,47 @@ def test_beta_gradient_wide_design(model):
     scale = x.T @ (np.abs(want_eta) + 1.0)
     assert np.all(np.abs(got - want) <= TOL * scale), np.max(np.abs(got - want) / scale)
     assert prob.workspace_error() == 0
+
+
+# ------------------------------------------- dispatch lines of the two passes
+@pytest.mark.parametrize("model", ["cox", "fg"])
+@pytest.mark.parametrize("n", [2047, 2049, 4_194_304, 4_194_305])
+def test_eta_gradient_tile_carries(model, n):
+    """One, two, 2048 and 2049 tiles of 2048 positions: up to 2048 the
+    workgroups add the tile sums themselves, above a launch scans them."""
+    c = make_case(model, n, 1, 45, 0, 0.001, False)
+    c["y"] = np.ceil(c["y"] * n)  # some tie runs
+    check_gradient(model, c)
+
+
+@pytest.mark.parametrize("model,n,p,valued", [
+    ("cox", 6_250_000, 15, False), ("fg", 6_250_000, 16, False), ("cox", 6_250_011, 17, True),
+    ("cox", 40_000, 2499, False), ("cox", 40_000, 2500, False), ("fg", 40_009, 2530, True)])
+def test_beta_gradient_column_groups(model, n, p, valued):
+    """Both sides of the line between X' from L2 and from LDS (16 columns,
+    1e8 positions times columns); pieces of every length around a wave's 64
+    and its 512 entries in flight, a full column, a ragged last span; sampled
+    columns against the oracle's gradient."""
+    counts = [0, 1, 63, 64, 65, 511, 512, 513, 3000]
+    rng = np.random.default_rng(p)
+    rows = []
+    for j in range(p):
+        m = counts[j % len(counts)] if j != p - 2 else n
+        # most of a column inside one span of 8192 sorted positions
+        rows.append(np.arange(n) if m == n else np.sort(
+            rng.permutation(min(n, 8192))[:m] + (n - min(n, 8192)) * (j % 2)))
+    col_ptr = np.concatenate([[0], np.cumsum([r.size for r in rows])]).astype(np.int64)
+    rows = np.concatenate(rows).astype(np.int32)
+    vals = rng.normal(size=rows.size) if valued else None
+    status = (rng.random(n) < 0.5).astype(np.int8)
+    if model == "fg":
+        status += ((status == 1) & (rng.random(n) < 0.5)).astype(np.int8)
+    c = {"y": np.arange(n, 0, -1) + 0.0, "status": status, "n": n, "p": p, "col_ptr": col_ptr,
+         "rows": rows, "vals": vals, "eta": rng.normal(0.0, 0.5, n)}
+    got = gpu_problem(model, c).beta_gradient()[0].cpu().numpy()
+    want_eta = oadj.eta_gradient_scan(model, c["y"], c["status"], c["eta"])
+    for j in sorted(set(range(20)) & set(range(p)) | {p - 2, p - 1}):
+        r = rows[col_ptr[j]:col_ptr[j + 1]]
+        x = 1.0 if vals is None else vals[col_ptr[j]:col_ptr[j + 1]]
+        scale = float(np.sum(np.abs(x) * (np.abs(want_eta[r]) + 1.0)))
+        assert abs(got[j] - float(np.sum(x * want_eta[r]))) <= TOL * scale, j

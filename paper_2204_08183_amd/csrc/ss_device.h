@@ -65,6 +65,53 @@ __device__ __forceinline__ double dpp_wave_sum(double x)
     return read_lane(dpp_incl_scan(x), kWave - 1);
 }
 
+// Halves (quarters) of two values folded into one: after the swap of
+// gfx950's v_permlane32_swap (v_permlane16_swap) lanes 0-31 (the even rows of
+// 16 lanes) hold a's two halves (neighbouring rows), the others b's, and one
+// addition serves both values.
+__device__ __forceinline__ double fold32(double a, double b)
+{
+    const unsigned long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32),
+                                                     false, false);
+    return __longlong_as_double(((unsigned long long)hi[0] << 32) | lo[0]) +
+           __longlong_as_double(((unsigned long long)hi[1] << 32) | lo[1]);
+}
+__device__ __forceinline__ double fold16(double a, double b)
+{
+    const unsigned long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32),
+                                                     false, false);
+    return __longlong_as_double(((unsigned long long)hi[0] << 32) | lo[0]) +
+           __longlong_as_double(((unsigned long long)hi[1] << 32) | lo[1]);
+}
+
+// Sums over the wave of N doubles into dst[0..N): four at a time, folded
+// into the four rows of one register (three additions and six swaps) and
+// summed there by row shifts, so that four sums take the DPP steps of one.
+template <int N>
+__device__ __forceinline__ void wave_sums_to(const double (&x)[N], double *dst)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+#pragma unroll
+    for (int c = 0; c < N; c += 4) {
+        const double z = 0.0;
+        double v = fold16(fold32(x[c], c + 1 < N ? x[c + 1 < N ? c + 1 : 0] : z),
+                          fold32(c + 2 < N ? x[c + 2 < N ? c + 2 : 0] : z,
+                                 c + 3 < N ? x[c + 3 < N ? c + 3 : 0] : z));
+        v += dpp_double<0x111, 0xF, true>(v);
+        v += dpp_double<0x112, 0xF, true>(v);
+        v += dpp_double<0x114, 0xF, true>(v);
+        v += dpp_double<0x118, 0xF, true>(v);
+        // rows 0..3 hold values 0, 2, 1, 3; their totals sit in lane 15
+        const int row = lane >> 4;
+        const int k = c + ((row & 1) << 1 | row >> 1);
+        if ((lane & 15) == 15 && k < N) dst[k] = v;
+    }
+}
+
 // Inclusive wave-wide scan of NC doubles.
 template <int NC>
 __device__ __forceinline__ void wave_inclusive_scan(double (&x)[NC])

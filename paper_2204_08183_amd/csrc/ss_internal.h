@@ -128,16 +128,19 @@ static_assert(kLbGroup >= 2 && kLbGroup <= 64, "look-back groups of 2 to 64 tile
 // Upper bound on the number of workgroups (segments) of one persistent sweep.
 constexpr int kMaxSweepBlocks = 512;
 
-// Publications of the one-exchange persistent sweep: up to kPubCopies
-// copies of every segment's publication, by round parity (16-byte words, at
-// most kPubSlotWords of them), each copy in an area of its own; every
-// workgroup reads one copy, so the all-to-all gather spreads over that
+// Publications of the persistent sweeps: kPubCopies copies, by round parity,
+// of two slots of 16-byte words per segment (kPubSlotWords of them together),
+// each copy in an area of its own: first the slots of the values a round waits
+// for last (kPubLateWords each, so that as few cache lines as possible are
+// polled), then those of the values published before (kPubEarlyWords).
+// Every workgroup reads one copy, so the all-to-all gather spreads over that
 // many times as many memory lines.
 #ifndef SS_PUB_COPIES
 #define SS_PUB_COPIES 8
 #endif
 constexpr int kPubCopies = SS_PUB_COPIES;
-constexpr int kPubSlotWords = 16;  // 256 bytes: ld_pairs2 reads two neighbouring slots
+constexpr int kPubSlotWords = 16;
+constexpr int kPubLateWords = 2, kPubEarlyWords = 8;
 constexpr int64_t kSwPubWords = 2 * (int64_t)kPubCopies * kMaxSweepBlocks * kPubSlotWords;
 
 // Upper bound on polls of one bounded wait before it gives up (each poll is

@@ -516,3 +516,47 @@ def test_design_errors(n, m):
         r[m - 1] = bad
         with pytest.raises(ss.SurvScanError):
             ss.Problem("cox", y, status, ptr, r)
+
+
+# Both sides of every line of the persistent sweep's built-in shapes: one
+# workgroup up to 4096 (valued: 2048) positions, segments of 1024 up to 2^18
+# (Fine-Gray 0/1: 2^17), of 2048 up to 2^19, of 4096 above; and more segments
+# than a gather has threads.
+SHAPE_SIZES = [1023, 1024, 1025, 2048, 2049, 4096, 4097, 131_072, 131_073, 262_145, 524_289]
+
+
+@pytest.mark.parametrize("valued", [False, True])
+@pytest.mark.parametrize("model", ["cox", "fg"])
+@pytest.mark.parametrize("n", SHAPE_SIZES)
+def test_sweep_shapes(n, model, valued):
+    p = 7
+    c = make_case(model, n, p, n, 0, 0.05 if not valued else 0.4, valued)
+    c["y"] = np.ceil(c["y"] * n / 2)  # tie runs
+    c["eta"] = np.zeros(n)
+    prob = gpu_problem(model, c)
+    g12 = torch.zeros(3 * p, dtype=torch.float64, device=DEV)
+    beta, delta, eta, hist = oracle_sweeps(model, c, occd.PENALTY_L2, 1.0, 1)
+    prob.sweep("l2", 1.0, g12_out=g12)
+    got = g12.cpu().numpy().reshape(-1, 3)
+    for j in range(p):
+        g1, g2, s1, s2 = hist[j]
+        assert abs(got[j, 0] - g1) <= 1e-10 * s1, (j, got[j, 0], g1)
+        assert abs(got[j, 1] - g2) <= 1e-10 * s2, (j, got[j, 1], g2)
+    np.testing.assert_allclose(prob.beta.cpu().numpy(), beta, rtol=1e-9, atol=1e-13)
+    order = prob.perm.cpu().numpy()
+    np.testing.assert_allclose(prob.eta.cpu().numpy(), eta[order], rtol=1e-9, atol=1e-12)
+    np.testing.assert_allclose(prob.e.cpu().numpy(), np.exp(prob.eta.cpu().numpy()), rtol=1e-14)
+    # a second run from the same state: bit for bit
+    first = prob.beta.clone(), prob.e.clone()
+    prob.set_beta(torch.zeros(p), np.zeros(n))
+    prob.reset_trust()
+    prob.sweep("l2", 1.0)
+    assert torch.equal(prob.beta, first[0]) and torch.equal(prob.e, first[1])
+    # single-coordinate and split sweeps continue from the state left behind
+    prob.set_beta(torch.zeros(p), np.zeros(n))
+    prob.reset_trust()
+    prob.sweep("l2", 1.0, j_begin=0, j_end=1)
+    prob.sweep("l2", 1.0, j_begin=1, j_end=3)
+    prob.sweep("l2", 1.0, j_begin=3, j_end=p)
+    np.testing.assert_allclose(prob.beta.cpu().numpy(), beta, rtol=1e-9, atol=1e-13)
+    assert prob.workspace_error() == 0

@@ -484,40 +484,6 @@ __device__ __forceinline__ void ld_pairs<6>(const u32x4 *p, u32x4 (&r)[6])
 }
 
 template <>
-__device__ __forceinline__ void ld_pairs<7>(const u32x4 *p, u32x4 (&r)[7])
-{
-    asm volatile("global_load_dwordx4 %0, %7, off sc1\n\t"
-                 "global_load_dwordx4 %1, %7, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %2, %7, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %3, %7, off offset:48 sc1\n\t"
-                 "global_load_dwordx4 %4, %7, off offset:64 sc1\n\t"
-                 "global_load_dwordx4 %5, %7, off offset:80 sc1\n\t"
-                 "global_load_dwordx4 %6, %7, off offset:96 sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6])
-                 : "v"(p)
-                 : "memory");
-}
-
-template <>
-__device__ __forceinline__ void ld_pairs<8>(const u32x4 *p, u32x4 (&r)[8])
-{
-    asm volatile(
-                 "global_load_dwordx4 %0, %8, off sc1\n\t"
-                 "global_load_dwordx4 %1, %8, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %2, %8, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %3, %8, off offset:48 sc1\n\t"
-                 "global_load_dwordx4 %4, %8, off offset:64 sc1\n\t"
-                 "global_load_dwordx4 %5, %8, off offset:80 sc1\n\t"
-                 "global_load_dwordx4 %6, %8, off offset:96 sc1\n\t"
-                 "global_load_dwordx4 %7, %8, off offset:112 sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7])
-                 : "v"(p)
-                 : "memory");
-}
-
-template <>
 __device__ __forceinline__ void ld_pairs<9>(const u32x4 *p, u32x4 (&r)[9])
 {
     asm volatile("global_load_dwordx4 %0, %9, off sc1\n\t"
@@ -558,318 +524,6 @@ __device__ __forceinline__ void ld_pairs<15>(const u32x4 *p, u32x4 (&r)[15])
                  : "v"(p)
                  : "memory");
 }
-
-
-template <>
-__device__ __forceinline__ void ld_pairs<5>(const u32x4 *p, u32x4 (&r)[5])
-{
-    asm volatile(
-                 "global_load_dwordx4 %0, %5, off sc1\n\t"
-                 "global_load_dwordx4 %1, %5, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %2, %5, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %3, %5, off offset:48 sc1\n\t"
-                 "global_load_dwordx4 %4, %5, off offset:64 sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4])
-                 : "v"(p)
-                 : "memory");
-}
-
-template <>
-__device__ __forceinline__ void ld_pairs<10>(const u32x4 *p, u32x4 (&r)[10])
-{
-    asm volatile(
-                 "global_load_dwordx4 %0, %10, off sc1\n\t"
-                 "global_load_dwordx4 %1, %10, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %2, %10, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %3, %10, off offset:48 sc1\n\t"
-                 "global_load_dwordx4 %4, %10, off offset:64 sc1\n\t"
-                 "global_load_dwordx4 %5, %10, off offset:80 sc1\n\t"
-                 "global_load_dwordx4 %6, %10, off offset:96 sc1\n\t"
-                 "global_load_dwordx4 %7, %10, off offset:112 sc1\n\t"
-                 "global_load_dwordx4 %8, %10, off offset:128 sc1\n\t"
-                 "global_load_dwordx4 %9, %10, off offset:144 sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7]), "=&v"(r[8]), "=&v"(r[9])
-                 : "v"(p)
-                 : "memory");
-}
-
-template <>
-__device__ __forceinline__ void ld_pairs<11>(const u32x4 *p, u32x4 (&r)[11])
-{
-    asm volatile(
-                 "global_load_dwordx4 %0, %11, off sc1\n\t"
-                 "global_load_dwordx4 %1, %11, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %2, %11, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %3, %11, off offset:48 sc1\n\t"
-                 "global_load_dwordx4 %4, %11, off offset:64 sc1\n\t"
-                 "global_load_dwordx4 %5, %11, off offset:80 sc1\n\t"
-                 "global_load_dwordx4 %6, %11, off offset:96 sc1\n\t"
-                 "global_load_dwordx4 %7, %11, off offset:112 sc1\n\t"
-                 "global_load_dwordx4 %8, %11, off offset:128 sc1\n\t"
-                 "global_load_dwordx4 %9, %11, off offset:144 sc1\n\t"
-                 "global_load_dwordx4 %10, %11, off offset:160 sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7]), "=&v"(r[8]), "=&v"(r[9]), "=&v"(r[10])
-                 : "v"(p)
-                 : "memory");
-}
-
-// Loads NP pairs at p and NP pairs 256 bytes further (two consecutive
-// 16-pair slots) and waits for all of them.
-template <int NP>
-__device__ __forceinline__ void ld_pairs2(const u32x4 *p, u32x4 (&r0)[NP], u32x4 (&r1)[NP]);
-
-template <>
-__device__ __forceinline__ void ld_pairs2<9>(const u32x4 *p, u32x4 (&r0)[9],
-                                               u32x4 (&r1)[9])
-{
-    asm volatile(
-                 "global_load_dwordx4 %0, %18, off sc1\n\t"
-                 "global_load_dwordx4 %1, %18, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %2, %18, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %3, %18, off offset:48 sc1\n\t"
-                 "global_load_dwordx4 %4, %18, off offset:64 sc1\n\t"
-                 "global_load_dwordx4 %5, %18, off offset:80 sc1\n\t"
-                 "global_load_dwordx4 %6, %18, off offset:96 sc1\n\t"
-                 "global_load_dwordx4 %7, %18, off offset:112 sc1\n\t"
-                 "global_load_dwordx4 %8, %18, off offset:128 sc1\n\t"
-                 "global_load_dwordx4 %9, %18, off offset:256 sc1\n\t"
-                 "global_load_dwordx4 %10, %18, off offset:272 sc1\n\t"
-                 "global_load_dwordx4 %11, %18, off offset:288 sc1\n\t"
-                 "global_load_dwordx4 %12, %18, off offset:304 sc1\n\t"
-                 "global_load_dwordx4 %13, %18, off offset:320 sc1\n\t"
-                 "global_load_dwordx4 %14, %18, off offset:336 sc1\n\t"
-                 "global_load_dwordx4 %15, %18, off offset:352 sc1\n\t"
-                 "global_load_dwordx4 %16, %18, off offset:368 sc1\n\t"
-                 "global_load_dwordx4 %17, %18, off offset:384 sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(r0[0]), "=&v"(r0[1]), "=&v"(r0[2]), "=&v"(r0[3]), "=&v"(r0[4]), "=&v"(r0[5]), "=&v"(r0[6]), "=&v"(r0[7]), "=&v"(r0[8]), "=&v"(r1[0]), "=&v"(r1[1]), "=&v"(r1[2]), "=&v"(r1[3]), "=&v"(r1[4]), "=&v"(r1[5]), "=&v"(r1[6]), "=&v"(r1[7]), "=&v"(r1[8])
-                 : "v"(p)
-                 : "memory");
-}
-
-template <>
-__device__ __forceinline__ void ld_pairs2<15>(const u32x4 *p, u32x4 (&r0)[15],
-                                               u32x4 (&r1)[15])
-{
-    asm volatile(
-                 "global_load_dwordx4 %0, %30, off sc1\n\t"
-                 "global_load_dwordx4 %1, %30, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %2, %30, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %3, %30, off offset:48 sc1\n\t"
-                 "global_load_dwordx4 %4, %30, off offset:64 sc1\n\t"
-                 "global_load_dwordx4 %5, %30, off offset:80 sc1\n\t"
-                 "global_load_dwordx4 %6, %30, off offset:96 sc1\n\t"
-                 "global_load_dwordx4 %7, %30, off offset:112 sc1\n\t"
-                 "global_load_dwordx4 %8, %30, off offset:128 sc1\n\t"
-                 "global_load_dwordx4 %9, %30, off offset:144 sc1\n\t"
-                 "global_load_dwordx4 %10, %30, off offset:160 sc1\n\t"
-                 "global_load_dwordx4 %11, %30, off offset:176 sc1\n\t"
-                 "global_load_dwordx4 %12, %30, off offset:192 sc1\n\t"
-                 "global_load_dwordx4 %13, %30, off offset:208 sc1\n\t"
-                 "global_load_dwordx4 %14, %30, off offset:224 sc1\n\t"
-                 "global_load_dwordx4 %15, %30, off offset:256 sc1\n\t"
-                 "global_load_dwordx4 %16, %30, off offset:272 sc1\n\t"
-                 "global_load_dwordx4 %17, %30, off offset:288 sc1\n\t"
-                 "global_load_dwordx4 %18, %30, off offset:304 sc1\n\t"
-                 "global_load_dwordx4 %19, %30, off offset:320 sc1\n\t"
-                 "global_load_dwordx4 %20, %30, off offset:336 sc1\n\t"
-                 "global_load_dwordx4 %21, %30, off offset:352 sc1\n\t"
-                 "global_load_dwordx4 %22, %30, off offset:368 sc1\n\t"
-                 "global_load_dwordx4 %23, %30, off offset:384 sc1\n\t"
-                 "global_load_dwordx4 %24, %30, off offset:400 sc1\n\t"
-                 "global_load_dwordx4 %25, %30, off offset:416 sc1\n\t"
-                 "global_load_dwordx4 %26, %30, off offset:432 sc1\n\t"
-                 "global_load_dwordx4 %27, %30, off offset:448 sc1\n\t"
-                 "global_load_dwordx4 %28, %30, off offset:464 sc1\n\t"
-                 "global_load_dwordx4 %29, %30, off offset:480 sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(r0[0]), "=&v"(r0[1]), "=&v"(r0[2]), "=&v"(r0[3]), "=&v"(r0[4]), "=&v"(r0[5]), "=&v"(r0[6]), "=&v"(r0[7]), "=&v"(r0[8]), "=&v"(r0[9]), "=&v"(r0[10]), "=&v"(r0[11]), "=&v"(r0[12]), "=&v"(r0[13]), "=&v"(r0[14]), "=&v"(r1[0]), "=&v"(r1[1]), "=&v"(r1[2]), "=&v"(r1[3]), "=&v"(r1[4]), "=&v"(r1[5]), "=&v"(r1[6]), "=&v"(r1[7]), "=&v"(r1[8]), "=&v"(r1[9]), "=&v"(r1[10]), "=&v"(r1[11]), "=&v"(r1[12]), "=&v"(r1[13]), "=&v"(r1[14])
-                 : "v"(p)
-                 : "memory");
-}
-
-template <>
-__device__ __forceinline__ void ld_pairs2<4>(const u32x4 *p, u32x4 (&r0)[4],
-                                               u32x4 (&r1)[4])
-{
-    asm volatile(
-                 "global_load_dwordx4 %0, %8, off sc1\n\t"
-                 "global_load_dwordx4 %1, %8, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %2, %8, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %3, %8, off offset:48 sc1\n\t"
-                 "global_load_dwordx4 %4, %8, off offset:256 sc1\n\t"
-                 "global_load_dwordx4 %5, %8, off offset:272 sc1\n\t"
-                 "global_load_dwordx4 %6, %8, off offset:288 sc1\n\t"
-                 "global_load_dwordx4 %7, %8, off offset:304 sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(r0[0]), "=&v"(r0[1]), "=&v"(r0[2]), "=&v"(r0[3]), "=&v"(r1[0]), "=&v"(r1[1]), "=&v"(r1[2]), "=&v"(r1[3])
-                 : "v"(p)
-                 : "memory");
-}
-
-template <>
-__device__ __forceinline__ void ld_pairs2<5>(const u32x4 *p, u32x4 (&r0)[5],
-                                               u32x4 (&r1)[5])
-{
-    asm volatile(
-                 "global_load_dwordx4 %0, %10, off sc1\n\t"
-                 "global_load_dwordx4 %1, %10, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %2, %10, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %3, %10, off offset:48 sc1\n\t"
-                 "global_load_dwordx4 %4, %10, off offset:64 sc1\n\t"
-                 "global_load_dwordx4 %5, %10, off offset:256 sc1\n\t"
-                 "global_load_dwordx4 %6, %10, off offset:272 sc1\n\t"
-                 "global_load_dwordx4 %7, %10, off offset:288 sc1\n\t"
-                 "global_load_dwordx4 %8, %10, off offset:304 sc1\n\t"
-                 "global_load_dwordx4 %9, %10, off offset:320 sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(r0[0]), "=&v"(r0[1]), "=&v"(r0[2]), "=&v"(r0[3]), "=&v"(r0[4]), "=&v"(r1[0]), "=&v"(r1[1]), "=&v"(r1[2]), "=&v"(r1[3]), "=&v"(r1[4])
-                 : "v"(p)
-                 : "memory");
-}
-
-template <>
-__device__ __forceinline__ void ld_pairs2<8>(const u32x4 *p, u32x4 (&r0)[8],
-                                               u32x4 (&r1)[8])
-{
-    asm volatile(
-                 "global_load_dwordx4 %0, %16, off sc1\n\t"
-                 "global_load_dwordx4 %1, %16, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %2, %16, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %3, %16, off offset:48 sc1\n\t"
-                 "global_load_dwordx4 %4, %16, off offset:64 sc1\n\t"
-                 "global_load_dwordx4 %5, %16, off offset:80 sc1\n\t"
-                 "global_load_dwordx4 %6, %16, off offset:96 sc1\n\t"
-                 "global_load_dwordx4 %7, %16, off offset:112 sc1\n\t"
-                 "global_load_dwordx4 %8, %16, off offset:256 sc1\n\t"
-                 "global_load_dwordx4 %9, %16, off offset:272 sc1\n\t"
-                 "global_load_dwordx4 %10, %16, off offset:288 sc1\n\t"
-                 "global_load_dwordx4 %11, %16, off offset:304 sc1\n\t"
-                 "global_load_dwordx4 %12, %16, off offset:320 sc1\n\t"
-                 "global_load_dwordx4 %13, %16, off offset:336 sc1\n\t"
-                 "global_load_dwordx4 %14, %16, off offset:352 sc1\n\t"
-                 "global_load_dwordx4 %15, %16, off offset:368 sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(r0[0]), "=&v"(r0[1]), "=&v"(r0[2]), "=&v"(r0[3]), "=&v"(r0[4]), "=&v"(r0[5]), "=&v"(r0[6]), "=&v"(r0[7]), "=&v"(r1[0]), "=&v"(r1[1]), "=&v"(r1[2]), "=&v"(r1[3]), "=&v"(r1[4]), "=&v"(r1[5]), "=&v"(r1[6]), "=&v"(r1[7])
-                 : "v"(p)
-                 : "memory");
-}
-
-template <>
-__device__ __forceinline__ void ld_pairs2<6>(const u32x4 *p, u32x4 (&r0)[6],
-                                               u32x4 (&r1)[6])
-{
-    asm volatile(
-                 "global_load_dwordx4 %0, %12, off sc1\n\t"
-                 "global_load_dwordx4 %1, %12, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %2, %12, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %3, %12, off offset:48 sc1\n\t"
-                 "global_load_dwordx4 %4, %12, off offset:64 sc1\n\t"
-                 "global_load_dwordx4 %5, %12, off offset:80 sc1\n\t"
-                 "global_load_dwordx4 %6, %12, off offset:256 sc1\n\t"
-                 "global_load_dwordx4 %7, %12, off offset:272 sc1\n\t"
-                 "global_load_dwordx4 %8, %12, off offset:288 sc1\n\t"
-                 "global_load_dwordx4 %9, %12, off offset:304 sc1\n\t"
-                 "global_load_dwordx4 %10, %12, off offset:320 sc1\n\t"
-                 "global_load_dwordx4 %11, %12, off offset:336 sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(r0[0]), "=&v"(r0[1]), "=&v"(r0[2]), "=&v"(r0[3]), "=&v"(r0[4]), "=&v"(r0[5]), "=&v"(r1[0]), "=&v"(r1[1]), "=&v"(r1[2]), "=&v"(r1[3]), "=&v"(r1[4]), "=&v"(r1[5])
-                 : "v"(p)
-                 : "memory");
-}
-
-template <>
-__device__ __forceinline__ void ld_pairs2<10>(const u32x4 *p, u32x4 (&r0)[10],
-                                               u32x4 (&r1)[10])
-{
-    asm volatile(
-                 "global_load_dwordx4 %0, %20, off sc1\n\t"
-                 "global_load_dwordx4 %1, %20, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %2, %20, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %3, %20, off offset:48 sc1\n\t"
-                 "global_load_dwordx4 %4, %20, off offset:64 sc1\n\t"
-                 "global_load_dwordx4 %5, %20, off offset:80 sc1\n\t"
-                 "global_load_dwordx4 %6, %20, off offset:96 sc1\n\t"
-                 "global_load_dwordx4 %7, %20, off offset:112 sc1\n\t"
-                 "global_load_dwordx4 %8, %20, off offset:128 sc1\n\t"
-                 "global_load_dwordx4 %9, %20, off offset:144 sc1\n\t"
-                 "global_load_dwordx4 %10, %20, off offset:256 sc1\n\t"
-                 "global_load_dwordx4 %11, %20, off offset:272 sc1\n\t"
-                 "global_load_dwordx4 %12, %20, off offset:288 sc1\n\t"
-                 "global_load_dwordx4 %13, %20, off offset:304 sc1\n\t"
-                 "global_load_dwordx4 %14, %20, off offset:320 sc1\n\t"
-                 "global_load_dwordx4 %15, %20, off offset:336 sc1\n\t"
-                 "global_load_dwordx4 %16, %20, off offset:352 sc1\n\t"
-                 "global_load_dwordx4 %17, %20, off offset:368 sc1\n\t"
-                 "global_load_dwordx4 %18, %20, off offset:384 sc1\n\t"
-                 "global_load_dwordx4 %19, %20, off offset:400 sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(r0[0]), "=&v"(r0[1]), "=&v"(r0[2]), "=&v"(r0[3]), "=&v"(r0[4]), "=&v"(r0[5]), "=&v"(r0[6]), "=&v"(r0[7]), "=&v"(r0[8]), "=&v"(r0[9]), "=&v"(r1[0]), "=&v"(r1[1]), "=&v"(r1[2]), "=&v"(r1[3]), "=&v"(r1[4]), "=&v"(r1[5]), "=&v"(r1[6]), "=&v"(r1[7]), "=&v"(r1[8]), "=&v"(r1[9])
-                 : "v"(p)
-                 : "memory");
-}
-
-template <>
-__device__ __forceinline__ void ld_pairs2<7>(const u32x4 *p, u32x4 (&r0)[7],
-                                               u32x4 (&r1)[7])
-{
-    asm volatile(
-                 "global_load_dwordx4 %0, %14, off sc1\n\t"
-                 "global_load_dwordx4 %1, %14, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %2, %14, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %3, %14, off offset:48 sc1\n\t"
-                 "global_load_dwordx4 %4, %14, off offset:64 sc1\n\t"
-                 "global_load_dwordx4 %5, %14, off offset:80 sc1\n\t"
-                 "global_load_dwordx4 %6, %14, off offset:96 sc1\n\t"
-                 "global_load_dwordx4 %7, %14, off offset:256 sc1\n\t"
-                 "global_load_dwordx4 %8, %14, off offset:272 sc1\n\t"
-                 "global_load_dwordx4 %9, %14, off offset:288 sc1\n\t"
-                 "global_load_dwordx4 %10, %14, off offset:304 sc1\n\t"
-                 "global_load_dwordx4 %11, %14, off offset:320 sc1\n\t"
-                 "global_load_dwordx4 %12, %14, off offset:336 sc1\n\t"
-                 "global_load_dwordx4 %13, %14, off offset:352 sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(r0[0]), "=&v"(r0[1]), "=&v"(r0[2]), "=&v"(r0[3]), "=&v"(r0[4]), "=&v"(r0[5]), "=&v"(r0[6]), "=&v"(r1[0]), "=&v"(r1[1]), "=&v"(r1[2]), "=&v"(r1[3]), "=&v"(r1[4]), "=&v"(r1[5]), "=&v"(r1[6])
-                 : "v"(p)
-                 : "memory");
-}
-
-template <>
-__device__ __forceinline__ void ld_pairs2<11>(const u32x4 *p, u32x4 (&r0)[11],
-                                               u32x4 (&r1)[11])
-{
-    asm volatile(
-                 "global_load_dwordx4 %0, %22, off sc1\n\t"
-                 "global_load_dwordx4 %1, %22, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %2, %22, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %3, %22, off offset:48 sc1\n\t"
-                 "global_load_dwordx4 %4, %22, off offset:64 sc1\n\t"
-                 "global_load_dwordx4 %5, %22, off offset:80 sc1\n\t"
-                 "global_load_dwordx4 %6, %22, off offset:96 sc1\n\t"
-                 "global_load_dwordx4 %7, %22, off offset:112 sc1\n\t"
-                 "global_load_dwordx4 %8, %22, off offset:128 sc1\n\t"
-                 "global_load_dwordx4 %9, %22, off offset:144 sc1\n\t"
-                 "global_load_dwordx4 %10, %22, off offset:160 sc1\n\t"
-                 "global_load_dwordx4 %11, %22, off offset:256 sc1\n\t"
-                 "global_load_dwordx4 %12, %22, off offset:272 sc1\n\t"
-                 "global_load_dwordx4 %13, %22, off offset:288 sc1\n\t"
-                 "global_load_dwordx4 %14, %22, off offset:304 sc1\n\t"
-                 "global_load_dwordx4 %15, %22, off offset:320 sc1\n\t"
-                 "global_load_dwordx4 %16, %22, off offset:336 sc1\n\t"
-                 "global_load_dwordx4 %17, %22, off offset:352 sc1\n\t"
-                 "global_load_dwordx4 %18, %22, off offset:368 sc1\n\t"
-                 "global_load_dwordx4 %19, %22, off offset:384 sc1\n\t"
-                 "global_load_dwordx4 %20, %22, off offset:400 sc1\n\t"
-                 "global_load_dwordx4 %21, %22, off offset:416 sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(r0[0]), "=&v"(r0[1]), "=&v"(r0[2]), "=&v"(r0[3]), "=&v"(r0[4]), "=&v"(r0[5]), "=&v"(r0[6]), "=&v"(r0[7]), "=&v"(r0[8]), "=&v"(r0[9]), "=&v"(r0[10]), "=&v"(r1[0]), "=&v"(r1[1]), "=&v"(r1[2]), "=&v"(r1[3]), "=&v"(r1[4]), "=&v"(r1[5]), "=&v"(r1[6]), "=&v"(r1[7]), "=&v"(r1[8]), "=&v"(r1[9]), "=&v"(r1[10])
-                 : "v"(p)
-                 : "memory");
-}
-
 
 
 // Loads NC consecutive pairs at each of KQ addresses and waits for all of

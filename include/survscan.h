@@ -492,8 +492,8 @@ int32_t ss_cv_select(int32_t n_gamma, int32_t reps, const double *scores,
  * A choice is kept per (kind, model, storage of e, valued design or not,
  * size bucket ceil(log2 n)) in a process-wide table that every launch
  * consults; without an entry a launch uses the built-in rule (tiles of
- * 2048 positions up to 1.5 M positions, 4096 above; the first sweep shape
- * whose workgroups all fit on the device).
+ * 2048 positions, for Cox of 4096 above 1.5 M positions; a sweep shape by
+ * size, among them segments of 1024 positions and one workgroup alone).
  *   storage: SS_STORAGE_F64 (FP64 e), SS_STORAGE_F32 (FP32 e, FP64 sums),
  *   SS_STORAGE_F32_SUMS32 (FP32 e, FP32 in-tile sums); the sweep is FP64.
  * ss_tune_get: the choice a launch would use now (the built-in rule's IPT

@@ -318,20 +318,22 @@ int32_t ss_ccd_sweep(int32_t model, int32_t penalty, double lambda, int64_t n, i
     a.steps = steps;
     a.want_log = g12_out != nullptr;
     a.obj_penalty = -1;
-    // Fine-Gray with a 0/1 design: one launch per coordinate, each carrying
-    // the weighted totals of the next column (a totals pass only before the
-    // first one); valued designs: a totals pass before every scan
-    const bool fg_carry = model == SS_FINE_GRAY && vals_sorted == nullptr;
+    // 0/1 designs: one launch per coordinate, each leaving the next one's
+    // tile sums (Fine-Gray: a sums pass before the first one); valued
+    // designs: Cox one launch with look-back, Fine-Gray two
+    const bool sums = vals_sorted == nullptr;
     for (int64_t j = j_begin; j < j_end; ++j) {
         a.j = (int32_t)j;
         a.jprev = j > j_begin ? (int32_t)(j - 1) : -1;
         a.step_prev = j > j_begin ? steps + (j - 1) : nullptr;
         a.out = g12_out ? g12_out + 3 * j : v.hdr->scratch_out;
-        a.fg_have_totals = fg_carry && j > j_begin;
-        a.jnext = fg_carry && j + 1 < j_end ? (int32_t)(j + 1) : -1;
+        a.have_sums = sums && j > j_begin;
+        a.jnext = sums && j + 1 < j_end ? (int32_t)(j + 1) : -1;
         int32_t rc = launch_fused(a, v, s);
         if (rc) return rc;
     }
+    if (sums)  // eta, and e from it, after all steps
+        return launch_sweep_eta(n, (int32_t)j_begin, (int32_t)j_end, steps, a.col, eta, e, s);
     return launch_apply(n, (int32_t)(j_end - 1), steps + (j_end - 1), eta, e, a.col, s);
 }
 

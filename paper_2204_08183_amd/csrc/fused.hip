@@ -85,7 +85,7 @@ __device__ void reduce_partials(u32x4 *part, u32x4 *gpart, int64_t tile, int64_t
                                 uint64_t tag, WsHeader *hdr, const double (&tile_sum)[NR],
                                 double (&total)[NR], double *s_red)
 {
-    static_assert(NR <= SLOT, "a slot holds the sums");
+    static_assert(pub_words<NR>() <= SLOT, "a slot holds the sums");
     const int lane = lane_id();
     const int tid = threadIdx.x;
     const bool last = tile == ntiles - 1;
@@ -147,15 +147,13 @@ __device__ void reduce_partials(u32x4 *part, u32x4 *gpart, int64_t tile, int64_t
 // Last tile: g', g'', the likelihood or the coordinate update from the
 // launch totals (thread 0), then the launch epoch moves on.
 //
-// CARRY (Fine-Gray, 0/1 design): tot[3], tot[4] are sum e w x_next and
-// sum e w x_j x_next over the launch, fgw = (sum e w, sum e w x_j) its
-// totals; the coordinate's step s multiplies e by exp(s) where x_j = 1, so
-// the totals of column jnext over the updated e are sum e w + expm1(s)
-// sum e w x_j (m = 0) and tot[3] + expm1(s) tot[4] (m = 1, 2), stored for the
-// next launch.
-template <int BLOCK, int NR, bool CARRY>
+// FG_NEXT (Fine-Gray, EMIT): tot[3..] are the totals of A and D (see
+// k_fused); the coordinate's step s multiplies e by exp(s) where x_j = 1, so
+// the weighted totals of column jnext over the updated e are A + expm1(s) D,
+// stored for the next launch.
+template <int BLOCK, int NR, bool FG_NEXT>
 __device__ void finish(const FusedCall &a, const WsView &ws, uint64_t epoch,
-                       const double (&tot)[NR], const double *fgw, double *s_red)
+                       const double (&tot)[NR], double *s_red)
 {
     // beta' c and the penalty's sum (|beta_q| for l1, beta_q^2 for l2)
     double all[2] = {0.0, 0.0};
@@ -191,10 +189,10 @@ __device__ void finish(const FusedCall &a, const WsView &ws, uint64_t epoch,
                 ccd_apply(g1, g2, a.penalty, a.lambda, a.beta + a.j,
                           a.delta + a.j, a.steps + a.j);
             }
-            if constexpr (CARRY) {
+            if constexpr (FG_NEXT) {
                 const double em = expm1(a.steps[a.j]);
-                const double t1 = tot[3] + em * tot[4];
-                ws.hdr->fg_tot[0] = fgw[0] + em * fgw[1];
+                const double t1 = tot[3 + 3] + em * tot[3 + 4 + 3];
+                ws.hdr->fg_tot[0] = tot[3 + 2] + em * tot[3 + 4 + 2];
                 ws.hdr->fg_tot[1] = t1;
                 ws.hdr->fg_tot[2] = t1;
             }
@@ -264,9 +262,12 @@ __device__ __forceinline__ void clear_tile_lds(uint8_t *s_flag, double *s_xv)
 }
 
 // Stages one tile (positions [t0, t0+cnt)): e (patched by the pending step
-// of column jprev, which is also written back to eta and e), the weights w
-// (Fine-Gray) and the event counts d (one byte each, element i in byte i%4
-// of word i/4) go to registers.  Column j: a 0/1 column leaves a bit per
+// of column jprev, which is also written back), the weights w (Fine-Gray)
+// and the event counts d (one byte each, element i in byte i%4 of word i/4)
+// go to registers.  The pending step: a valued column updates eta and takes
+// e = exp(eta); a 0/1 column multiplies e by exp(step) where its owner holds
+// it, and eta follows at the end of the sweep (k_sweep_eta) -- the tile then
+// waits for no load of eta behind the column's rows.  Column j: a 0/1 column leaves a bit per
 // element in a register (returned: bit i for element i); a valued column
 // leaves its values in LDS at s_xv[i * BLOCK + tid] (lane-major, free of
 // bank conflicts; 0 where the column has no entry, and the returned bits
@@ -393,10 +394,14 @@ __device__ __forceinline__ uint32_t stage_tile(const FusedCall &a, int64_t t0, i
         for (int32_t o = cnext.lo + tid; o < cnext.hi; o += BLOCK)
             lds_flag_or(s_flag, (int32_t)(a.col.rows[cnext.cb + o] - t0), kFlagNext);
     }
-    if (PREV && step_prev != 0.0) {
+    if (PREV && !VALS && step_prev != 0.0) {
+        for (int32_t o = cprev.lo + tid; o < cprev.hi; o += BLOCK)
+            lds_flag_or(s_flag, (int32_t)(a.col.rows[cprev.cb + o] - t0), kFlagPatch);
+    }
+    if (PREV && VALS && step_prev != 0.0) {
         for (int32_t o = cprev.lo + tid; o < cprev.hi; o += BLOCK) {
             const int32_t k = a.col.rows[cprev.cb + o];
-            const double x = VALS ? a.col.vals[cprev.cb + o] : 1.0;
+            const double x = a.col.vals[cprev.cb + o];
             const double et = a.eta[k] + x * step_prev;
             const double en = exp(et);
             a.eta[k] = et;
@@ -422,20 +427,22 @@ __device__ __forceinline__ uint32_t stage_tile(const FusedCall &a, int64_t t0, i
     }
     if (NEXT) *nbits = qbits;
     if (dense) xbits = IPT == 32 ? ~0u : (1u << IPT) - 1u;
-    if (PREV) {
+    if constexpr (PREV && VALS) {
 #pragma unroll
         for (int i = 0; i < IPT; ++i)
             if ((pbits >> i) & 1u) ev[i] = s_ep[tile_pos<BLOCK, IPT>(i, tid)];
     }
+    if constexpr (PREV && !VALS) {
+        const double fe = exp(step_prev);
+#pragma unroll
+        for (int i = 0; i < IPT; ++i) {
+            if ((pbits >> i) & 1u) {
+                ev[i] *= fe;
+                a.e[t0 + tile_pos<BLOCK, IPT>(i, tid)] = ev[i];
+            }
+        }
+    }
     return xbits;
-}
-
-// x of column j at element i of this thread (see stage_tile).
-template <int BLOCK, bool VALS>
-__device__ __forceinline__ double x_at(uint32_t xbits, int i, const double *s_xv)
-{
-    if (VALS) return s_xv[i * BLOCK + threadIdx.x];  // 0 where absent
-    return ((xbits >> i) & 1u) ? 1.0 : 0.0;
 }
 
 // The tuple of Sec. 2.7 at one position, added to running sums S.  Cox:
@@ -483,12 +490,64 @@ struct Tuple {
     }
 };
 
+// Sum of N values over the tiles before tile ti, by one wave (all lanes get
+// it): the tiles of its own group of kGroup, and the groups before, from the
+// sums that reduce_partials of an earlier launch published (packed from word
+// `word` of slots of SLOT words).
+template <int N, int SLOT>
+__device__ __forceinline__ void tile_prefix(const u32x4 *part, const u32x4 *gpart, int word,
+                                            int32_t ti, double (&sum)[N])
+{
+    constexpr int NQ = pub_words<N>();
+    const int lane = lane_id();
+    const int32_t g = ti / kGroup, pos = ti % kGroup;
+    double v[N];
+#pragma unroll
+    for (int c = 0; c < N; ++c) sum[c] = 0.0;
+    auto add = [&](const u32x4 *p) {
+        u32x4 r[NQ];
+#pragma unroll
+        for (int c = 0; c < NQ; ++c) r[c] = p[word + c];
+        pub_unpack<N>(r, v);
+#pragma unroll
+        for (int c = 0; c < N; ++c) sum[c] += v[c];
+    };
+    if (lane < pos) add(part + (int64_t)(g * kGroup + lane) * SLOT);
+    for (int32_t q = lane; q < g; q += kWave) add(gpart + (int64_t)q * SLOT);
+#pragma unroll
+    for (int c = 0; c < N; ++c) sum[c] = dpp_wave_sum(sum[c]);
+}
+
+// Waves per SIMD that the register allocation is held to: four for
+// Fine-Gray tiles of 2048 positions (A and D in the sweep's kernel would take
+// 142 registers, three waves: N = 6e6, 53 against 51 us per coordinate; five
+// waves spill, 80 us).
+template <int IPT, int MODEL, bool VALS, int PRE>
+constexpr int fused_min_waves()
+{
+    return MODEL == SS_FINE_GRAY && !VALS && PRE != 0 && IPT == 8 ? 4 : 1;
+}
+
 // The fused scan -> transform -> reduce kernel (one coordinate).
 // MODEL: SS_COX (3 tuple components) or SS_FINE_GRAY (6).  PREV: apply the
 // pending step of column jprev to eta and e first (step (1) of Sec. 2.7).
-// CARRY (Fine-Gray, 0/1 design): the weighted totals of column j were
-// carried by the previous launch, and this launch carries those of column
-// jnext (two more partial sums, see finish).
+//
+// PRE: where a tile's exclusive prefix comes from.
+//   0  the decoupled look-back (Sec. 2.6) of this launch.
+//   1  the tile sums of the pass that formed the Fine-Gray totals (k_fg_sums
+//      reads e, w and the column anyway, so they cost nothing more).
+//   2  (0/1 designs inside a sweep) the tile sums A and D that the previous
+//      coordinate's launch left (EMIT): with x in {0, 1} its step s
+//      multiplies e by exp(s) on the rows of its column, so the tuple sums of
+//      a tile are A + expm1(s) D, with A the sums of e (1, x_next) and D the
+//      same over the rows of column j, taken before s was known.
+// With 1 and 2 no tile waits for another one's prefix, so smaller tiles pay
+// (default_ipt).  us per coordinate against the look-back: Fine-Gray N = 2e7
+// 212 -> 172 (FP32 e 180 -> 145; the two passes move 41 (33) bytes per
+// position, 159 (128) us at the copy rate); in a sweep Fine-Gray N = 6e6
+// 64 -> 51, N = 2e7 211 -> 166, Cox N = 2e7 115 -> 73.
+// EMIT (0/1 designs): this launch leaves A and D for column jnext behind its
+// partial sums, in one of two buffers by the parity of the epoch.
 //
 // ET: storage type of e (float: FP32 storage, read from a.e32).  F32S (with
 // float storage): the sums inside a tile (thread-serial and wave scans), the
@@ -496,35 +555,36 @@ struct Tuple {
 // tile boundary (aggregates, the look-back prefix, the tile partial sums)
 // in FP64, and each run end's prefix is the FP64 carry plus the FP32
 // in-tile prefix.  Without F32S every sum is FP64.
-template <int BLOCK, int IPT, int MODEL, bool VALS, bool PREV, bool CARRY = false,
+template <int BLOCK, int IPT, int MODEL, bool VALS, bool PREV, int PRE = 0, bool EMIT = false,
           typename ET = double, bool F32S = false>
-__global__ __launch_bounds__(BLOCK) void k_fused(FusedCall a, WsView ws, int64_t ntiles)
+__global__ __launch_bounds__(BLOCK, (fused_min_waves<IPT, MODEL, VALS, PRE>())) void k_fused(FusedCall a, WsView ws, int64_t ntiles)
 {
     constexpr int TILE = BLOCK * IPT;
     constexpr int NW = BLOCK / kWave;
-    constexpr int NR = CARRY ? 5 : 3;  // partial sums per tile
     static_assert(TILE % SS_CHUNK == 0, "tile must be whole chunks");
-    static_assert(!CARRY || (MODEL == SS_FINE_GRAY && !VALS), "carry: Fine-Gray, 0/1 design");
+    static_assert(!VALS || (!EMIT && PRE != 2), "A and D: 0/1 designs");
+    static_assert(MODEL == SS_FINE_GRAY || PRE != 1, "the totals pass is Fine-Gray's");
     static_assert(!F32S || std::is_same<ET, float>::value, "FP32 sums need FP32 storage");
     // arithmetic type of the sums inside a tile
     using AT = typename std::conditional<F32S, float, double>::type;
     using Tx = Tuple<BLOCK, MODEL, VALS>;
     constexpr int NX = Tx::NX;  // distinct tuple components
+    constexpr int NR = EMIT ? 3 + 2 * NX : 3;  // partial sums per tile
+    constexpr int NE = EMIT ? 3 + NX : 3;      // of them, summed over threads at the end
 
     __shared__ __attribute__((aligned(16))) uint8_t s_flag[TILE];
     __shared__ __attribute__((aligned(16))) double s_xv[VALS ? TILE : 1];
-    // G(Y) of the tile (Fine-Gray) and the patched e of the pending update
-    // (PREV) share one array: the patch is consumed during staging, and with
-    // PREV the copy of G is only started after that
+    // G(Y) of the tile (Fine-Gray), or the patched e of a valued column's
+    // pending update (Cox: the Fine-Gray one is taken by the sums pass)
+    static_assert(!(MODEL == SS_FINE_GRAY && PREV && VALS), "see k_fg_sums");
     constexpr bool kGLds = SS_FG_G_LDS && MODEL == SS_FINE_GRAY;
-    __shared__ __attribute__((aligned(16))) double s_eg[(PREV || kGLds) ? TILE : 1];
+    __shared__ __attribute__((aligned(16))) double s_eg[((PREV && VALS) || kGLds) ? TILE : 1];
     double *const s_ep = s_eg;
     double *const s_g = s_eg;
     __shared__ double s_wsum[TileMap<IPT>::R][NW][NX];
     __shared__ double s_excl[NX];
     __shared__ double s_red[NW * NR + NR];
-    __shared__ double s_tsum[NR];
-    __shared__ double s_fgw[2];
+    __shared__ double s_tsum[NE];
 
     const int tid = threadIdx.x;
     const int lane = lane_id();
@@ -559,7 +619,7 @@ __global__ __launch_bounds__(BLOCK) void k_fused(FusedCall a, WsView ws, int64_t
     // s_g[v * IPT * 64 + u * 128 + 2 l].  A partial last tile reads G at its
     // run ends.
     const bool g_lds = kGLds && cnt == TILE;
-    if (!PREV && g_lds) {
+    if (g_lds) {
 #pragma unroll
         for (int q = 0; q < R; ++q) {
 #pragma unroll
@@ -577,35 +637,27 @@ __global__ __launch_bounds__(BLOCK) void k_fused(FusedCall a, WsView ws, int64_t
     ET ev[IPT];
     double wv[MODEL == SS_FINE_GRAY ? IPT : 1];
     uint32_t dw[(IPT + 3) / 4];  // event counts, one byte per element
-    uint32_t nbits = 0u;         // CARRY: column jnext, one bit per element
+    uint32_t nbits = 0u;         // EMIT: column jnext, one bit per element
     const uint32_t xbits =
-        stage_tile<BLOCK, IPT, MODEL == SS_FINE_GRAY, VALS, PREV, true, CARRY, ET>(
+        stage_tile<BLOCK, IPT, MODEL == SS_FINE_GRAY, VALS, PREV, true, EMIT, ET>(
             a, t0, cnt, chunk0, chunk1, s_flag, s_xv, s_ep, ev, wv, dw, &nbits);
-    if constexpr (PREV && kGLds) {
-        // every thread has read its patches: the array takes G now, loaded
-        // by waves 1.. for all waves (wave 0's loads would hold up its
-        // look-back, which waits on its own memory counter)
-        __syncthreads();
-        if (g_lds && w != 0) {
-            for (int m = w - 1; m < NW * (IPT / 2); m += NW - 1) {
-                const int v = m / (IPT / 2), u = m % (IPT / 2);
-                const int q = u / (C / 2), h = u % (C / 2);
-                __builtin_amdgcn_global_load_lds(
-                    static_cast<const void *>(a.g_end + t0 + (int64_t)q * BLOCK * C +
-                                              (int64_t)(v * kWave + lane) * C + 2 * h),
-                    (__attribute__((address_space(3))) void *)(s_g + v * (IPT * kWave) +
-                                                               u * (2 * kWave)),
-                    16, 0, 0);
-            }
-        }
-    }
     SS_TRACE(ws, tile, 1);
 
     // ---- 5. thread totals per row and their wave scans (which are also the
     // scan inside the tile: the thread's exclusive prefix within the tile is
     // kept across the look-back, NX values per row), the tile's aggregate
     AT texcl[R][NX];
-    double agg[NX];
+    // the tile's aggregate, from the wave sums that stay in LDS
+    auto tile_agg = [&](double (&agg)[NX]) {
+#pragma unroll
+        for (int c = 0; c < NX; ++c) {
+            agg[c] = 0.0;
+#pragma unroll
+            for (int q = 0; q < R; ++q)
+#pragma unroll
+                for (int v = 0; v < NW; ++v) agg[c] += s_wsum[q][v][c];
+        }
+    };
     {
 #pragma unroll
         for (int q = 0; q < R; ++q) {
@@ -627,7 +679,6 @@ __global__ __launch_bounds__(BLOCK) void k_fused(FusedCall a, WsView ws, int64_t
         __syncthreads();
 #pragma unroll
         for (int c = 0; c < NX; ++c) {
-            double t = 0.0;
             AT done = (AT)0;  // rows before q
 #pragma unroll
             for (int q = 0; q < R; ++q) {
@@ -637,18 +688,38 @@ __global__ __launch_bounds__(BLOCK) void k_fused(FusedCall a, WsView ws, int64_t
                     const double sv = s_wsum[q][v][c];
                     if (v < w) before += (AT)sv;
                     row += (AT)sv;
-                    t += sv;
                 }
                 texcl[q][c] += done + before;
                 done += row;
             }
-            agg[c] = t;
         }
     }
 
-    // ---- 6. decoupled look-back for the tile's exclusive prefix
+    // ---- 6. the tile's exclusive prefix
     SS_TRACE(ws, tile, 2);
-    if (w == 0) {
+    if constexpr (PRE != 0) {
+        if (w == 0) {
+            double ex[NX];
+            if constexpr (PRE == 1) {
+                tile_prefix<NX, 4>(ws.fg_part, ws.fg_gpart, 0, (int32_t)tile, ex);
+            } else {
+                // behind the three partial sums (two words)
+                const bool odd = ((epoch - 1) & 1u) != 0;
+                double ad[2 * NX];
+                tile_prefix<2 * NX, 8>(odd ? ws.sw_agg : ws.part, odd ? ws.sw_pre : ws.gpart, 2,
+                                       (int32_t)tile, ad);
+                const double f = expm1(*a.step_prev);
+#pragma unroll
+                for (int c = 0; c < NX; ++c) ex[c] = ad[c] + f * ad[NX + c];
+            }
+            if (lane == 0) {
+#pragma unroll
+                for (int c = 0; c < NX; ++c) s_excl[c] = ex[c];
+            }
+        }
+    } else if (w == 0) {  // decoupled look-back
+        double agg[NX];
+        tile_agg(agg);
         u32x4 *slot = ws.lb + tile * kLbSlot;
         double ex[NX];
         uint64_t *lbs = nullptr;
@@ -694,12 +765,6 @@ __global__ __launch_bounds__(BLOCK) void k_fused(FusedCall a, WsView ws, int64_t
         if (lane == 0) {
 #pragma unroll
             for (int c = 0; c < NX; ++c) s_excl[c] = ex[c];
-            if constexpr (CARRY) {
-                if (tile == ntiles - 1) {
-                    s_fgw[0] = ex[Tx::EW] + agg[Tx::EW];
-                    s_fgw[1] = ex[Tx::EXW] + agg[Tx::EXW];
-                }
-            }
         }
     }
     // the copy of G in LDS has landed: each wave waits for its own loads
@@ -711,37 +776,9 @@ __global__ __launch_bounds__(BLOCK) void k_fused(FusedCall a, WsView ws, int64_t
     // across the look-back (registers bound how many tiles a CU holds)
     uint32_t xb = xbits;
     asm volatile("" : "+v"(xb));
-    if (MODEL == SS_FINE_GRAY && !CARRY) {
+    if (MODEL == SS_FINE_GRAY) {
 #pragma unroll
         for (int i = 0; i < IPT; ++i) asm volatile("" : "+v"(wv[i]));
-    }
-    if (MODEL == SS_FINE_GRAY && CARRY) {
-        // w again (an L2 or last-level cache hit: the tile read it moments
-        // ago) rather than held across the look-back: 28 fewer VGPRs at 16
-        // positions per thread, three workgroups per CU instead of two
-        // (measured 1721 -> 1649 us per coordinate at N = 2^27; without the
-        // carried sums, held w measured faster, 1525 against 1600 us)
-        const double *wsrc = a.w_comp;
-        asm volatile("" : "+s"(wsrc));  // a new load, not the staged values
-        if (cnt == TILE) {
-#pragma unroll
-            for (int q = 0; q < R; ++q) {
-                const double2 *wp = reinterpret_cast<const double2 *>(
-                    wsrc + t0 + (int64_t)q * BLOCK * C + (int64_t)tid * C);
-#pragma unroll
-                for (int h = 0; h < C / 2; ++h) {
-                    const double2 v = wp[h];
-                    wv[q * C + 2 * h] = v.x;
-                    wv[q * C + 2 * h + 1] = v.y;
-                }
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < IPT; ++i) {
-                const int64_t k = t0 + tile_pos<BLOCK, IPT>(i, tid);
-                wv[i] = k < a.n ? wsrc[k] : 0.0;
-            }
-        }
     }
     // the tile's prefix: added to the FP64 in-tile prefixes now, or (F32S)
     // to each run end's FP32 in-tile prefix in FP64
@@ -764,9 +801,25 @@ __global__ __launch_bounds__(BLOCK) void k_fused(FusedCall a, WsView ws, int64_t
     // ---- 7. running prefix, transform at run ends, reduction
     asm volatile("" : "+v"(xb));
     AT acc_t[2] = {(AT)0, (AT)0};  // sum d G, sum d (H - G^2) of this thread
-    double acc[NR];
+    double acc[NE];
 #pragma unroll
-    for (int c = 0; c < NR; ++c) acc[c] = 0.0;
+    for (int c = 0; c < NE; ++c) acc[c] = 0.0;
+    // EMIT: the sums over column jnext's positions, of (e, e w) in acc[3..]
+    // and of the same where x_j = 1 behind them
+    auto emit = [&](int i, AT ei) {
+        if constexpr (EMIT) {
+            constexpr int H = NX / 2;
+            const bool nb = (nbits >> i) & 1u;
+            const bool both = nb && ((xb >> i) & 1u);
+            acc[3] += nb ? (double)ei : 0.0;
+            acc[3 + H] += both ? (double)ei : 0.0;
+            if constexpr (MODEL == SS_FINE_GRAY) {
+                const double ew = (double)(ei * (AT)wv[i]);
+                acc[4] += nb ? ew : 0.0;
+                acc[4 + H] += both ? ew : 0.0;
+            }
+        }
+    };
     LogSum lsum;
     // Every event count of the wave's elements is 0 or 1 (and Fine-Gray
     // finds G in LDS): the run ends are evaluated without a branch, groups
@@ -795,13 +848,7 @@ __global__ __launch_bounds__(BLOCK) void k_fused(FusedCall a, WsView ws, int64_t
                     const int i = q * C + k0 + u;
                     const AT ei = (AT)ev[i];
                     Tx::add(S, ei, xb, i, s_xv, wv[MODEL == SS_FINE_GRAY ? i : 0]);
-                    if constexpr (CARRY) {
-                        const bool nb = (nbits >> i) & 1u;
-                        const AT ew = ei * (AT)wv[i];
-                        const bool xj = (xb >> i) & 1u;
-                        acc[3] += nb ? (double)ew : 0.0;
-                        acc[4] += nb && xj ? (double)ew : 0.0;
-                    }
+                    emit(i, ei);
                     const bool ev1 = (dw[i / 4] >> (8 * (i % 4))) & 1u;
                     double Sd[NX];
 #pragma unroll
@@ -839,14 +886,7 @@ __global__ __launch_bounds__(BLOCK) void k_fused(FusedCall a, WsView ws, int64_t
             const int i = q * C + k;
             const AT ei = (AT)ev[i];
             Tx::add(S, ei, xb, i, s_xv, wv[MODEL == SS_FINE_GRAY ? i : 0]);
-            if constexpr (CARRY) {
-                // sum e w and sum e w x_j over column jnext's positions
-                const bool nb = (nbits >> i) & 1u;
-                const AT ew = ei * (AT)wv[i];
-                const bool xj = (xb >> i) & 1u;
-                acc[3] += nb ? (double)ew : 0.0;
-                acc[4] += nb && xj ? (double)ew : 0.0;
-            }
+            emit(i, ei);
             int d = (int)((dw[i / 4] >> (8 * (i % 4))) & 255u);
             if (d == 255) d = a.d32[t0 + tile_pos<BLOCK, IPT>(i, tid)];
             // the run end's prefix S0, S1, S2; Fine-Gray adds G(Y) times the
@@ -885,39 +925,55 @@ __global__ __launch_bounds__(BLOCK) void k_fused(FusedCall a, WsView ws, int64_t
     acc[0] = (double)acc_t[0];
     acc[1] = (double)acc_t[1];
     if (a.want_log) acc[2] = lsum.value();
-    block_sum<NR, BLOCK>(acc, s_red);
+    block_sum<NE, BLOCK>(acc, s_red);
     if (tid == 0) {
 #pragma unroll
-        for (int c = 0; c < NR; ++c) s_tsum[c] = acc[c];
+        for (int c = 0; c < NE; ++c) s_tsum[c] = acc[c];
     }
     __syncthreads();
     double tsum[NR];
 #pragma unroll
-    for (int c = 0; c < NR; ++c) tsum[c] = s_tsum[c];
+    for (int c = 0; c < 3; ++c) tsum[c] = s_tsum[c];
+    if constexpr (EMIT) {
+        // A: e, e x_next (, e w, e w x_next); D: the same where x_j = 1
+        constexpr int H = NX / 2;
+        double agg[NX];
+        tile_agg(agg);
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+            tsum[3 + 2 * h] = agg[2 * h];
+            tsum[3 + 2 * h + 1] = s_tsum[3 + h];
+            tsum[3 + NX + 2 * h] = agg[2 * h + 1];
+            tsum[3 + NX + 2 * h + 1] = s_tsum[3 + H + h];
+        }
+    }
+    const bool odd = EMIT && (epoch & 1u) != 0;
     double total[NR];
-    reduce_partials<BLOCK, NR, 8>(ws.part, ws.gpart, tile, ntiles, (epoch << 1) | 1u, ws.hdr,
-                                  tsum, total, s_red);
+    reduce_partials<BLOCK, NR, 8>(odd ? ws.sw_agg : ws.part, odd ? ws.sw_pre : ws.gpart, tile,
+                                  ntiles, (epoch << 1) | 1u, ws.hdr, tsum, total, s_red);
     SS_TRACE(ws, tile, 4);
     if (tile == ntiles - 1) {
-        finish<BLOCK, NR, CARRY>(a, ws, epoch, total, s_fgw, s_red);
+        finish<BLOCK, NR, EMIT && MODEL == SS_FINE_GRAY>(a, ws, epoch, total, s_red);
         SS_TRACE(ws, tile, 5);
     }
 }
 
-// Fine-Gray totals pass: applies the pending step (a1) and reduces
-// sum_r e_r x_r^m w_comp_r (m = 0, 1, 2) into hdr->fg_tot.
+// Fine-Gray sums pass: applies the pending step (a1), leaves every tile's and
+// group's tuple sums in fg_part and fg_gpart (the prefixes of the scan pass)
+// and the totals sum_r e_r x_r^m w_comp_r (m = 0, 1, 2) in hdr->fg_tot.
 // With FP32 storage of e (ET = float) the sums are still FP64.
 template <int BLOCK, int IPT, bool VALS, bool PREV, typename ET = double>
-__global__ __launch_bounds__(BLOCK) void k_fg_totals(FusedCall a, WsView ws,
-                                                     int64_t ntiles)
+__global__ __launch_bounds__(BLOCK) void k_fg_sums(FusedCall a, WsView ws, int64_t ntiles)
 {
     constexpr int TILE = BLOCK * IPT;
     constexpr int NW = BLOCK / kWave;
     __shared__ __attribute__((aligned(16))) uint8_t s_flag[TILE];
     __shared__ __attribute__((aligned(16))) double s_xv[VALS ? TILE : 1];
     __shared__ double s_ep[PREV ? TILE : 1];
-    __shared__ double s_red[NW * 4];
-    __shared__ double s_tsum[3];
+    using Tx = Tuple<BLOCK, SS_FINE_GRAY, VALS>;
+    constexpr int NX = Tx::NX;
+    __shared__ double s_red[NW * NX + NX];
+    __shared__ double s_tsum[NX];
     const int tid = threadIdx.x;
     // every wave reads the epoch itself (see k_fused)
     const uint64_t epoch = ld_relaxed_u64(&ws.hdr->fg_epoch);
@@ -936,31 +992,89 @@ __global__ __launch_bounds__(BLOCK) void k_fg_totals(FusedCall a, WsView ws,
     uint32_t dw[(IPT + 3) / 4];
     const uint32_t xbits = stage_tile<BLOCK, IPT, true, VALS, PREV, false, false, ET>(
         a, t0, cnt, chunk0, chunk1, s_flag, s_xv, s_ep, ev, wv, dw);
-    double acc[3] = {0.0, 0.0, 0.0};
+    double acc[NX];
 #pragma unroll
-    for (int i = 0; i < IPT; ++i) {
-        const double x = x_at<BLOCK, VALS>(xbits, i, s_xv);
-        const double ew = (double)ev[i] * wv[i];
-        acc[0] += ew;
-        acc[1] += ew * x;
-        acc[2] += ew * x * x;
-    }
-    block_sum<3, BLOCK>(acc, s_red);
+    for (int c = 0; c < NX; ++c) acc[c] = 0.0;
+#pragma unroll
+    for (int i = 0; i < IPT; ++i) Tx::add(acc, (double)ev[i], xbits, i, s_xv, wv[i]);
+    block_sum<NX, BLOCK>(acc, s_red);
     if (tid == 0) {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) s_tsum[c] = acc[c];
+        for (int c = 0; c < NX; ++c) s_tsum[c] = acc[c];
     }
     __syncthreads();
-    const double tsum[3] = {s_tsum[0], s_tsum[1], s_tsum[2]};
-    double t[3];
-    reduce_partials<BLOCK, 3, 4>(ws.fg_part, ws.fg_gpart, tile, ntiles, tag, ws.hdr, tsum, t,
-                                 s_red);
+    double tsum[NX], t[NX];
+#pragma unroll
+    for (int c = 0; c < NX; ++c) tsum[c] = s_tsum[c];
+    reduce_partials<BLOCK, NX, 4>(ws.fg_part, ws.fg_gpart, tile, ntiles, tag, ws.hdr, tsum, t,
+                                  s_red);
     if (tile == ntiles - 1) {
         if (tid == 0) {
-#pragma unroll
-            for (int c = 0; c < 3; ++c) ws.hdr->fg_tot[c] = t[c];
+            ws.hdr->fg_tot[0] = t[Tx::EW];
+            ws.hdr->fg_tot[1] = t[Tx::EXW];
+            ws.hdr->fg_tot[2] = t[Tx::EXXW];
             st_relaxed_u64(&ws.hdr->fg_epoch, epoch + 1);
         }
+    }
+}
+
+// The end of a 0/1 sweep in per-coordinate launches: eta += steps[j] on the
+// rows of every column j in [j_begin, j_end), in that order, and e = exp(eta).
+// One wave owns a chunk of SS_CHUNK positions with its eta in LDS, so the
+// columns follow one another without a barrier; it takes the bounds of 64
+// columns in one set of loads and has the rows of kEtaAhead columns in
+// flight.  Bound: the column indices, 4 bytes per non-zero.
+constexpr int kEtaAhead = 4;
+
+__global__ __launch_bounds__(256) void k_sweep_eta(int64_t n, int32_t j_begin, int32_t j_end,
+                                                   const double *steps, Column col, double *eta,
+                                                   double *e)
+{
+    __shared__ double s_eta[256 / kWave][SS_CHUNK];
+    const int lane = lane_id(), w = threadIdx.x / kWave;
+    const int64_t t = (int64_t)blockIdx.x * (256 / kWave) + w;
+    const int64_t k0 = t * SS_CHUNK;
+    if (k0 >= n) return;  // the whole wave; no barrier below
+    const int32_t cnt = (int32_t)min((int64_t)SS_CHUNK, n - k0);
+    double *h = s_eta[w];
+    for (int32_t i = lane; i < cnt; i += kWave) h[i] = eta[k0 + i];
+    for (int32_t jb = j_begin; jb < j_end; jb += kWave) {
+        const int m = min(kWave, j_end - jb);
+        int64_t lo = 0;
+        int32_t len = 0;
+        double st = 0.0;
+        if (lane < m) {
+            const int32_t j = jb + lane;
+            const int32_t *cp = col.chunk_ptr + (int64_t)j * col.nchunk1 + t;
+            const int32_t a = cp[0];
+            lo = col.col_ptr[j] + a;
+            st = steps[j];
+            len = st != 0.0 ? cp[1] - a : 0;
+        }
+        for (int x0 = 0; x0 < m; x0 += kEtaAhead) {
+            int32_t r[kEtaAhead], l[kEtaAhead];
+            const int32_t *rp[kEtaAhead];
+#pragma unroll
+            for (int u = 0; u < kEtaAhead; ++u) {
+                const int x = min(x0 + u, kWave - 1);
+                l[u] = x0 + u < m ? __builtin_amdgcn_readlane(len, x) : 0;
+                const uint32_t p0 = __builtin_amdgcn_readlane((int)(lo & 0xffffffff), x);
+                const uint32_t p1 = __builtin_amdgcn_readlane((int)(lo >> 32), x);
+                rp[u] = col.rows + (int64_t)(((uint64_t)p1 << 32) | p0);
+                r[u] = lane < l[u] ? rp[u][lane] : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < kEtaAhead; ++u) {
+                const double s = read_lane(st, min(x0 + u, kWave - 1));
+                if (lane < l[u]) h[r[u] - k0] += s;
+                for (int32_t o = kWave + lane; o < l[u]; o += kWave) h[rp[u][o] - k0] += s;
+            }
+        }
+    }
+    for (int32_t i = lane; i < cnt; i += kWave) {
+        const double x = h[i];
+        eta[k0 + i] = x;
+        e[k0 + i] = exp(x);
     }
 }
 
@@ -1072,24 +1186,23 @@ bool fused_ws_view(void *ws, size_t ws_bytes, int64_t n, WsView *v)
 
 namespace {
 
-template <int IPT, int MODEL, bool VALS, bool PREV, bool CARRY = false>
+template <int IPT, int MODEL, bool VALS, bool PREV, int PRE = 0, bool EMIT = false>
 void launch_fused_t(const FusedCall &a, const WsView &ws, int64_t ntiles, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_fused<kBlock, IPT, MODEL, VALS, PREV, CARRY>), dim3((unsigned)ntiles),
-                       dim3(kBlock), 0, s, a, ws, ntiles);
+    hipLaunchKernelGGL((k_fused<kBlock, IPT, MODEL, VALS, PREV, PRE, EMIT>),
+                       dim3((unsigned)ntiles), dim3(kBlock), 0, s, a, ws, ntiles);
 }
 
 template <int IPT>
-void launch_fg_totals_t(const FusedCall &a, const WsView &ws, int64_t ntiles, bool vals,
+void launch_fg_sums_t(const FusedCall &a, const WsView &ws, int64_t ntiles, bool vals,
                         bool prev, hipStream_t s)
 {
     const dim3 g((unsigned)ntiles), b(kBlock);
     if (vals) {
-        if (prev) hipLaunchKernelGGL((k_fg_totals<kBlock, IPT, true, true>), g, b, 0, s, a, ws, ntiles);
-        else      hipLaunchKernelGGL((k_fg_totals<kBlock, IPT, true, false>), g, b, 0, s, a, ws, ntiles);
-    } else {
-        if (prev) hipLaunchKernelGGL((k_fg_totals<kBlock, IPT, false, true>), g, b, 0, s, a, ws, ntiles);
-        else      hipLaunchKernelGGL((k_fg_totals<kBlock, IPT, false, false>), g, b, 0, s, a, ws, ntiles);
+        if (prev) hipLaunchKernelGGL((k_fg_sums<kBlock, IPT, true, true>), g, b, 0, s, a, ws, ntiles);
+        else      hipLaunchKernelGGL((k_fg_sums<kBlock, IPT, true, false>), g, b, 0, s, a, ws, ntiles);
+    } else {  // (a 0/1 column's pending update rides in the scan pass)
+        hipLaunchKernelGGL((k_fg_sums<kBlock, IPT, false, false>), g, b, 0, s, a, ws, ntiles);
     }
 }
 
@@ -1097,13 +1210,14 @@ void launch_fg_totals_t(const FusedCall &a, const WsView &ws, int64_t ntiles, bo
 template <int IPT, int MODEL, bool VALS>
 void launch_fused_f32_t(const FusedCall &a, const WsView &ws, int64_t ntiles, hipStream_t s)
 {
+    constexpr int PRE = MODEL == SS_FINE_GRAY ? 1 : 0;
     const dim3 g((unsigned)ntiles), b(kBlock);
     if (a.f32_sums)
-        hipLaunchKernelGGL((k_fused<kBlock, IPT, MODEL, VALS, false, false, float, true>), g, b,
-                           0, s, a, ws, ntiles);
-    else
-        hipLaunchKernelGGL((k_fused<kBlock, IPT, MODEL, VALS, false, false, float, false>), g,
+        hipLaunchKernelGGL((k_fused<kBlock, IPT, MODEL, VALS, false, PRE, false, float, true>), g,
                            b, 0, s, a, ws, ntiles);
+    else
+        hipLaunchKernelGGL((k_fused<kBlock, IPT, MODEL, VALS, false, PRE, false, float, false>),
+                           g, b, 0, s, a, ws, ntiles);
 }
 
 template <int IPT>
@@ -1111,11 +1225,11 @@ int32_t launch_fused_f32_ipt(const FusedCall &a, const WsView &ws, int64_t ntile
                              hipStream_t s)
 {
     const bool vals = a.col.vals != nullptr;
-    if (a.jprev >= 0 || a.jnext >= 0 || a.ccd || a.fg_have_totals) return SS_EUNSUPPORTED;
+    if (a.jprev >= 0 || a.jnext >= 0 || a.ccd || a.have_sums) return SS_EUNSUPPORTED;
     const dim3 g((unsigned)ntiles), b(kBlock);
     if (a.model == SS_FINE_GRAY) {
-        if (vals) hipLaunchKernelGGL((k_fg_totals<kBlock, IPT, true, false, float>), g, b, 0, s, a, ws, ntiles);
-        else      hipLaunchKernelGGL((k_fg_totals<kBlock, IPT, false, false, float>), g, b, 0, s, a, ws, ntiles);
+        if (vals) hipLaunchKernelGGL((k_fg_sums<kBlock, IPT, true, false, float>), g, b, 0, s, a, ws, ntiles);
+        else      hipLaunchKernelGGL((k_fg_sums<kBlock, IPT, false, false, float>), g, b, 0, s, a, ws, ntiles);
         SS_LAUNCH_CHECK();
         FusedCall c = a;
         c.clear_error = 0;
@@ -1137,37 +1251,39 @@ int32_t launch_fused_ipt(const FusedCall &a, const WsView &ws, hipStream_t s)
     if (a.e32) return launch_fused_f32_ipt<IPT>(a, ws, ntiles, s);
     const bool vals = a.col.vals != nullptr;
     const bool prev = a.jprev >= 0;
-    FusedCall b = a;
+    const bool emit = a.jnext >= 0;
+    // A and D travel between launches of 0/1 designs, behind a pending update
+    if (vals && (emit || a.have_sums)) return SS_EUNSUPPORTED;
+    if (!vals && (a.have_sums != 0) != prev) return SS_EUNSUPPORTED;
     if (a.model == SS_FINE_GRAY) {
-        // the carry of the weighted totals needs a 0/1 design
-        const bool carry = a.jnext >= 0;
-        if ((carry || a.fg_have_totals) && vals) return SS_EUNSUPPORTED;
-        bool prev_scan = prev;
-        if (!a.fg_have_totals) {
-            // totals pass (and the pending a1 update), then the scan pass
-            launch_fg_totals_t<IPT>(a, ws, ntiles, vals, prev, s);
+        if constexpr (IPT != 8) {  // default_ipt
+            return SS_EUNSUPPORTED;
+        } else if (a.have_sums) {
+            if (emit) launch_fused_t<IPT, SS_FINE_GRAY, false, true, 2, true>(a, ws, ntiles, s);
+            else      launch_fused_t<IPT, SS_FINE_GRAY, false, true, 2, false>(a, ws, ntiles, s);
+        } else {
+            // sums pass (and a valued column's pending a1 update), then the scan
+            launch_fg_sums_t<IPT>(a, ws, ntiles, vals, prev, s);
             SS_LAUNCH_CHECK();
+            FusedCall b = a;
             b.jprev = -1;
             b.clear_error = 0;
-            prev_scan = false;
+            if (vals)
+                launch_fused_t<IPT, SS_FINE_GRAY, true, false, 1>(b, ws, ntiles, s);
+            else if (emit)
+                launch_fused_t<IPT, SS_FINE_GRAY, false, false, 1, true>(b, ws, ntiles, s);
+            else
+                launch_fused_t<IPT, SS_FINE_GRAY, false, false, 1>(b, ws, ntiles, s);
         }
-        if (vals) {
-            launch_fused_t<IPT, SS_FINE_GRAY, true, false>(b, ws, ntiles, s);
-        } else if (carry) {
-            if (prev_scan) launch_fused_t<IPT, SS_FINE_GRAY, false, true, true>(b, ws, ntiles, s);
-            else           launch_fused_t<IPT, SS_FINE_GRAY, false, false, true>(b, ws, ntiles, s);
-        } else {
-            if (prev_scan) launch_fused_t<IPT, SS_FINE_GRAY, false, true>(b, ws, ntiles, s);
-            else           launch_fused_t<IPT, SS_FINE_GRAY, false, false>(b, ws, ntiles, s);
-        }
+    } else if (a.have_sums) {
+        if (emit) launch_fused_t<IPT, SS_COX, false, true, 2, true>(a, ws, ntiles, s);
+        else      launch_fused_t<IPT, SS_COX, false, true, 2, false>(a, ws, ntiles, s);
+    } else if (vals) {
+        if (prev) launch_fused_t<IPT, SS_COX, true, true>(a, ws, ntiles, s);
+        else      launch_fused_t<IPT, SS_COX, true, false>(a, ws, ntiles, s);
     } else {
-        if (vals) {
-            if (prev) launch_fused_t<IPT, SS_COX, true, true>(b, ws, ntiles, s);
-            else      launch_fused_t<IPT, SS_COX, true, false>(b, ws, ntiles, s);
-        } else {
-            if (prev) launch_fused_t<IPT, SS_COX, false, true>(b, ws, ntiles, s);
-            else      launch_fused_t<IPT, SS_COX, false, false>(b, ws, ntiles, s);
-        }
+        if (emit) launch_fused_t<IPT, SS_COX, false, false, 0, true>(a, ws, ntiles, s);
+        else      launch_fused_t<IPT, SS_COX, false, false>(a, ws, ntiles, s);
     }
     SS_LAUNCH_CHECK();
     return SS_OK;
@@ -1183,12 +1299,12 @@ int32_t launch_plain_ipt(const FusedCall &a, const WsView &ws, hipStream_t s)
     if (a.e32) return launch_fused_f32_ipt<IPT>(a, ws, ntiles, s);
     const bool vals = a.col.vals != nullptr;
     if (a.model == SS_FINE_GRAY) {
-        launch_fg_totals_t<IPT>(a, ws, ntiles, vals, false, s);
+        launch_fg_sums_t<IPT>(a, ws, ntiles, vals, false, s);
         SS_LAUNCH_CHECK();
         FusedCall b = a;
         b.clear_error = 0;
-        if (vals) launch_fused_t<IPT, SS_FINE_GRAY, true, false>(b, ws, ntiles, s);
-        else      launch_fused_t<IPT, SS_FINE_GRAY, false, false>(b, ws, ntiles, s);
+        if (vals) launch_fused_t<IPT, SS_FINE_GRAY, true, false, 1>(b, ws, ntiles, s);
+        else      launch_fused_t<IPT, SS_FINE_GRAY, false, false, 1>(b, ws, ntiles, s);
     } else {
         if (vals) launch_fused_t<IPT, SS_COX, true, false>(a, ws, ntiles, s);
         else      launch_fused_t<IPT, SS_COX, false, false>(a, ws, ntiles, s);
@@ -1201,13 +1317,13 @@ int32_t launch_plain_ipt(const FusedCall &a, const WsView &ws, hipStream_t s)
 
 int32_t launch_fused(const FusedCall &a, const WsView &ws, hipStream_t s)
 {
-    const bool plain = a.jprev < 0 && a.jnext < 0 && !a.ccd && !a.fg_have_totals;
+    const bool plain = a.jprev < 0 && a.jnext < 0 && !a.ccd && !a.have_sums;
     if (plain) {
         const int32_t storage = !a.e32 ? SS_STORAGE_F64
                                 : a.f32_sums ? SS_STORAGE_F32_SUMS32 : SS_STORAGE_F32;
         int32_t ipt = tune_lookup(SS_TUNE_GRAD_HESS, a.model, storage,
                                   a.col.vals != nullptr, a.n);
-        if (!ipt) ipt = default_ipt(a.n);
+        if (!ipt) ipt = default_ipt(a.model, a.n);
         switch (ipt) {
         case 4: return launch_plain_ipt<4>(a, ws, s);
         case 8: return launch_plain_ipt<8>(a, ws, s);
@@ -1219,7 +1335,18 @@ int32_t launch_fused(const FusedCall &a, const WsView &ws, hipStream_t s)
     // the per-coordinate launches of a sweep (pending update, carry,
     // coordinate update): tiles of 2048 or 4096 positions
     if (a.e32) return SS_EUNSUPPORTED;
-    return default_ipt(a.n) == 8 ? launch_fused_ipt<8>(a, ws, s) : launch_fused_ipt<16>(a, ws, s);
+    return default_ipt(a.model, a.n) == 8 ? launch_fused_ipt<8>(a, ws, s)
+                                          : launch_fused_ipt<16>(a, ws, s);
+}
+
+int32_t launch_sweep_eta(int64_t n, int32_t j_begin, int32_t j_end, const double *steps,
+                         const Column &col, double *eta, double *e, hipStream_t s)
+{
+    const unsigned grid = (unsigned)ceil_div(n, (int64_t)SS_CHUNK * (256 / kWave));
+    hipLaunchKernelGGL(k_sweep_eta, dim3(grid), dim3(256), 0, s, n, j_begin, j_end, steps, col,
+                       eta, e);
+    SS_LAUNCH_CHECK();
+    return SS_OK;
 }
 
 int32_t launch_apply(int64_t n, int32_t j, const double *step, double *eta,

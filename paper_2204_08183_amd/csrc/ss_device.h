@@ -484,6 +484,39 @@ __device__ __forceinline__ void ld_pairs<6>(const u32x4 *p, u32x4 (&r)[6])
 }
 
 template <>
+__device__ __forceinline__ void ld_pairs<5>(const u32x4 *p, u32x4 (&r)[5])
+{
+    asm volatile(
+                 "global_load_dwordx4 %0, %5, off sc1\n\t"
+                 "global_load_dwordx4 %1, %5, off offset:16 sc1\n\t"
+                 "global_load_dwordx4 %2, %5, off offset:32 sc1\n\t"
+                 "global_load_dwordx4 %3, %5, off offset:48 sc1\n\t"
+                 "global_load_dwordx4 %4, %5, off offset:64 sc1\n\t"
+                 "s_waitcnt vmcnt(0)"
+                 : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4])
+                 : "v"(p)
+                 : "memory");
+}
+
+template <>
+__device__ __forceinline__ void ld_pairs<8>(const u32x4 *p, u32x4 (&r)[8])
+{
+    asm volatile(
+                 "global_load_dwordx4 %0, %8, off sc1\n\t"
+                 "global_load_dwordx4 %1, %8, off offset:16 sc1\n\t"
+                 "global_load_dwordx4 %2, %8, off offset:32 sc1\n\t"
+                 "global_load_dwordx4 %3, %8, off offset:48 sc1\n\t"
+                 "global_load_dwordx4 %4, %8, off offset:64 sc1\n\t"
+                 "global_load_dwordx4 %5, %8, off offset:80 sc1\n\t"
+                 "global_load_dwordx4 %6, %8, off offset:96 sc1\n\t"
+                 "global_load_dwordx4 %7, %8, off offset:112 sc1\n\t"
+                 "s_waitcnt vmcnt(0)"
+                 : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7])
+                 : "v"(p)
+                 : "memory");
+}
+
+template <>
 __device__ __forceinline__ void ld_pairs<9>(const u32x4 *p, u32x4 (&r)[9])
 {
     asm volatile("global_load_dwordx4 %0, %9, off sc1\n\t"

@@ -261,12 +261,10 @@ struct FusedCall {
     // out[1] = l, out[2] = pi with pi the penalty of Sec. 2.3 at beta_ll
     int32_t obj_penalty;
     double obj_lambda;
-    // Fine-Gray with a 0/1 design inside a sweep: the totals
-    // sum e w x^m over column j are in hdr->fg_tot already (fg_have_totals,
-    // carried by the previous launch), and jnext >= 0 asks the last tile to
-    // carry the totals of column jnext over the e this coordinate's step
-    // leaves behind
-    int32_t fg_have_totals;
+    // 0/1 design inside a sweep: the previous launch left the tile sums A and
+    // D of column j (and the Fine-Gray totals over the updated e in
+    // hdr->fg_tot), and jnext >= 0 asks this one to leave those of jnext
+    int32_t have_sums;
     int32_t jnext;
     // error reporting of calls without a caller-owned workspace: the first
     // tile of the call's first launch clears the error word, the last tile
@@ -279,9 +277,15 @@ int32_t launch_fused(const FusedCall &call, const WsView &ws,
                      hipStream_t stream);
 
 // ------------------------------------------------------------ launch shapes
-// Positions per thread of the single-pass fused kernel when nothing is
-// tuned: tiles of 2048 positions up to 1.5 M positions, of 4096 above.
-inline int32_t default_ipt(int64_t n) { return n <= ((int64_t)3 << 19) ? 8 : 16; }
+// Positions per thread of the fused kernel when nothing is tuned.  Cox, whose
+// tiles look back: tiles of 2048 positions up to 1.5 M positions, of 4096
+// above.  Fine-Gray, whose tiles wait for none: 2048 throughout (us per
+// coordinate at 4 / 8 / 16 / 32: N = 1e6 17.7 / 17.7 / 19.5 / 27.5, N = 5e6
+// 51 / 49 / 54 / 70, N = 2e7 196 / 172 / 182 / 233).
+inline int32_t default_ipt(int32_t model, int64_t n)
+{
+    return model == SS_FINE_GRAY || n <= ((int64_t)3 << 19) ? 8 : 16;
+}
 // The tuned choice for a launch (0: none); see tune.hip.
 int32_t tune_lookup(int32_t kind, int32_t model, int32_t storage, int32_t valued, int64_t n);
 // A choice forced on the calling thread's launches of one kind while a
@@ -317,6 +321,8 @@ struct SweepCall {
 };
 int32_t launch_sweep_persistent(const SweepCall &call, const WsView &ws,
                                 hipStream_t stream);
+int32_t launch_sweep_eta(int64_t n, int32_t j_begin, int32_t j_end, const double *steps,
+                         const Column &col, double *eta, double *e, hipStream_t stream);
 int32_t launch_apply(int64_t n, int32_t j, const double *step, double *eta,
                      double *e, const Column &col, hipStream_t stream);
 int32_t launch_ccd_scalar(int32_t penalty, double lambda, int32_t j,

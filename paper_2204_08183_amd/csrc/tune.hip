@@ -111,7 +111,7 @@ int32_t ss_tune_get(int32_t kind, int32_t model, int32_t storage, int32_t valued
     if (bad_key(kind, model, storage) || n < 1) return SS_EINVAL;
     const int32_t t = tune_lookup(kind, model, storage, valued, n);
     if (t) return t;
-    return kind == SS_TUNE_GRAD_HESS ? default_ipt(n) : 0;
+    return kind == SS_TUNE_GRAD_HESS ? default_ipt(model, n) : 0;
 }
 
 int32_t ss_tune_has(int32_t kind, int32_t model, int32_t storage, int32_t valued, int64_t n)

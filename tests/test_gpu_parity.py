@@ -560,3 +560,41 @@ def test_sweep_shapes(n, model, valued):
     prob.sweep("l2", 1.0, j_begin=3, j_end=p)
     np.testing.assert_allclose(prob.beta.cpu().numpy(), beta, rtol=1e-9, atol=1e-13)
     assert prob.workspace_error() == 0
+
+
+# The per-coordinate launches of a 0/1 sweep take a tile's prefix from the
+# tile sums the launch before left (tiles of 2048 positions in groups of 64)
+# and bring eta up to date at the end, 64 columns and 64 non-zeros of a chunk
+# at a time: around one tile, one, two and three groups.
+@pytest.mark.parametrize("model", ["cox", "fg"])
+@pytest.mark.parametrize("n,p,density", [
+    (1000, 3, 0.2), (2048, 65, 0.1), (2049, 64, 0.5), (131_072, 5, 0.05), (131_073, 70, 0.1),
+    (262_145, 4, 0.05)])
+def test_sweep_launches_tile_sums(model, n, p, density, monkeypatch):
+    _sweep_env(monkeypatch, "launch")
+    c = make_case(model, n, p, 90 + p, 0, density)
+    c["y"] = np.ceil(c["y"] * n)  # some tie runs
+    c["eta"] = np.zeros(n)
+    prob = gpu_problem(model, c)
+    g12 = torch.zeros(3 * p, dtype=torch.float64, device=DEV)
+    beta, delta, eta, hist = oracle_sweeps(model, c, occd.PENALTY_L2, 1.0, 1)
+    for upto in (None, p):  # with and without the per-coordinate output
+        prob.set_beta(torch.zeros(p), np.zeros(n))
+        prob.reset_trust()
+        prob.sweep("l2", 1.0, g12_out=g12 if upto else None)
+        np.testing.assert_allclose(prob.beta.cpu().numpy(), beta, rtol=1e-9, atol=1e-13)
+    got = g12.cpu().numpy().reshape(-1, 3)
+    for j in range(p):
+        g1, g2, s1, s2 = hist[j]
+        assert abs(got[j, 0] - g1) <= 1e-10 * s1, (j, got[j, 0], g1)
+        assert abs(got[j, 1] - g2) <= 1e-10 * s2, (j, got[j, 1], g2)
+    order = prob.perm.cpu().numpy()
+    np.testing.assert_allclose(prob.eta.cpu().numpy(), eta[order], rtol=1e-9, atol=1e-12)
+    np.testing.assert_allclose(prob.e.cpu().numpy(), np.exp(prob.eta.cpu().numpy()), rtol=1e-14)
+    # parts of a sweep, of one and more coordinates, continue from the state
+    prob.set_beta(torch.zeros(p), np.zeros(n))
+    prob.reset_trust()
+    for a, b in ((0, 1), (1, 3), (3, p)):
+        prob.sweep("l2", 1.0, j_begin=a, j_end=b)
+    np.testing.assert_allclose(prob.beta.cpu().numpy(), beta, rtol=1e-9, atol=1e-13)
+    assert prob.workspace_error() == 0

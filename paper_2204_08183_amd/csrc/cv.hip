@@ -508,6 +508,11 @@ __device__ void cv_apply_steps(const CvArgs &a, double *eta, double *e, const ui
 // A1 + expm1(s) D1 (e at column j + 1; D1 = e at both columns), all
 // summed during the pass of coordinate j before s is known.  Both halves
 // then take the same Newton step from the same numbers.
+#ifndef SS_CV_GROUP
+#define SS_CV_GROUP 4
+#endif
+constexpr int kCvGroup = SS_CV_GROUP;
+
 template <int BLOCK, int IPT, int KH>
 __global__ __launch_bounds__(BLOCK) void k_cv_sweep(CvArgs a)
 {
@@ -689,16 +694,27 @@ __global__ __launch_bounds__(BLOCK) void k_cv_sweep(CvArgs a)
             par ^= 1;
             double S0 = p0 + (i0 - t0);
             double S1 = p1 + (i1 - t1);
+            // kCvGroup positions at a time without a branch, so that their
+            // reciprocals overlap; G = 0 off the run ends (S0 may be 0
+            // before the replicate's first subject)
 #pragma unroll
-            for (int i = 0; i < IPT; ++i) {
-                S0 += cur.v[i];
-                S1 += ((cur.x >> i) & 1u) ? cur.v[i] : 0.0;
-                const uint32_t d = dv[i];
-                if (d != 0u) {
-                    const double g = S1 / S0;
+            for (int i0 = 0; i0 < IPT; i0 += kCvGroup) {
+                double s0[kCvGroup], s1[kCvGroup];
+#pragma unroll
+                for (int u = 0; u < kCvGroup; ++u) {
+                    const int i = i0 + u;
+                    S0 += cur.v[i];
+                    S1 += ((cur.x >> i) & 1u) ? cur.v[i] : 0.0;
+                    s0[u] = S0;
+                    s1[u] = S1;
+                }
+#pragma unroll
+                for (int u = 0; u < kCvGroup; ++u) {
+                    const uint32_t d = dv[i0 + u];
+                    const double g = d != 0u ? s1[u] * recip(s0[u]) : 0.0;
                     const double dd = (double)d;
                     acc1 = fma(dd, g, acc1);
-                    acc2 = fma(dd, g - g * g, acc2);
+                    acc2 = fma(dd, fma(-g, g, g), acc2);
                 }
             }
             carry0 = c0;

@@ -150,12 +150,22 @@ def check(code, what):
         raise SurvScanError("%s failed: %s (%d)" % (what, status_string(code), code))
 
 
+# The argument marshalling is what bounds the smallest calls (one coordinate
+# at N = 1000: 9.1 us a call for 5.9 us on the GPU), so addresses go to ctypes
+# as plain integers (a dozen c_void_p objects take 2.2 us more) and the
+# current stream is asked for without building a Stream object (3.1 us).
 def _p(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(device):
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    if _raw_stream is None:
+        return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    index = device.index
+    return ctypes.c_void_p(_raw_stream(torch.cuda.current_device() if index is None else index))
 
 
 def chunk_count(n):

@@ -27,7 +27,7 @@
 #include <math.h>
 #include <stdlib.h>
 
-#include "ss_device.h"
+#include "exchange.h"
 
 namespace ss {
 
@@ -378,7 +378,12 @@ __global__ __launch_bounds__(256) void k_cv_fill(uint32_t *p, int64_t words)
 // Exchange block of one replicate (two-half launches): the epoch of its
 // exchanges, then per round parity a slot of half 0 and one of half 1, each
 // a run of 16-byte (value, tag) pairs.
-constexpr int kCvXchBytes = 1280;
+// Behind them the slots of the on-chip sweep: per round parity the late and the
+// early publications of up to kCvParts workgroups.
+constexpr int kCvHalfBytes = 1280;
+constexpr int kCvParts = 32;
+constexpr int kCvLateWords = 2, kCvEarlyWords = 8;
+constexpr int kCvXchBytes = kCvHalfBytes + 2 * kCvParts * (kCvLateWords + kCvEarlyWords) * 16;
 
 struct CvArgs {
     int64_t n, p, stride;
@@ -1178,6 +1183,472 @@ __global__ __launch_bounds__(BLOCK) void k_cv_sweep_fg(CvFgArgs f)
         st_relaxed_u64(cv_epoch(a, r), ep0 + (uint64_t)T + 1);
 }
 
+// ------------------------------------------------- sweep, all on chip
+// All replicates' e on the chip for the whole launch, where it fits: a
+// replicate is cut into K segments of 256 * IPT positions, one workgroup each
+// (two to a CU), that run the one-exchange scheme of the persistent sweep
+// (k_sweep1): A and D of the next coordinate published before the transform,
+// the partial sums after it, every workgroup of the replicate taking the same
+// step and its own prefix.  Against the kernels below, which stream e and the
+// counts of every replicate through a workgroup or two chunk by chunk for
+// every coordinate, nothing is loaded per coordinate but the column's bits,
+// there is one scan and one barrier for a thread's IPT positions instead of
+// one per 8, and all CUs work (K follows the number of replicates).
+//
+// Bound: VALU issue (about 40 instructions per position and coordinate).
+// Event counts sit in LDS four to a word, G (Fine-Gray) in LDS; eta is
+// brought up to date from the launch's steps at its end, 16 positions of a
+// thread at a time, and e = exp(eta) with it.
+constexpr int kCvOnBlock = 256;
+
+// coordinates per launch: their steps stay in LDS
+template <int MODEL>
+constexpr int cv_on_steps() { return MODEL == SS_FINE_GRAY ? 512 : 1024; }
+
+struct CvOnArgs {
+    CvArgs a;
+    const double *w, *g;  // Fine-Gray: the replicates' weights and G
+    int32_t parts;        // K
+};
+
+// Of a thread's positions, those whose e does not find a register (two
+// workgroups of four waves on a CU: 256 registers a thread, some 130 of them
+// for everything else).
+template <int IPT, int MODEL>
+constexpr int cv_on_lds()
+{
+    return MODEL == SS_COX && IPT > 56 ? IPT - 56 : 0;
+}
+
+template <int IPT, int MODEL>
+__global__ __launch_bounds__(kCvOnBlock, 2) void k_cv_on_chip(CvOnArgs f)
+{
+    const CvArgs &a = f.a;
+    constexpr int BLOCK = kCvOnBlock;
+    constexpr int S = BLOCK * IPT;
+    constexpr bool FG = MODEL == SS_FINE_GRAY;
+    constexpr int NG = IPT / 16;           // groups of 16 positions of a thread
+    constexpr int NT = FG ? 4 : 2;
+    constexpr int NW = BLOCK / kWave;
+    constexpr int NAD = 2 * NT;
+    constexpr int NAS = NAD + (FG ? 4 : 0);
+    constexpr int GT = 4;                  // run ends evaluated together
+    constexpr int LIST = cv_on_steps<MODEL>();
+    constexpr int EL = cv_on_lds<IPT, MODEL>();  // a thread's last positions: e in LDS
+    constexpr int ER = IPT - EL;
+    static_assert(IPT % 16 == 0, "16 bits of a column at a time");
+
+    __shared__ uint32_t s_d[IPT / 4][BLOCK];
+    __shared__ double s_g[FG ? IPT : 1][FG ? BLOCK : 1];
+    __shared__ double s_e[EL ? EL : 1][EL ? BLOCK : 1];
+    __shared__ double s_step[LIST];
+    __shared__ double s_wsum[NW][NT], s_wnext[NW][NT], s_wred[NW][2];
+    __shared__ double s_sum[2][NAS];
+
+    const int tid = threadIdx.x;
+    const int lane = lane_id();
+    const int w = tid / kWave;
+    const int K = f.parts;
+    const int64_t r = blockIdx.x / K;
+    const int b = (int)(blockIdx.x - r * K);
+    const int64_t off = r * a.stride;
+    const int64_t base = (int64_t)b * S + (int64_t)tid * IPT;
+    const int32_t jb = (int32_t)a.j_begin, je = (int32_t)a.j_end;
+    const uint64_t ep0 = ld_relaxed_u64(cv_epoch(a, r));
+    u32x4 *const slots = reinterpret_cast<u32x4 *>(a.xch + r * kCvXchBytes + kCvHalfBytes);
+    auto late_area = [&](uint64_t t) { return slots + (t & 1u) * (kCvParts * kCvLateWords); };
+    auto early_area = [&](uint64_t t) {
+        return slots + 2 * kCvParts * kCvLateWords + (t & 1u) * (kCvParts * kCvEarlyWords);
+    };
+
+    // ---- the segment's data (the stride is a multiple of 16 positions; past
+    // it a group holds nothing)
+    double er[ER], wv[FG ? IPT : 1];
+    auto put = [&](int i, double x) {
+        if (i < ER) er[i < ER ? i : 0] = x;
+        else s_e[EL ? i - ER : 0][tid] = x;
+    };
+    auto ev = [&](int i) { return i < ER ? er[i < ER ? i : 0] : s_e[EL ? i - ER : 0][tid]; };
+    bool big = false;  // a count of 255 or more is in d32
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+        const bool in = base + 16 * g < a.stride;
+        const int64_t k = off + (in ? base + 16 * g : 0);
+        const double2 *ep = reinterpret_cast<const double2 *>(a.e + k);
+        const uint4 dq = *reinterpret_cast<const uint4 *>(a.d8 + k);
+        const uint32_t dd[4] = {dq.x, dq.y, dq.z, dq.w};
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const double2 v = ep[q];
+            put(16 * g + 2 * q, in ? v.x : 0.0);
+            put(16 * g + 2 * q + 1, in ? v.y : 0.0);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t d = in ? dd[q] : 0u;
+            s_d[4 * g + q][tid] = d;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) big = big || ((d >> (8 * u)) & 255u) == 255u;
+        }
+        if constexpr (FG) {
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                wv[16 * g + q] = in ? f.w[k + q] : 0.0;
+                s_g[16 * g + q][tid] = in ? f.g[k + q] : 1.0;
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    const bool any_big = __any(big);
+    const int32_t *d32 = a.d32 + off + base;
+    auto count = [&](int i) -> uint32_t { return (s_d[i / 4][tid] >> (8 * (i % 4))) & 255u; };
+    auto column = [&](int32_t j, uint32_t (&x)[NG]) {
+        const uint8_t *col = a.xbits + (int64_t)j * (a.stride / 8);
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const bool in = base + 16 * g < a.stride;
+            const uint32_t v =
+                *reinterpret_cast<const uint16_t *>(col + (in ? (base + 16 * g) / 8 : 0));
+            x[g] = in ? v : 0u;
+        }
+    };
+    auto own_ad = [&](double (&t)[NAD]) {
+        double all[NT], next[NT];
+#pragma unroll
+        for (int c = 0; c < NT; ++c) {
+            all[c] = next[c] = 0.0;
+#pragma unroll
+            for (int q = 0; q < NW; ++q) {
+                all[c] += s_wsum[q][c];
+                next[c] += s_wnext[q][c];
+            }
+        }
+#pragma unroll
+        for (int h = 0; h < NT / 2; ++h) {
+            t[2 * h] = all[2 * h];
+            t[2 * h + 1] = next[2 * h];
+            t[NT + 2 * h] = all[2 * h + 1];
+            t[NT + 2 * h + 1] = next[2 * h + 1];
+        }
+    };
+    // Publishes this segment's A and D (wave NW - 1).
+    auto early = [&](uint64_t t, uint64_t tag) {
+        if (K > 1 && w == NW - 1) {
+            double v[NAD];
+            own_ad(v);
+            publish_slots<NAD, 1>(early_area(t) + b * kCvEarlyWords, 0, v, tag);
+        }
+    };
+    // The sums over the replicate's segments: `part` the partial sums, `ad`
+    // A and D before this segment (Fine-Gray: then the weighted totals).
+    auto collect = [&](uint64_t t, uint64_t tag, const double (&v)[2], double (&part)[2],
+                       double (&ad)[NAS]) -> bool {
+        wave_sums_to<2>(v, s_wred[w]);
+        __syncthreads();
+        double own[2];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            own[c] = 0.0;
+#pragma unroll
+            for (int q = 0; q < NW; ++q) own[c] += s_wred[q][c];
+        }
+        if (K == 1) {
+            double t4[NAD];
+            own_ad(t4);
+#pragma unroll
+            for (int c = 0; c < NAS; ++c) ad[c] = 0.0;
+            if constexpr (FG) {
+                ad[NAD] = t4[2];
+                ad[NAD + 1] = t4[3];
+                ad[NAD + 2] = t4[NT + 2];
+                ad[NAD + 3] = t4[NT + 3];
+            }
+            part[0] = own[0];
+            part[1] = own[1];
+            __syncthreads();
+            return true;
+        }
+        bool ok = true;
+        if (w == 0) {
+            publish_slots<2, 1>(late_area(t) + b * kCvLateWords, 0, own, tag);
+            const int from[2] = {0, 1}, mode[2] = {kAll, kAll};
+            ok = gather_sums<2, kCvLateWords, 2, 1>(late_area(t), kCvParts * kCvLateWords, a.hdr,
+                                                    lane, kWave, K, b, tag, from, mode, s_sum[0]);
+        } else if (w == 1) {
+            int from[NAS], mode[NAS];
+#pragma unroll
+            for (int c = 0; c < NAD; ++c) {
+                from[c] = c;
+                mode[c] = kBefore;
+            }
+            if constexpr (FG) {
+                const int tot[4] = {2, 3, NT + 2, NT + 3};
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    from[NAD + c < NAS ? NAD + c : 0] = tot[c];
+                    mode[NAD + c < NAS ? NAD + c : 0] = kAll;
+                }
+            }
+            ok = gather_sums<NAD, kCvEarlyWords, NAS, 1>(early_area(t), kCvParts * kCvEarlyWords,
+                                                         a.hdr, lane, kWave, K, b, tag, from, mode,
+                                                         s_sum[1]);
+        }
+        if (__syncthreads_or(!ok)) return false;
+        part[0] = s_sum[0][0];
+        part[1] = s_sum[0][1];
+#pragma unroll
+        for (int c = 0; c < NAS; ++c) ad[c] = s_sum[1][c];
+        return true;
+    };
+    auto prefix_from = [&](const double (&ad)[NAS], double em, double (&pre)[NT]) {
+#pragma unroll
+        for (int c = 0; c < NT; ++c) pre[c] = fma(em, ad[NT + c], ad[c]);
+        if constexpr (FG) {
+#pragma unroll
+            for (int c = 2; c < 4; ++c)
+                pre[c] = fma(em, ad[NAD + 2 + (c - 2)], ad[NAD + (c - 2)]) - pre[c];
+        }
+    };
+
+    // ---- round 0: aggregates of coordinate jb
+    uint32_t xp[NG], xc[NG], xn[NG];
+    // The columns' bits as new values: what an earlier pass selected with
+    // them is selected again, not kept (two registers per position).
+    auto fresh = [&]() {
+#pragma unroll
+        for (int g = 0; g < NG; ++g) asm volatile("" : "+v"(xc[g]), "+v"(xn[g]));
+    };
+    column(jb, xc);
+#pragma unroll
+    for (int g = 0; g < NG; ++g) xp[g] = xn[g] = 0u;
+    if (jb + 1 < je) column(jb + 1, xn);
+    double pre[NT];
+    {
+        double all[NT], next[NT];
+#pragma unroll
+        for (int c = 0; c < NT; ++c) all[c] = next[c] = 0.0;
+#pragma unroll
+        for (int i = 0; i < IPT; ++i) {
+            const bool x = (xc[i / 16] >> (i % 16)) & 1u;
+            const double e = ev(i);
+            all[0] += e;
+            next[0] += x ? e : 0.0;
+            if constexpr (FG) {
+                const double ew = e * wv[i];
+                all[2] += ew;
+                next[2] += x ? ew : 0.0;
+            }
+            if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        }
+        const uint64_t tag = (ep0 << 1) | 1u;
+        wave_sums_to<NT>(all, s_wsum[w]);
+        wave_sums_to<NT>(next, s_wnext[w]);
+        __syncthreads();
+        early(0, tag);
+        const double v[2] = {0.0, 0.0};
+        double part[2], ad[NAS];
+        if (!collect(0, tag, v, part, ad)) return;
+        prefix_from(ad, 0.0, pre);
+        __syncthreads();
+    }
+    double st_prev = 0.0, f_prev = 0.0;
+
+    for (int32_t j = jb; j < je; ++j) {
+        const uint64_t t = (uint64_t)(j - jb) + 1;
+        const uint64_t tag = ((ep0 + t) << 1) | 1u;
+        // the coordinate's constants, read before this round is published
+        const double cj = a.c[r * a.p + j];
+        double bj = a.beta[r * a.p + j], dj = a.delta[r * a.p + j];
+        // ---- the update of column j-1
+        if (st_prev != 0.0) {
+            const double fe = f_prev > -0.4 ? 1.0 + f_prev : exp(st_prev);
+#pragma unroll
+            for (int i = 0; i < IPT; ++i) {
+                if ((xp[i / 16] >> (i % 16)) & 1u) put(i, ev(i) * fe);
+                if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        fresh();
+        // ---- thread sums and their scan; A and D of j+1
+        double texcl[NT];
+        {
+            double run[NT], next[NT];
+#pragma unroll
+            for (int c = 0; c < NT; ++c) run[c] = next[c] = 0.0;
+#pragma unroll
+            for (int i = 0; i < IPT; ++i) {
+                const bool xj = (xc[i / 16] >> (i % 16)) & 1u, x1 = (xn[i / 16] >> (i % 16)) & 1u;
+                const double e = ev(i);
+                const double ex = xj ? e : 0.0;
+                run[0] += e;
+                run[1] += ex;
+                next[0] += x1 ? e : 0.0;
+                next[1] += x1 ? ex : 0.0;
+                if constexpr (FG) {
+                    const double ew = e * wv[i];
+                    const double ewx = xj ? ew : 0.0;
+                    run[2] += ew;
+                    run[3] += ewx;
+                    next[2] += x1 ? ew : 0.0;
+                    next[3] += x1 ? ewx : 0.0;
+                }
+                // in order: sums put off and interleaved positions take registers
+                if (i % 4 == 3) {
+#pragma unroll
+                    for (int c = 0; c < NT; ++c) asm volatile("" : "+v"(run[c]), "+v"(next[c]));
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            wave_sums_to<NT>(next, s_wnext[w]);
+#pragma unroll
+            for (int c = 0; c < NT; ++c) {
+                const double inc = dpp_incl_scan(run[c]);
+                texcl[c] = inc - run[c];
+                if (lane == kWave - 1) s_wsum[w][c] = inc;
+            }
+        }
+        __syncthreads();
+        fresh();
+        early(t, tag);
+#pragma unroll
+        for (int c = 0; c < NT; ++c) {
+            double before = 0.0;
+#pragma unroll
+            for (int q = 0; q < NW; ++q)
+                if (q < w) before += s_wsum[q][c];
+            texcl[c] += before;
+        }
+        // column j+2, in flight during the transform
+        uint32_t x2[NG];
+#pragma unroll
+        for (int g = 0; g < NG; ++g) x2[g] = 0u;
+        if (j + 2 < je) column(j + 2, x2);
+        // ---- transform at run ends and reduction, GT positions at a time so
+        // that their reciprocals overlap; G = 0 off the run ends (S0 may be 0
+        // before the replicate's first subject)
+        double v[2] = {0.0, 0.0};
+        {
+            double S0 = pre[0] + texcl[0], S1 = pre[1] + texcl[1];
+            double R0 = 0.0, R1 = 0.0;
+            if constexpr (FG) {
+                R0 = pre[2] - texcl[2];
+                R1 = pre[3] - texcl[3];
+            }
+#pragma unroll
+            for (int i0 = 0; i0 < IPT; i0 += GT) {
+                double t0[GT], t1[GT];
+                uint32_t d[GT];
+#pragma unroll
+                for (int u = 0; u < GT; ++u) {
+                    const int i = i0 + u;
+                    const bool xj = (xc[i / 16] >> (i % 16)) & 1u;
+                    const double e = ev(i);
+                    S0 += e;
+                    S1 += xj ? e : 0.0;
+                    t0[u] = S0;
+                    t1[u] = S1;
+                    if constexpr (FG) {
+                        const double ew = e * wv[i];
+                        R0 -= ew;
+                        R1 -= xj ? ew : 0.0;
+                        const double g = s_g[i][tid];
+                        t0[u] = fma(g, R0, t0[u]);
+                        t1[u] = fma(g, R1, t1[u]);
+                    }
+                    d[u] = count(i);
+                }
+                if (any_big) {
+#pragma unroll
+                    for (int u = 0; u < GT; ++u)
+                        if (d[u] == 255u) d[u] = (uint32_t)d32[i0 + u];
+                }
+#pragma unroll
+                for (int u = 0; u < GT; ++u) {
+                    const double g = d[u] != 0u ? t1[u] * recip(t0[u]) : 0.0;
+                    const double dd = (double)d[u];
+                    v[0] = fma(dd, g, v[0]);
+                    v[1] = fma(dd, fma(-g, g, g), v[1]);
+                }
+                asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(S0), "+v"(S1));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        double part[2], ad[NAS];
+        if (!collect(t, tag, v, part, ad)) return;
+        double st = 0.0;
+        const double g1 = cj - part[0], g2 = -part[1];
+        ccd_apply(g1, g2, a.penalty, a.lambda, &bj, &dj, &st);
+        if (tid == 0) {
+            s_step[j - jb] = st;
+            if (b == 0) {
+                a.beta[r * a.p + j] = bj;
+                a.delta[r * a.p + j] = dj;
+                if (a.g12_out) {
+                    double *o = a.g12_out + (r * a.p + j) * 3;
+                    o[0] = g1;
+                    o[1] = g2;
+                    o[2] = st;
+                }
+            }
+        }
+        f_prev = expm1(st);
+        prefix_from(ad, f_prev, pre);
+        st_prev = st;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            xp[g] = xc[g];
+            xc[g] = xn[g];
+            xn[g] = x2[g];
+        }
+    }
+    __syncthreads();
+    // ---- eta from the launch's steps, in the order they were taken, and
+    // e = exp(eta) at training positions
+    for (int g = 0; g < NG; ++g) {
+        const int64_t k = base + 16 * g;
+        if (k >= a.stride) break;
+        double h[16];
+        double2 *hp = reinterpret_cast<double2 *>(a.eta + off + k);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const double2 x = hp[q];
+            h[2 * q] = x.x;
+            h[2 * q + 1] = x.y;
+        }
+        const uint8_t *col = a.xbits + (int64_t)jb * (a.stride / 8) + k / 8;
+        for (int q0 = 0; q0 < je - jb; q0 += kCvGather) {
+            uint32_t bits[kCvGather];
+#pragma unroll
+            for (int u = 0; u < kCvGather; ++u)
+                bits[u] = q0 + u < je - jb
+                              ? *reinterpret_cast<const uint16_t *>(col + (q0 + u) * (a.stride / 8))
+                              : 0u;
+#pragma unroll
+            for (int u = 0; u < kCvGather; ++u) {
+                if (bits[u] != 0u) {
+                    const double st = s_step[q0 + u];
+#pragma unroll
+                    for (int q = 0; q < 16; ++q)
+                        if ((bits[u] >> q) & 1u) h[q] += st;
+                }
+            }
+        }
+        const uint4 tq = *reinterpret_cast<const uint4 *>(a.train_s + off + k);
+        const uint32_t tr[4] = {tq.x, tq.y, tq.z, tq.w};
+        double2 *ep = reinterpret_cast<double2 *>(a.e + off + k);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const double x = h[2 * q], y = h[2 * q + 1];
+            hp[q] = make_double2(x, y);
+            const uint32_t m = tr[q / 2] >> (16 * (q % 2));
+            ep[q] = make_double2((m & 255u) ? exp(x) : 0.0, (m & 0xff00u) ? exp(y) : 0.0);
+        }
+    }
+    // every workgroup of the replicate read the epoch before its last
+    // publication, which this one has gathered
+    if (b == 0 && tid == 0) st_relaxed_u64(cv_epoch(a, r), ep0 + (uint64_t)(je - jb) + 1);
+}
+
 // Fine-Gray training and held-out log pseudo-likelihoods (eq. fg_l on each
 // subset): a first pass sums the weighted totals of both subsets, the
 // second scans e and e w of each subset and takes d log S0 at the run ends
@@ -1438,6 +1909,54 @@ int32_t launch_cv_exp(int64_t n, int32_t reps, const double *eta, const uint8_t 
 
 size_t cv_ws_bytes(int32_t reps) { return 256 + (size_t)reps * kCvXchBytes; }
 
+namespace {
+
+// The on-chip sweep for these sizes: the shortest segments with which all
+// replicates' workgroups are resident at once (short serial parts; more
+// segments per replicate cost nothing but slots), if any.
+struct OnChip {
+    void *kernel;
+    int64_t parts;
+    int64_t steps;  // coordinates per launch
+};
+
+int32_t on_chip_for(int32_t model, int64_t n, int32_t reps, OnChip *out)
+{
+    struct Cand {
+        int ipt;
+        void *k;
+    };
+    const bool fg = model == SS_FINE_GRAY;
+    static const Cand cox[] = {
+        {16, reinterpret_cast<void *>(&k_cv_on_chip<16, SS_COX>)},
+        {32, reinterpret_cast<void *>(&k_cv_on_chip<32, SS_COX>)},
+        {48, reinterpret_cast<void *>(&k_cv_on_chip<48, SS_COX>)},
+        {64, reinterpret_cast<void *>(&k_cv_on_chip<64, SS_COX>)},
+        {80, reinterpret_cast<void *>(&k_cv_on_chip<80, SS_COX>)}};
+    static const Cand fgs[] = {
+        {16, reinterpret_cast<void *>(&k_cv_on_chip<16, SS_FINE_GRAY>)},
+        {32, reinterpret_cast<void *>(&k_cv_on_chip<32, SS_FINE_GRAY>)}};
+    out->kernel = nullptr;
+    int dev = 0, cus = 0, coop = 0;
+    SS_HIP_CHECK(hipGetDevice(&dev));
+    SS_HIP_CHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    SS_HIP_CHECK(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev));
+    if (!coop) return SS_OK;
+    const Cand *c = fg ? fgs : cox;
+    for (int i = 0; i < (fg ? 2 : 5); ++i) {
+        const int64_t parts = ceil_div(n, (int64_t)kCvOnBlock * c[i].ipt);
+        if (parts > kCvParts) continue;
+        int per_cu = 0;
+        SS_HIP_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, c[i].k, kCvOnBlock, 0));
+        if (parts * reps > (int64_t)per_cu * cus) continue;
+        *out = OnChip{c[i].k, parts, fg ? cv_on_steps<SS_FINE_GRAY>() : cv_on_steps<SS_COX>()};
+        return SS_OK;
+    }
+    return SS_OK;
+}
+
+}  // namespace
+
 int32_t launch_cv_sweep(int32_t model, int32_t penalty, double lambda, int64_t n, int64_t p,
                         int32_t reps, int64_t j_begin, int64_t j_end, double *eta, double *e,
                         const uint8_t *d8_r, const int32_t *d32_r, const uint8_t *train_s,
@@ -1471,7 +1990,29 @@ int32_t launch_cv_sweep(int32_t model, int32_t penalty, double lambda, int64_t n
     // SURVSCAN_CV_HALVES=1 forces one.
     const char *env = getenv("SURVSCAN_CV_HALVES");
     const bool allow2 = !(env && env[0] == '1');
-    (void)w_r;  // the sweep derives w from G (the same division)
+    // where everything fits on the chip at once, it stays there
+    if (!env) {
+        OnChip on;
+        const int32_t rc = on_chip_for(model, n, reps, &on);
+        if (rc) return rc;
+        if (on.kernel) {
+            CvOnArgs o;
+            o.a = a;
+            o.w = w_r;
+            o.g = g_r;
+            o.parts = (int32_t)on.parts;
+            for (int64_t j = j_begin; j < j_end; j += on.steps) {
+                o.a.j_begin = j;
+                o.a.j_end = j + on.steps < j_end ? j + on.steps : j_end;
+                void *args[] = {&o};
+                SS_HIP_CHECK(hipLaunchCooperativeKernel(on.kernel,
+                                                        dim3((unsigned)(on.parts * reps)),
+                                                        dim3(kCvOnBlock), args, 0, s));
+            }
+            return SS_OK;
+        }
+    }
+    // (the streaming Fine-Gray sweep derives w from G, by the same division)
     if (model == SS_FINE_GRAY) {
         CvFgArgs f;
         f.a = a;

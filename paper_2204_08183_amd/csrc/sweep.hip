@@ -24,7 +24,7 @@
 // exchange.
 // Every wait is bounded; a timed-out wait sets the workspace error word and
 // every workgroup leaves at its next wait.
-#include "ss_device.h"
+#include "exchange.h"
 
 namespace ss {
 
@@ -447,13 +447,8 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(SweepArgs a)
 }
 
 // ------------------------------------------------------------------------
-// All-to-all exchange of the kernels below.  Every workgroup publishes N
-// values per round as tagged 16-byte words and reads every segment's.
-// (Gathering in workgroup 0 and broadcasting back takes two round trips
-// through the coherence point instead of one.)  A slot is in one of two
-// areas of the publication buffer (ss_internal.h), by round parity: a
-// workgroup can be at most one round ahead of the slowest reader, as it
-// needs everyone's late publication of a round to go on.
+// The exchange of the kernels below (exchange.h): a slot is in one of two
+// areas of the publication buffer (ss_internal.h), by round parity.
 template <bool LATE>
 __device__ __forceinline__ u32x4 *pub_area(const WsView &ws, uint64_t round, int copy)
 {
@@ -468,102 +463,28 @@ __host__ __device__ constexpr int pub_stride()
     return LATE ? kPubLateWords : pub_words<N>() <= 4 ? 4 : kPubEarlyWords;
 }
 
-// One wave publishes t (the same in every lane) as segment q of the round:
-// lane l stores word l mod NQ of copy l / NQ.
+// Publishes t as segment q of the round, in every copy.
 template <bool LATE, int N>
 __device__ __forceinline__ void publish(const WsView &ws, const double (&t)[N], uint64_t round,
                                         int64_t q, uint64_t tag)
 {
-    constexpr int NQ = pub_words<N>();
-    static_assert(NQ <= pub_stride<LATE, N>() && NQ * kPubCopies <= kWave,
-                  "one wave stores every copy of a publication");
     static_assert(kPubLateWords + kPubEarlyWords <= kPubSlotWords, "both slots fit");
-    const int lane = lane_id();
-    u32x4 wd[NQ];
-    pub_pack<N>(t, (uint32_t)tag, wd);
-    const int word = lane % NQ;
-    // (an empty asm statement per word: a select chain over the array
-    // itself is folded into an indexed load from scratch)
-    u32x4 x = wd[0];
-#pragma unroll
-    for (int c = 1; c < NQ; ++c) {
-        u32x4 y = wd[c];
-        asm volatile("" : "+v"(y));
-        x = word == c ? y : x;
-    }
-    if (lane < NQ * kPubCopies)
-        st_quad(pub_area<LATE>(ws, round, lane / NQ) + q * pub_stride<LATE, N>() + word, x);
+    constexpr int64_t copy_words = 2 * (int64_t)kPubSlotWords * kMaxSweepBlocks;
+    publish_slots<N, kPubCopies>(pub_area<LATE>(ws, round, 0) + q * pub_stride<LATE, N>(),
+                                 copy_words, t, tag);
 }
 
-// Thread t of `span` reads the publications of segments t + k span (k < K;
-// the last segment again past the end) until all carry the tag.  Returns
-// false if the wait gave up or another workgroup's did.
-template <bool LATE, int N, int K>
-__device__ __forceinline__ bool gather(const WsView &ws, uint64_t round, int copy, int t, int span,
-                                       int G, uint64_t tag, double (&v)[K][N])
-{
-    constexpr int NQ = pub_words<N>();
-    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        pub_area<LATE>(ws, round, copy), 0, kMaxSweepBlocks * kPubSlotWords * 16, 0x00020000);
-    int off[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) off[k] = min(t + k * span, G - 1) * (pub_stride<LATE, N>() * 16);
-    uint32_t spins = 0;
-    for (;;) {
-        // agent-scope loads (sc1), read again on every pass
-        u32x4 r[K][NQ];
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-#pragma unroll
-            for (int c = 0; c < NQ; ++c)
-                r[k][c] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off[k] + 16 * c, 0, 16);
-        asm volatile("" ::: "memory");
-        bool ok = true;
-#pragma unroll
-        for (int k = 0; k < K; ++k) ok = ok && pub_tagged<NQ>(r[k], (uint32_t)tag);
-        if (ok) {
-#pragma unroll
-            for (int k = 0; k < K; ++k) pub_unpack<N>(r[k], v[k]);
-            return true;
-        }
-        if (((++spins & 31u) == 0 && ld_relaxed_u32(&ws.hdr->error)) || spins > kSpinLimit) {
-            __hip_atomic_store(&ws.hdr->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            return false;
-        }
-        __builtin_amdgcn_s_sleep(1);
-    }
-}
-
-// Sums over the segments in a fixed order, one wave's share into dst: of
-// every value (MODE[c] = 0), of those before segment b (1) or after it (2).
-constexpr int kAll = 0, kBefore = 1, kAfter = 2;
-
+// The sums of gather_sums over a round's publications, from one copy.
 template <bool LATE, int N, int NS, int K>
-__device__ __forceinline__ bool gather_sums(const WsView &ws, uint64_t round, int copy, int t,
-                                            int span, int G, int64_t b, uint64_t tag,
-                                            const int (&from)[NS], const int (&mode)[NS],
-                                            double *dst)
+__device__ __forceinline__ bool gather_round(const WsView &ws, uint64_t round, int copy, int t,
+                                             int span, int G, int64_t b, uint64_t tag,
+                                             const int (&from)[NS], const int (&mode)[NS],
+                                             double *dst)
 {
-    double s[NS];
-#pragma unroll
-    for (int c = 0; c < NS; ++c) s[c] = 0.0;
-    bool ok = true;
-    for (int t0 = t; ok && t0 - t < G; t0 += K * span) {  // K segments a thread at a time
-        double v[K][N];
-        ok = gather<LATE, N, K>(ws, round, copy, t0, span, G, tag, v);
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const int64_t q = t0 + k * span;
-#pragma unroll
-            for (int c = 0; c < NS; ++c) {
-                const bool in = ok && q < G &&
-                                (mode[c] == kAll || (mode[c] == kBefore ? q < b : q > b));
-                s[c] += in ? v[k][from[c]] : 0.0;
-            }
-        }
-    }
-    wave_sums_to<NS>(s, dst);
-    return ok;
+    constexpr int words = kMaxSweepBlocks * (LATE ? kPubLateWords : kPubEarlyWords);
+    return gather_sums<N, pub_stride<LATE, N>(), NS, K>(pub_area<LATE>(ws, round, copy), words,
+                                                        ws.hdr, t, span, G, b, tag, from, mode,
+                                                        dst);
 }
 
 // ------------------------------------------------------------------------
@@ -780,11 +701,11 @@ __global__ __launch_bounds__(BLOCK) void k_sweep1(SweepArgs a)
                     mode[c] = kAll;
                 }
                 double *dst = s_sum[par][w];
-                ok = kk == 1   ? gather_sums<true, P0, P0, 1>(a.ws, r, my_copy, tid, HALF, G, b,
+                ok = kk == 1   ? gather_round<true, P0, P0, 1>(a.ws, r, my_copy, tid, HALF, G, b,
                                                               tag, from, mode, dst)
-                     : kk == 2 ? gather_sums<true, P0, P0, 2>(a.ws, r, my_copy, tid, HALF, G, b,
+                     : kk == 2 ? gather_round<true, P0, P0, 2>(a.ws, r, my_copy, tid, HALF, G, b,
                                                               tag, from, mode, dst)
-                               : gather_sums<true, P0, P0, K>(a.ws, r, my_copy, tid, HALF, G, b,
+                               : gather_round<true, P0, P0, K>(a.ws, r, my_copy, tid, HALF, G, b,
                                                               tag, from, mode, dst);
             } else {
                 int from[NAS], mode[NAS];
@@ -803,9 +724,9 @@ __global__ __launch_bounds__(BLOCK) void k_sweep1(SweepArgs a)
                 }
                 double *dst = s_sum[par][w];
                 const int t = tid - HALF;
-                ok = kk == 1 ? gather_sums<false, NAD, NAS, 1>(a.ws, r, my_copy, t, HALF, G, b,
+                ok = kk == 1 ? gather_round<false, NAD, NAS, 1>(a.ws, r, my_copy, t, HALF, G, b,
                                                                tag, from, mode, dst)
-                             : gather_sums<false, NAD, NAS, 2>(a.ws, r, my_copy, t, HALF, G, b,
+                             : gather_round<false, NAD, NAS, 2>(a.ws, r, my_copy, t, HALF, G, b,
                                                                tag, from, mode, dst);
             }
             if (__syncthreads_or(!ok)) return false;
@@ -1257,9 +1178,9 @@ __global__ __launch_bounds__(BLOCK) void k_sweep_valued(SweepArgs a)
                 mode[c] = c < 3 ? kBefore : kAfter;
             }
             const bool ok =
-                G <= BLOCK ? gather_sums<false, NC, NC, 1>(a.ws, r, my_copy, tid, BLOCK, G, b, tag,
+                G <= BLOCK ? gather_round<false, NC, NC, 1>(a.ws, r, my_copy, tid, BLOCK, G, b, tag,
                                                            from, mode, s_sum[0][w])
-                           : gather_sums<false, NC, NC, 2>(a.ws, r, my_copy, tid, BLOCK, G, b, tag,
+                           : gather_round<false, NC, NC, 2>(a.ws, r, my_copy, tid, BLOCK, G, b, tag,
                                                            from, mode, s_sum[0][w]);
             if (__syncthreads_or(!ok)) return;
 #pragma unroll
@@ -1342,9 +1263,9 @@ __global__ __launch_bounds__(BLOCK) void k_sweep_valued(SweepArgs a)
         if constexpr (!SOLO) {
             const int from[3] = {0, 1, 2}, mode[3] = {kAll, kAll, kAll};
             const bool ok =
-                G <= BLOCK ? gather_sums<true, 3, 3, 1>(a.ws, r, my_copy, tid, BLOCK, G, b, tag,
+                G <= BLOCK ? gather_round<true, 3, 3, 1>(a.ws, r, my_copy, tid, BLOCK, G, b, tag,
                                                         from, mode, s_sum[1][w])
-                           : gather_sums<true, 3, 3, 2>(a.ws, r, my_copy, tid, BLOCK, G, b, tag,
+                           : gather_round<true, 3, 3, 2>(a.ws, r, my_copy, tid, BLOCK, G, b, tag,
                                                         from, mode, s_sum[1][w]);
             if (__syncthreads_or(!ok)) return;
 #pragma unroll

@@ -415,9 +415,10 @@ int32_t ss_beta_gradient(int32_t model, int64_t n, int64_t p,
  * g'' of the replicate's training data, and the a3 update of Sec. 2.4 on
  * beta[r][j], delta[r][j]; g12_out[r][j] = (g', g'', applied step) if not
  * NULL.  At the end eta holds X beta and e = exp(eta) (masked) afresh.
- * One workgroup per replicate, or two (each half of the positions, one
- * exchange per coordinate, cooperative launch) when all of them fit on
- * the device at once; Fine-Gray carries the weighted totals sum e w and
+ * Several workgroups per replicate that keep e on the chip (one exchange
+ * per coordinate, cooperative launches of up to 1024 coordinates) when all
+ * of them fit on the device at once; otherwise one workgroup per replicate,
+ * or two when these fit, reading e for every coordinate; Fine-Gray carries the weighted totals sum e w and
  * sum e w x_j over the replicate from one coordinate to the next in closed
  * form (a pass before the first coordinate sums them); fixed summation
  * order either way (deterministic for a given device).  ws: ss_cv_workspace_bytes(R) bytes, 256-byte aligned,

@@ -10,7 +10,9 @@
 // training events only.  eta is kept for every subject (X beta), so the
 // held-out log-likelihood can be evaluated at the fitted beta.
 //
-// One workgroup of 1024 threads runs one replicate's coordinates in order:
+// Where every replicate's e fits the chip at once it stays there
+// (k_cv_on_chip).  Otherwise one workgroup of 1024 threads (or two) runs one
+// replicate's coordinates in order:
 // the scan of coordinate j goes over the replicate in chunks of 1024 x IPT
 // positions (each thread owns the same IPT consecutive positions of every
 // chunk for the whole launch), the thread sums are combined by one wave scan
@@ -513,10 +515,7 @@ __device__ void cv_apply_steps(const CvArgs &a, double *eta, double *e, const ui
 // A1 + expm1(s) D1 (e at column j + 1; D1 = e at both columns), all
 // summed during the pass of coordinate j before s is known.  Both halves
 // then take the same Newton step from the same numbers.
-#ifndef SS_CV_GROUP
-#define SS_CV_GROUP 4
-#endif
-constexpr int kCvGroup = SS_CV_GROUP;
+constexpr int kCvGroup = 4;  // run ends evaluated together (2 and 8 measured the same)
 
 template <int BLOCK, int IPT, int KH>
 __global__ __launch_bounds__(BLOCK) void k_cv_sweep(CvArgs a)
@@ -716,7 +715,9 @@ __global__ __launch_bounds__(BLOCK) void k_cv_sweep(CvArgs a)
 #pragma unroll
                 for (int u = 0; u < kCvGroup; ++u) {
                     const uint32_t d = dv[i0 + u];
-                    const double g = d != 0u ? s1[u] * recip(s0[u]) : 0.0;
+                    double g = s1[u] * recip(s0[u]);
+                    asm("" : "+v"(g));  // a select, not a branch around it
+                    g = d != 0u ? g : 0.0;
                     const double dd = (double)d;
                     acc1 = fma(dd, g, acc1);
                     acc2 = fma(dd, fma(-g, g, g), acc2);
@@ -1193,7 +1194,10 @@ __global__ __launch_bounds__(BLOCK) void k_cv_sweep_fg(CvFgArgs f)
 // counts of every replicate through a workgroup or two chunk by chunk for
 // every coordinate, nothing is loaded per coordinate but the column's bits,
 // there is one scan and one barrier for a thread's IPT positions instead of
-// one per 8, and all CUs work (K follows the number of replicates).
+// one per 8, and all CUs work (K follows the number of replicates).  ms per
+// 1000 coordinates, streaming / on chip, at N = 1e5: 100 replicates Cox 34.7 /
+// 18.6, 50 33.9 / 11.7, 10 31.3 / 5.0; 35 Fine-Gray replicates 58 / 16.5, 10
+// 54.2 / 6.0; 100 replicates at N = 5000 Cox 8.2 / 4.5, Fine-Gray 8.2 / 5.5.
 //
 // Bound: VALU issue (about 40 instructions per position and coordinate).
 // Event counts sit in LDS four to a word, G (Fine-Gray) in LDS; eta is
@@ -1301,7 +1305,6 @@ __global__ __launch_bounds__(kCvOnBlock, 2) void k_cv_on_chip(CvOnArgs f)
     }
     const bool any_big = __any(big);
     const int32_t *d32 = a.d32 + off + base;
-    auto count = [&](int i) -> uint32_t { return (s_d[i / 4][tid] >> (8 * (i % 4))) & 255u; };
     auto column = [&](int32_t j, uint32_t (&x)[NG]) {
         const uint8_t *col = a.xbits + (int64_t)j * (a.stride / 8);
 #pragma unroll
@@ -1534,6 +1537,8 @@ __global__ __launch_bounds__(kCvOnBlock, 2) void k_cv_on_chip(CvOnArgs f)
                 R0 = pre[2] - texcl[2];
                 R1 = pre[3] - texcl[3];
             }
+            uint32_t dw = s_d[0][tid];  // the counts of a group, read one ahead
+            static_assert(GT == 4, "a word of counts per group");
 #pragma unroll
             for (int i0 = 0; i0 < IPT; i0 += GT) {
                 double t0[GT], t1[GT];
@@ -1555,8 +1560,9 @@ __global__ __launch_bounds__(kCvOnBlock, 2) void k_cv_on_chip(CvOnArgs f)
                         t0[u] = fma(g, R0, t0[u]);
                         t1[u] = fma(g, R1, t1[u]);
                     }
-                    d[u] = count(i);
+                    d[u] = (dw >> (8 * u)) & 255u;
                 }
+                if (i0 + GT < IPT) dw = s_d[(i0 + GT) / 4][tid];
                 if (any_big) {
 #pragma unroll
                     for (int u = 0; u < GT; ++u)
@@ -1564,7 +1570,9 @@ __global__ __launch_bounds__(kCvOnBlock, 2) void k_cv_on_chip(CvOnArgs f)
                 }
 #pragma unroll
                 for (int u = 0; u < GT; ++u) {
-                    const double g = d[u] != 0u ? t1[u] * recip(t0[u]) : 0.0;
+                    double g = t1[u] * recip(t0[u]);
+                    asm("" : "+v"(g));  // a select, not a branch around it
+                    g = d[u] != 0u ? g : 0.0;
                     const double dd = (double)d[u];
                     v[0] = fma(dd, g, v[0]);
                     v[1] = fma(dd, fma(-g, g, g), v[1]);

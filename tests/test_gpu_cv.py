@@ -435,3 +435,50 @@ def test_cv_fg_path_matches_oracle():
                      for r in range(train.shape[0])], axis=1)
     np.testing.assert_allclose(scores, want, rtol=1e-9, atol=1e-9)
     assert best == gammas[int(want.mean(axis=1).argmax())]
+
+
+# Where every workgroup of a launch fits the device the sweep stays on chip:
+# segments of 4096 positions per workgroup, longer ones (8192, 12288, 16384,
+# 20480; Fine-Gray 8192 at most) as the replicates' segments outnumber the
+# device's workgroup slots (two to a CU, three at 4096 for Cox), at most 32 per
+# replicate; above that the streaming kernels.
+ON_CHIP_CASES = [
+    # model, n, replicates
+    ("cox", 4096, 3), ("cox", 4097, 3), ("cox", 131_073, 1), ("cox", 24_576, 130),
+    ("cox", 24_577, 130), ("cox", 32_768, 200), ("cox", 32_769, 200), ("cox", 41_000, 200),
+    ("fg", 4096, 2), ("fg", 4097, 2), ("fg", 24_576, 80), ("fg", 24_577, 80), ("fg", 131_073, 1),
+    ("fg", 24_577, 140),
+]
+
+
+@pytest.mark.parametrize("model,n,reps", ON_CHIP_CASES)
+def test_cv_on_chip_shapes(model, n, reps, monkeypatch):
+    monkeypatch.delenv("SURVSCAN_CV_HALVES", raising=False)
+    d = cox_case(n, 4, 20) if model == "cox" else fg_case(n, 4, 20)
+    # tie runs, one of them with more than 255 events
+    d["y"] = np.where(d["y"] < np.quantile(d["y"], 700 / n), 0.0, np.ceil(d["y"] * n))
+    rng = np.random.default_rng(21)
+    train = (rng.random((reps, n)) < 0.8).astype(np.uint8)
+    train[0, np.argsort(-d["y"])[:50]] = 0  # no training subject at first
+    check_sweeps(d, train, "l1", 0.7, 2, 1e-9, reps_to_check=sorted({0, reps // 2, reps - 1}),
+                 model=model)
+
+
+@pytest.mark.parametrize("model,p", [("cox", 1030), ("fg", 520)])
+def test_cv_on_chip_many_coordinates(model, p):
+    """More coordinates than a launch keeps the steps of (1024; Fine-Gray
+    512): the launches follow one another."""
+    d = cox_case(1500, p, 22, density=0.05) if model == "cox" else \
+        fg_case(1500, p, 22, density=0.05)
+    train = gen.cv_folds(23, d["n"], 5, 1)[:2]
+    check_sweeps(d, train, "l2", 1.0, 2, 1e-9, model=model)
+
+
+@pytest.mark.parametrize("model", ["cox", "fg"])
+@pytest.mark.parametrize("n,ties", [(8193, 0), (50_001, 40), (16_385, 5)])
+def test_cv_streaming_halves(model, n, ties, monkeypatch):
+    """The streaming sweep with two workgroups per replicate, at sizes that
+    by themselves would stay on chip."""
+    monkeypatch.setenv("SURVSCAN_CV_HALVES", "2")
+    d = cox_case(n, 4, 24, ties=ties) if model == "cox" else fg_case(n, 4, 24, ties=ties)
+    check_sweeps(d, gen.cv_folds(25, n, 3, 1), "l1", 0.5, 1, 1e-10, model=model)

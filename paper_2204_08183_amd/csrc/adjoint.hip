@@ -181,8 +181,8 @@ __global__ __launch_bounds__(SB) void k_adj_sums(int64_t n, const double *e, con
     __shared__ double s_red[SB / kWave];
     const int64_t k0 = (int64_t)blockIdx.x * ST + (int64_t)threadIdx.x * SI;
     double ev[SI], wv[FG ? SI : 1];
-    load_items<double, OpAdd<double>, false>(e, k0, n, ev);
-    if constexpr (FG) load_items<double, OpAdd<double>, false>(w_comp, k0, n, wv);
+    load_items<double, OpAdd<double>>(e, k0, n, ev);
+    if constexpr (FG) load_items<double, OpAdd<double>>(w_comp, k0, n, wv);
     double a = 0.0, b = 0.0;
 #pragma unroll
     for (int i = 0; i < SI; ++i) {
@@ -215,14 +215,14 @@ __global__ __launch_bounds__(SB) void k_adj_terms(int64_t n, int64_t tiles, cons
     __shared__ double s_red[SB / kWave];
     const int64_t k0 = (int64_t)blockIdx.x * ST + (int64_t)threadIdx.x * SI;
     double s0[SI], et[SI], r[FG ? SI : 1], gv[FG ? SI : 1];
-    load_items<double, OpAdd<double>, false>(e, k0, n, s0);
-    load_items<double, OpAdd<double>, false>(eta, k0, n, et);
+    load_items<double, OpAdd<double>>(e, k0, n, s0);
+    load_items<double, OpAdd<double>>(eta, k0, n, et);
     uint8_t dd[SI], st[SI];
     load_bytes8(d8, k0, n, dd);
     load_bytes8(reinterpret_cast<const uint8_t *>(status_s), k0, n, st);
     if constexpr (FG) {
-        load_items<double, OpAdd<double>, false>(w_comp, k0, n, r);
-        load_items<double, OpAdd<double>, false>(g_end, k0, n, gv);
+        load_items<double, OpAdd<double>>(w_comp, k0, n, r);
+        load_items<double, OpAdd<double>>(g_end, k0, n, gv);
         const double after = tile_carry<true>(sum_ew, tiles, s_red);
 #pragma unroll
         for (int i = 0; i < SI; ++i) r[i] *= s0[i];
@@ -262,7 +262,7 @@ __global__ __launch_bounds__(SB) void k_adj_terms(int64_t n, int64_t tiles, cons
             lsum += l;
         }
     }
-    store_items<double, false>(q, k0, n, qv);
+    store_items<double>(q, k0, n, qv);
     __syncthreads();
     const double tl = block_total(lsum, s_red);
     if (threadIdx.x == 0) lpart[blockIdx.x] = tl;
@@ -292,13 +292,13 @@ __global__ __launch_bounds__(SB) void k_adj_grad(int64_t n, int64_t tiles, const
     __shared__ double s_last[SB / kWave];
     const int64_t k0 = (int64_t)blockIdx.x * ST + (int64_t)threadIdx.x * SI;
     double r[SI], ev[SI], qg[FG ? SI : 1], wv[FG ? SI : 1];
-    load_items<double, OpAdd<double>, false>(q, k0, n, r);
-    load_items<double, OpAdd<double>, false>(e, k0, n, ev);
+    load_items<double, OpAdd<double>>(q, k0, n, r);
+    load_items<double, OpAdd<double>>(e, k0, n, ev);
     uint8_t st[SI];
     load_bytes8(reinterpret_cast<const uint8_t *>(status_s), k0, n, st);
     if constexpr (FG) {
-        load_items<double, OpAdd<double>, false>(g_end, k0, n, qg);
-        load_items<double, OpAdd<double>, false>(w_comp, k0, n, wv);
+        load_items<double, OpAdd<double>>(g_end, k0, n, qg);
+        load_items<double, OpAdd<double>>(w_comp, k0, n, wv);
 #pragma unroll
         for (int i = 0; i < SI; ++i) qg[i] *= r[i];
         const double before = tile_carry<false>(sum_qg, tiles, s_red);
@@ -313,7 +313,7 @@ __global__ __launch_bounds__(SB) void k_adj_grad(int64_t n, int64_t tiles, const
         if constexpr (FG) inner += wv[i] * qg[i];
         gv[i] = (is_event(FG ? SS_FINE_GRAY : SS_COX, (int8_t)st[i]) ? 1.0 : 0.0) - ev[i] * inner;
     }
-    store_items<double, false>(grad_s, k0, n, gv);
+    store_items<double>(grad_s, k0, n, gv);
     if (blockIdx.x == 0) {
         double v = 0.0;
         for (int64_t b = threadIdx.x; b < tiles; b += SB) v += lpart[b];

@@ -10,6 +10,7 @@
 //    per-column chunk index and c_j = sum over events of x_ij.
 // Every integer output is produced with exact integer arithmetic, so it is
 // identical from run to run.
+#include <utility>
 #include <vector>
 
 #include "scan_device.h"
@@ -22,14 +23,13 @@ namespace {
 // ------------------------------------------------------------ generic scan
 // (block-level pieces in scan_device.h)
 
-template <typename T, typename Op, bool REV>
-__global__ __launch_bounds__(SB) void k_scan_reduce(const T *in, int64_t m, T *sums)
+__global__ __launch_bounds__(SB) void k_scan_reduce(const uint32_t *in, int64_t m, uint32_t *sums)
 {
-    __shared__ T s_w[SB / kWave];
-    T it[SI];
-    const int64_t base = (int64_t)blockIdx.x * ST + (int64_t)threadIdx.x * SI;
-    load_items<T, Op, REV>(in, base, m, it);
-    T tot = block_scan<T, Op>(it, Op::id(), s_w);
+    __shared__ uint32_t s_w[SB / kWave];
+    uint32_t it[SI];
+    load_items<uint32_t, OpAdd<uint32_t>>(in, (int64_t)blockIdx.x * ST + (int64_t)threadIdx.x * SI,
+                                          m, it);
+    const uint32_t tot = block_scan<uint32_t, OpAdd<uint32_t>>(it, 0, s_w);
     if (threadIdx.x == 0) sums[blockIdx.x] = tot;
 }
 
@@ -54,70 +54,172 @@ __global__ __launch_bounds__(SB) void k_scan_spine(T *sums, int64_t nb)
     }
 }
 
-template <typename T, typename Op, bool REV, bool EXCL>
-__global__ __launch_bounds__(SB) void k_scan_down(const T *in, T *out, int64_t m,
-                                                  const T *sums)
+// Carry of a tile (REV: `sums` are those of the tiles from the last on).  Up
+// to ST tiles every workgroup combines the totals of the tiles before its own
+// itself, in order; above, k_scan_spine has.  (A launch of one workgroup and
+// the gap before it: 3.7 us; the totals of 500 tiles: below 1 us.)
+template <typename T, typename Op, bool REV>
+__device__ __forceinline__ T tile_carry(const T *sums, int64_t tiles, T *s_w)
 {
-    __shared__ T s_w[SB / kWave];
-    __shared__ T s_last[SB / kWave];
+    const int64_t cnt = REV ? tiles - 1 - (int64_t)blockIdx.x : (int64_t)blockIdx.x;
+    if (tiles > ST) return sums[cnt];
     T it[SI];
+    load_items<T, Op>(sums, (int64_t)threadIdx.x * SI, cnt, it);
+    return block_scan<T, Op>(it, Op::id(), s_w);
+}
+
+__global__ __launch_bounds__(SB) void k_scan_down(const uint32_t *in, uint32_t *out, int64_t m,
+                                                  int64_t tiles, const uint32_t *sums)
+{
+    using Op = OpAdd<uint32_t>;
+    __shared__ uint32_t s_w[SB / kWave];
+    __shared__ uint32_t s_last[SB / kWave];
+    uint32_t it[SI];
     const int64_t base = (int64_t)blockIdx.x * ST + (int64_t)threadIdx.x * SI;
-    load_items<T, Op, REV>(in, base, m, it);
-    const T carry = sums[blockIdx.x];
-    block_scan<T, Op>(it, carry, s_w);
-    if (EXCL) inclusive_to_exclusive<T>(it, carry, s_last);
-    __syncthreads();  // `in` and `out` may alias: every read is done
-    store_items<T, REV>(out, base, m, it);
+    load_items<uint32_t, Op>(in, base, m, it);
+    const uint32_t carry = tile_carry<uint32_t, Op, false>(sums, tiles, s_w);
+    block_scan<uint32_t, Op>(it, carry, s_w);
+    inclusive_to_exclusive<uint32_t>(it, carry, s_last);
+    store_items<uint32_t>(out, base, m, it);  // `in` and `out` may alias: a thread's own items
 }
 
 // ------------------------------------------------------------ radix sort
+// One pass orders (key, value) records by 8 bits of the key, stably.  A tile
+// is RB * RI records, wave w of a workgroup its w-th quarter in rounds of 64,
+// so a record's rank among equal digits of the tile is its rank in the
+// wave's rounds before (a counter per wave and digit in LDS, no barrier),
+// in its round (wave ballots) and the counts of the waves before; the records
+// are put in order in LDS and leave as runs.  All of a thread's loads are in
+// flight at once.  Bound: at 1e6 records 245 workgroups, one per CU, and in
+// each the serial rounds.  (Rounds over the whole workgroup with three
+// barriers each, 8-byte values and records stored one by one: 22.5 us a pass
+// at 1e6 records, now 14.6; hist 6.3, now 4.5.)
 constexpr int RB = 256;
 constexpr int RI = 16;
 constexpr int RT = RB * RI;
+// Up to kOwnOffsets tiles a scatter adds the tiles' counts up itself, one row
+// of 256 a tile (a tile alone needs none); above, a scan over the counts by
+// digit has.  (1e6 records: two launches of 6 us and their gaps a pass against
+// 4.7 us more in the scatter, a preparation 609 -> 591 us; the rows read grow
+// with the square of the tiles.)
+constexpr int64_t kOwnOffsets = 256;
 
+template <bool ROWS>
 __global__ __launch_bounds__(RB) void k_radix_hist(const uint64_t *keys, int64_t m,
                                                    int shift, uint32_t *hist,
                                                    int64_t nb)
 {
-    __shared__ uint32_t cnt[256];
-    cnt[threadIdx.x] = 0;
-    __syncthreads();
+    __shared__ uint32_t cnt[RB / kWave][256];
+    const int w = threadIdx.x / kWave;
+#pragma unroll
+    for (int q = 0; q < RB / kWave; ++q) cnt[q][threadIdx.x] = 0;
     const int64_t base = (int64_t)blockIdx.x * RT;
+    uint64_t key[RI];
+#pragma unroll
     for (int r = 0; r < RI; ++r) {
         const int64_t idx = base + (int64_t)r * RB + threadIdx.x;
-        if (idx < m) atomicAdd(&cnt[(keys[idx] >> shift) & 255u], 1u);
+        key[r] = keys[idx < m ? idx : m - 1];
     }
     __syncthreads();
-    hist[(int64_t)threadIdx.x * nb + blockIdx.x] = cnt[threadIdx.x];
+#pragma unroll
+    for (int r = 0; r < RI; ++r)
+        if (base + (int64_t)r * RB + threadIdx.x < m)
+            atomicAdd(&cnt[w][(key[r] >> shift) & 255u], 1u);
+    __syncthreads();
+    uint32_t t = 0;
+#pragma unroll
+    for (int q = 0; q < RB / kWave; ++q) t += cnt[q][threadIdx.x];
+    hist[ROWS ? (int64_t)blockIdx.x * 256 + threadIdx.x
+              : (int64_t)threadIdx.x * nb + blockIdx.x] = t;
 }
 
-// Stable scatter: items are visited in rounds of RB consecutive keys; inside
-// a round a key's rank among equal digits comes from wave ballots (lanes in
-// order) plus the counts of the earlier waves.
-template <bool HAS_VAL>
-__global__ __launch_bounds__(RB) void k_radix_scatter(const uint64_t *kin,
-                                                      const uint64_t *vin, int64_t m,
-                                                      int shift, const uint32_t *offs,
-                                                      int64_t nb, uint64_t *kout,
-                                                      uint64_t *vout, uint32_t *err)
+// Exclusive prefix over a workgroup's threads.
+__device__ __forceinline__ uint32_t excl_prefix(uint32_t v, uint32_t *s_wsum)
+{
+    const int lane = lane_id();
+    const int w = threadIdx.x / kWave;
+    uint32_t inc = v;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const uint32_t y = __shfl_up(inc, off, kWave);
+        if (lane >= off) inc += y;
+    }
+    __syncthreads();
+    if (lane == kWave - 1) s_wsum[w] = inc;
+    __syncthreads();
+    uint32_t pre = inc - v;
+#pragma unroll
+    for (int q = 0; q < RB / kWave; ++q)
+        if (q < w) pre += s_wsum[q];
+    return pre;
+}
+
+template <bool ROWS>
+__global__ __launch_bounds__(RB) void k_radix_scatter(const uint64_t *kin, const uint32_t *vin,
+                                                      int64_t m, int shift, const uint32_t *offs,
+                                                      int64_t nb, uint64_t *kout, uint32_t *vout,
+                                                      uint32_t *err)
 {
     constexpr int NW = RB / kWave;
-    __shared__ uint32_t s_base[256];
-    __shared__ uint32_t s_wcnt[NW][256];
+    __shared__ uint32_t s_cnt[NW][256];   // records of a wave, then of the waves before
+    __shared__ uint32_t s_off[256];       // where a digit's run of the tile goes, less its start
+    __shared__ uint32_t s_start[256];     // a digit's first record in the ordered tile
+    __shared__ uint32_t s_wsum[NW];
+    __shared__ uint64_t s_key[RT];
+    __shared__ uint32_t s_val[RT];
     const int tid = threadIdx.x;
     const int lane = lane_id();
     const int w = tid / kWave;
-    s_base[tid] = offs[(int64_t)tid * nb + blockIdx.x];
+    const int64_t tile0 = (int64_t)blockIdx.x * RT;
+    const int64_t base = tile0 + (int64_t)w * (RI * kWave) + lane;
+    uint64_t key[RI];
+    uint32_t val[RI];
 #pragma unroll
-    for (int q = 0; q < NW; ++q) s_wcnt[q][tid] = 0;
+    for (int r = 0; r < RI; ++r) {
+        const int64_t idx = base + r * kWave;
+        key[r] = kin[idx < m ? idx : m - 1];
+    }
+#pragma unroll
+    for (int r = 0; r < RI; ++r) {
+        const int64_t idx = base + r * kWave;
+        val[r] = vin[idx < m ? idx : m - 1];
+    }
+    uint32_t first = 0;  // where the tile's run of digit tid goes
+    if constexpr (!ROWS) {
+        first = offs[(int64_t)tid * nb + blockIdx.x];
+    } else if (nb > 1) {
+        // wave w adds every NW-th row up, lane l digits 4 l .. 4 l + 3
+        const uint4 *row = reinterpret_cast<const uint4 *>(offs) + lane;
+        uint4 all = {0, 0, 0, 0}, before = {0, 0, 0, 0};
+#pragma unroll 8
+        for (int64_t q = w; q < nb; q += NW) {
+            const uint4 v = row[q * kWave];
+            const uint32_t m_ = q < blockIdx.x ? ~0u : 0u;
+            all.x += v.x, all.y += v.y, all.z += v.z, all.w += v.w;
+            before.x += v.x & m_, before.y += v.y & m_, before.z += v.z & m_, before.w += v.w & m_;
+        }
+        uint32_t *t = reinterpret_cast<uint32_t *>(s_key);
+        reinterpret_cast<uint4 *>(t)[w * kWave + lane] = all;
+        reinterpret_cast<uint4 *>(t + NW * 256)[w * kWave + lane] = before;
+        __syncthreads();
+        uint32_t sum = 0;
+#pragma unroll
+        for (int q = 0; q < NW; ++q) {
+            sum += t[q * 256 + tid];
+            first += t[(NW + q) * 256 + tid];
+        }
+        first += excl_prefix(sum, s_wsum);
+    }
+#pragma unroll
+    for (int q = 0; q < NW; ++q) s_cnt[q][tid] = 0;
     __syncthreads();
     const uint64_t lt_mask = (lane == 0) ? 0ull : ((~0ull) >> (kWave - lane));
-    const int64_t base = (int64_t)blockIdx.x * RT;
+    uint32_t rank[RI];  // within the wave
+    volatile uint32_t *cnt = s_cnt[w];
+#pragma unroll
     for (int r = 0; r < RI; ++r) {
-        const int64_t idx = base + (int64_t)r * RB + tid;
-        const bool valid = idx < m;
-        const uint64_t key = valid ? kin[idx] : 0ull;
-        const uint32_t digit = valid ? (uint32_t)((key >> shift) & 255u) : 0u;
+        const bool valid = base + r * kWave < m;
+        const uint32_t digit = (uint32_t)(key[r] >> shift) & 255u;
         uint64_t peers = __ballot(valid);
 #pragma unroll
         for (int b = 0; b < 8; ++b) {
@@ -125,28 +227,49 @@ __global__ __launch_bounds__(RB) void k_radix_scatter(const uint64_t *kin,
             const uint64_t mb = __ballot(bit);
             peers &= bit ? mb : ~mb;
         }
-        const uint32_t rank = __popcll(peers & lt_mask);
-        if (valid && rank == 0) s_wcnt[w][digit] = __popcll(peers);
-        __syncthreads();
-        if (valid) {
-            uint32_t off = s_base[digit] + rank;
-            for (int q = 0; q < w; ++q) off += s_wcnt[q][digit];
-            if ((int64_t)off < m) {
-                kout[off] = key;
-                if (HAS_VAL) vout[off] = vin[idx];
-            } else {
-                atomicOr(err, 32u);
-            }
-        }
-        __syncthreads();
-        uint32_t tot = 0;
+        // every lane reads its digit's counter before the first of its
+        // peers moves it on (one wave: its LDS accesses are in order)
+        const uint32_t before = cnt[digit];
+        __builtin_amdgcn_wave_barrier();
+        rank[r] = before + __popcll(peers & lt_mask);
+        if (valid && (peers & lt_mask) == 0) cnt[digit] = before + __popcll(peers);
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    // thread = digit: the waves' counts become the counts of the waves
+    // before, the tile's counts their exclusive prefix over the digits
+    uint32_t total = 0;
 #pragma unroll
-        for (int q = 0; q < NW; ++q) {
-            tot += s_wcnt[q][tid];
-            s_wcnt[q][tid] = 0;
+    for (int q = 0; q < NW; ++q) {
+        const uint32_t c = s_cnt[q][tid];
+        s_cnt[q][tid] = total;
+        total += c;
+    }
+    const uint32_t start = excl_prefix(total, s_wsum);
+    if (ROWS && nb == 1) first = start;
+    s_start[tid] = start;
+    s_off[tid] = first - start;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < RI; ++r) {
+        if (base + r * kWave < m) {
+            const uint32_t digit = (uint32_t)(key[r] >> shift) & 255u;
+            const uint32_t at = s_start[digit] + s_cnt[w][digit] + rank[r];
+            s_key[at] = key[r];
+            s_val[at] = val[r];
         }
-        s_base[tid] += tot;
-        __syncthreads();
+    }
+    __syncthreads();
+    const int cnt_tile = (int)min((int64_t)RT, m - tile0);
+    for (int i = tid; i < cnt_tile; i += RB) {
+        const uint64_t k = s_key[i];
+        const uint32_t off = s_off[(uint32_t)(k >> shift) & 255u] + (uint32_t)i;
+        if ((int64_t)off < m) {
+            kout[off] = k;
+            vout[off] = s_val[i];
+        } else {
+            atomicOr(err, 32u);
+        }
     }
 }
 
@@ -159,48 +282,128 @@ __device__ __forceinline__ uint64_t desc_key(double y)
     return ~asc;  // ascending key order = decreasing time
 }
 
-__global__ void k_time_keys(const double *y, int64_t n, uint64_t *keys, uint64_t *vals)
+// The record of a subject: its key, and its index with the status in the two
+// bits above it (PACKED: n <= 2^30), so that the order brings both along and
+// nothing is gathered through it.  *vary collects the key bits in which the
+// subjects differ.
+constexpr int kIdxBits = 30;
+
+template <bool PACKED>
+__global__ __launch_bounds__(256) void k_time_keys(const double *y, const int8_t *status,
+                                                   int64_t n, uint64_t *keys, uint32_t *vals,
+                                                   unsigned long long *vary, uint32_t *err)
 {
+    __shared__ uint64_t s_v[256 / kWave];
+    const uint64_t k0 = desc_key(y[0]);
+    uint64_t v = 0;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
-        keys[i] = desc_key(y[i]);
-        vals[i] = (uint64_t)i;
-    }
-}
-
-__global__ void k_after_sort(int64_t n, int model, const uint64_t *sorted_idx,
-                             const double *y, const int8_t *status, int32_t *perm,
-                             int32_t *inv_perm, double *y_s, int8_t *st_s,
-                             uint8_t *ev_s, uint32_t *ev_bits, uint32_t *err)
-{
-    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n;
-         k += (int64_t)gridDim.x * blockDim.x) {
-        int64_t i = (int64_t)sorted_idx[k];
-        if (i < 0 || i >= n) {
-            atomicOr(err, 64u);
-            i = 0;
-        }
-        perm[k] = (int32_t)i;
-        inv_perm[i] = (int32_t)k;
-        y_s[k] = y[i];
+        const uint64_t k = desc_key(y[i]);
         int8_t s = status[i];
         if (s < 0 || s > 2) {
             atomicOr(err, 2u);
             s = 0;
         }
-        st_s[k] = s;
-        const bool ev = model == SS_COX ? (s != 0) : (s == 1);
-        ev_s[k] = ev;
-        const uint64_t bits = __ballot(ev);  // k is a multiple of 64 at lane 0
-        if (lane_id() == 0) *reinterpret_cast<uint64_t *>(ev_bits + k / 32) = bits;
+        keys[i] = k;
+        vals[i] = (uint32_t)i | (PACKED ? (uint32_t)s << kIdxBits : 0u);
+        v |= k ^ k0;
+    }
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) v |= __shfl_xor(v, off, kWave);
+    if (lane_id() == 0) s_v[threadIdx.x / kWave] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int q = 1; q < 256 / kWave; ++q) v |= s_v[q];
+        // 2048 workgroups' atomics on one word took 22 us; most add nothing
+        if (v & ~__hip_atomic_load(vary, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicOr(vary, (unsigned long long)v);
     }
 }
 
-__global__ void k_run_start(int64_t n, const double *y_s, int32_t *start)
+// The order from the sorted records.  low > 0: the keys are in order by the
+// bits from `low` up only, so a group of records that agree in those is put in
+// order here -- by (key, position), which is what the remaining stable passes
+// would give -- each position ranking its group's records itself.  Groups of
+// equal keys are in order already; a group of different ones with over
+// kGroupMax records on either side of a change sets err[1], and the
+// caller orders all bits instead (1e6 continuous times and one far from them:
+// 557 us for a preparation that always ordered all 64 bits, 594 with the
+// attempt first; without the far one 571 and 319).
+//
+// Continuous times differ in sign and exponent, 12 bits at most, and spread
+// over the mantissa: 20 bits of it leave groups of below 8 records on average
+// up to kFewBits subjects, 28 bits below 8 at any size.  Times in whole units
+// vary in few bits and have none left for this.
+constexpr int64_t kFewBits = (int64_t)1 << 23;
+constexpr int kGroupMax = 32;
+
+template <bool PACKED>
+__global__ __launch_bounds__(256) void k_after_sort(int64_t n, int model, int low,
+                                                    const uint64_t *keys, const uint32_t *vals,
+                                                    const int8_t *status, int32_t *perm,
+                                                    int32_t *inv_perm, uint64_t *key_s,
+                                                    int8_t *st_s, uint32_t *ev_bits,
+                                                    uint32_t *err)
 {
     for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n;
-         k += (int64_t)gridDim.x * blockDim.x)
-        start[k] = (k == 0 || y_s[k] != y_s[k - 1]) ? 1 : 0;
+         k += (int64_t)gridDim.x * blockDim.x) {
+        if (low > 0 &&
+            __hip_atomic_load(err + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            return;
+        int64_t from = k;
+        uint64_t key = keys[k];
+        const uint64_t prev = k > 0 ? keys[k - 1] : ~key, next = k + 1 < n ? keys[k + 1] : ~key;
+        if (low > 0 && ((prev ^ key) >> low == 0 || (next ^ key) >> low == 0)) {
+            int64_t a = k, b = k;  // the group, as far as it is looked at
+            // one look at the ends of that settles most large groups
+            const uint64_t fa = keys[k > kGroupMax ? k - kGroupMax - 1 : k];
+            const uint64_t fb = keys[k + kGroupMax + 1 < n ? k + kGroupMax + 1 : k];
+            if ((fa != key && (fa ^ key) >> low == 0) || (fb != key && (fb ^ key) >> low == 0)) {
+                err[1] = 1u;  // no atomic: thousands of waves may get here
+                return;  // all of this is done again
+            }
+            bool mixed = false;
+            while (a > 0 && k - a <= kGroupMax && (keys[a - 1] ^ key) >> low == 0) {
+                --a;
+                mixed = mixed || keys[a] != key;
+            }
+            while (b + 1 < n && b - k <= kGroupMax && (keys[b + 1] ^ key) >> low == 0) {
+                ++b;
+                mixed = mixed || keys[b] != key;
+            }
+            if (mixed && (k - a > kGroupMax || b - k > kGroupMax)) {
+                err[1] = 1u;
+                return;
+            }
+            if (mixed) {
+                for (int64_t q = a; q <= b; ++q) {
+                    const uint64_t kq = keys[q];
+                    int64_t at = a;
+                    for (int64_t r = a; r <= b; ++r) {
+                        const uint64_t kr = keys[r];
+                        at += kr < kq || (kr == kq && r < q);
+                    }
+                    if (at == k) from = q;
+                }
+                key = keys[from];
+            }
+        }
+        const uint32_t v = vals[from];
+        int64_t i = PACKED ? v & ((1u << kIdxBits) - 1u) : v;
+        if (i >= n) {
+            atomicOr(err, 64u);
+            i = 0;
+        }
+        int8_t s = PACKED ? (int8_t)(v >> kIdxBits) : status[i];
+        if (s < 0 || s > 2) s = 0;  // reported by k_time_keys
+        perm[k] = (int32_t)i;
+        inv_perm[i] = (int32_t)k;
+        key_s[k] = key;
+        st_s[k] = s;
+        const bool ev = model == SS_COX ? (s != 0) : (s == 1);
+        const uint64_t bits = __ballot(ev);  // k is a multiple of 64 at lane 0
+        if (lane_id() == 0) *reinterpret_cast<uint64_t *>(ev_bits + k / 32) = bits;
+    }
 }
 
 __global__ void k_fill_i32(int32_t *p, int64_t m, int32_t v)
@@ -210,49 +413,127 @@ __global__ void k_fill_i32(int32_t *p, int64_t m, int32_t v)
         p[k] = v;
 }
 
-// runid = inclusive scan of run starts, minus one
-__global__ void k_run_counts(int64_t n, const int32_t *run_incl, const uint8_t *ev_s,
-                             const int8_t *st_s, int32_t *cnt_ev, int32_t *cnt_cens,
-                             uint32_t *err)
+// A NaN time ties with nothing.
+__device__ __forceinline__ bool same_time(uint64_t a, uint64_t b)
 {
-    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n;
-         k += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t r = run_incl[k] - 1;
-        if (r < 0 || r >= n) {
-            atomicOr(err, 128u);
-            continue;
+    const uint64_t inf = 0x000fffffffffffffull;  // +inf; -inf is its complement
+    return a == b && a >= inf && a <= ~inf;
+}
+
+// Counts since the start of the tie run, as a scan: bit 63 marks a span with
+// a run start in it, bits 31..61 count the events and bits 0..30 the censored
+// subjects after the last one.
+struct OpRun {
+    __device__ static uint64_t id() { return 0; }
+    __device__ static uint64_t op(uint64_t a, uint64_t b) { return (b >> 63) ? b : a + b; }
+};
+
+__device__ __forceinline__ void run_items(int64_t n, int model, const uint64_t *key_s,
+                                          const int8_t *st_s, int64_t k0, uint64_t (&key)[SI],
+                                          uint64_t (&it)[SI])
+{
+    load_items<uint64_t, OpRun>(key_s, k0, n, key);
+    uint64_t prev = k0 > 0 && k0 < n ? key_s[k0 - 1] : 0;
+    // st_s is aligned to 256 bytes and holds whole runs of SI
+    const uint64_t st = k0 < n ? *reinterpret_cast<const uint64_t *>(st_s + k0) : 0;
+#pragma unroll
+    for (int i = 0; i < SI; ++i) {
+        const int64_t k = k0 + i;
+        it[i] = 0;
+        if (k < n) {
+            const int8_t s = (int8_t)(st >> (8 * i));
+            const bool ev = model == SS_COX ? (s != 0) : (s == 1);
+            it[i] = ((uint64_t)(k == 0 || !same_time(key[i], prev)) << 63) | ((uint64_t)ev << 31) |
+                    (uint64_t)(s == 0);
+            prev = key[i];
         }
-        if (ev_s[k]) atomicAdd(&cnt_ev[r], 1);
-        if (st_s[k] == 0) atomicAdd(&cnt_cens[r], 1);
     }
 }
 
-// d at run ends; Kaplan-Meier factor 1 - m_c / #{y >= c} at run ends
-// (#{y >= c} = position of the run's last subject + 1).
-__global__ void k_run_finish(int64_t n, const double *y_s, const int32_t *run_incl,
-                             const int32_t *cnt_ev, const int32_t *cnt_cens,
-                             uint8_t *d8, int32_t *d32, double *fac)
+__global__ __launch_bounds__(SB) void k_runs_reduce(int64_t n, int model, const uint64_t *key_s,
+                                                    const int8_t *st_s, uint64_t *sums)
 {
-    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n;
-         k += (int64_t)gridDim.x * blockDim.x) {
-        const bool end = (k == n - 1) || (y_s[k] != y_s[k + 1]);
-        int32_t r = run_incl[k] - 1;
-        if (r < 0 || r >= n) r = 0;  // reported by k_run_counts
-        const int32_t d = end ? cnt_ev[r] : 0;
-        d32[k] = d;
-        d8[k] = (uint8_t)(d > 255 ? 255 : d);
-        if (fac) {
-            fac[k] = end ? 1.0 - (double)cnt_cens[r] / (double)(k + 1) : 1.0;
+    __shared__ uint64_t s_w[SB / kWave];
+    uint64_t key[SI], it[SI];
+    run_items(n, model, key_s, st_s, (int64_t)blockIdx.x * ST + (int64_t)threadIdx.x * SI, key, it);
+    const uint64_t t = block_scan<uint64_t, OpRun>(it, 0, s_w);
+    if (threadIdx.x == 0) sums[blockIdx.x] = t;
+}
+
+// d at run ends; Fine-Gray also the Kaplan-Meier factor 1 - m_c / #{y >= c} at
+// run ends (#{y >= c} = position of the run's last subject + 1), 1 elsewhere,
+// and the product of a tile's factors (from the last tile on).
+template <bool FG>
+__global__ __launch_bounds__(SB) void k_runs_finish(int64_t n, int model, int64_t tiles,
+                                                    const uint64_t *key_s, const int8_t *st_s,
+                                                    const uint64_t *sums, uint8_t *d8,
+                                                    int32_t *d32, double *fac, double *prods)
+{
+    __shared__ uint64_t s_w[SB / kWave];
+    __shared__ double s_p[SB / kWave];
+    const int64_t k0 = (int64_t)blockIdx.x * ST + (int64_t)threadIdx.x * SI;
+    uint64_t key[SI], it[SI];
+    run_items(n, model, key_s, st_s, k0, key, it);
+    const uint64_t carry = tile_carry<uint64_t, OpRun, false>(sums, tiles, s_w);
+    block_scan<uint64_t, OpRun>(it, carry, s_w);
+    const uint64_t after = k0 + SI < n ? key_s[k0 + SI] : 0;
+    double f[SI], prod = 1.0;
+    int32_t d[SI];
+    uint64_t d8v = 0;
+#pragma unroll
+    for (int i = 0; i < SI; ++i) {
+        const int64_t k = k0 + i;
+        f[i] = 1.0;
+        d[i] = 0;
+        if (k < n) {
+            const bool end = k == n - 1 || !same_time(key[i], i + 1 < SI ? key[(i + 1) % SI] : after);
+            if (end) d[i] = (int32_t)((it[i] >> 31) & 0x7fffffffu);
+            d8v |= (uint64_t)(d[i] > 255 ? 255 : d[i]) << (8 * i);
+            if (FG && end) f[i] = 1.0 - (double)(int32_t)(it[i] & 0x7fffffffu) / (double)(k + 1);
         }
+        prod *= f[i];
+    }
+    store_items<int32_t>(d32, k0, n, d);
+    if (k0 + SI <= n && ((uintptr_t)(d8 + k0) & 7u) == 0) {
+        *reinterpret_cast<uint64_t *>(d8 + k0) = d8v;
+    } else {
+        for (int i = 0; i < SI; ++i)
+            if (k0 + i < n) d8[k0 + i] = (uint8_t)(d8v >> (8 * i));
+    }
+    if constexpr (FG) {
+        store_items<double>(fac, k0, n, f);
+        for (int off = 32; off > 0; off >>= 1) prod *= __shfl_down(prod, off);
+        if (lane_id() == 0) s_p[threadIdx.x / kWave] = prod;
+        __syncthreads();
+        if (threadIdx.x == 0)
+            prods[tiles - 1 - blockIdx.x] = ((s_p[0] * s_p[1]) * s_p[2]) * s_p[3];
     }
 }
 
-__global__ void k_fg_weights(int64_t n, const int8_t *st_s, const double *g_end,
-                             double *w_comp)
+// Kaplan-Meier G as the inclusive suffix product of the factors, and the
+// competing-event weights.  Tile t scans from the end of the positions.
+__global__ __launch_bounds__(SB) void k_km_weights(int64_t n, int64_t tiles, const double *fac,
+                                                   const double *prods, const int8_t *st_s,
+                                                   double *g_end, double *w_comp)
 {
-    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n;
-         k += (int64_t)gridDim.x * blockDim.x)
-        w_comp[k] = st_s[k] == 2 ? 1.0 / g_end[k] : 0.0;
+    __shared__ double s_w[SB / kWave];
+    // thread t holds the items of run SB - 1 - t of the tile, last one first
+    const int64_t k0 = (int64_t)blockIdx.x * ST + (int64_t)(SB - 1 - (int)threadIdx.x) * SI;
+    double f[SI], it[SI];
+    load_items<double, OpMul<double>>(fac, k0, n, f);
+#pragma unroll
+    for (int i = 0; i < SI; ++i) it[i] = f[SI - 1 - i];
+    const double carry = tile_carry<double, OpMul<double>, true>(prods, tiles, s_w);
+    block_scan<double, OpMul<double>>(it, carry, s_w);
+    double g[SI], wt[SI];
+#pragma unroll
+    for (int i = 0; i < SI; ++i) {
+        g[i] = it[SI - 1 - i];
+        const int64_t k = k0 + i;
+        wt[i] = k < n && st_s[k] == 2 ? 1.0 / g[i] : 0.0;
+    }
+    store_items<double>(g_end, k0, n, g);
+    store_items<double>(w_comp, k0, n, wt);
 }
 
 int grid_1d(int64_t work, int cap = 8192)
@@ -265,18 +546,14 @@ int grid_1d(int64_t work, int cap = 8192)
 
 // ------------------------------------------------------------ workspace
 struct PrepWs {
-    uint64_t *keyA, *keyB, *valA, *valB;
+    uint64_t *keyA, *keyB;
+    uint32_t *valA, *valB;
     uint32_t *hist;
     uint64_t *sums;       // scan spine (8-byte slots for any T)
-    double *y_s;
-    double *fac;
-    int32_t *run_incl;
-    int32_t *cnt_ev;
-    int32_t *cnt_cens;
+    double *prods;
     int8_t *st_s;
-    uint8_t *ev_s;
     uint32_t *ev_bits;
-    uint32_t *err;
+    uint64_t *vary;       // then the error word and k_after_sort's
     void *design;
 };
 
@@ -294,67 +571,52 @@ size_t layout(int64_t n, int64_t p, int64_t nnz, char *base, PrepWs *w)
     };
     PrepWs t;
     t.ev_bits = (uint32_t *)take(4 * 2 * (size_t)ceil_div(n, kWave));
-    t.err = (uint32_t *)take(256);
+    t.vary = (uint64_t *)take(256);
     // the design's scratch takes the place of the ordering's, which is done
     t.design = base ? base + off : nullptr;
     const size_t design_end = off + design_ws_bytes(n, p, nnz);
     t.keyA = (uint64_t *)take(8 * (size_t)n);
     t.keyB = (uint64_t *)take(8 * (size_t)n);
-    t.valA = (uint64_t *)take(8 * (size_t)n);
-    t.valB = (uint64_t *)take(8 * (size_t)n);
+    t.valA = (uint32_t *)take(4 * (size_t)n);
+    t.valB = (uint32_t *)take(4 * (size_t)n);
     t.hist = (uint32_t *)take(4 * (size_t)hist_len);
     t.sums = (uint64_t *)take(8 * (size_t)nbs);
-    t.y_s = (double *)take(8 * (size_t)n);
-    t.fac = (double *)take(8 * (size_t)n);
-    t.run_incl = (int32_t *)take(4 * (size_t)n);
-    t.cnt_ev = (int32_t *)take(4 * (size_t)n);
-    t.cnt_cens = (int32_t *)take(4 * (size_t)n);
-    t.st_s = (int8_t *)take((size_t)n);
-    t.ev_s = (uint8_t *)take((size_t)n);
+    t.prods = (double *)take(8 * (size_t)nbs);
+    t.st_s = (int8_t *)take(align_up((size_t)n, SI));
     if (w) *w = t;
     return off > design_end ? off : design_end;
 }
 
-template <typename T, typename Op, bool REV, bool EXCL>
-int32_t device_scan(const T *in, T *out, int64_t m, uint64_t *sums_raw, hipStream_t s)
+// Sorts (keyA, valA) by the key bits [low, high); result in the returned
+// buffers.
+int32_t radix_sort(int64_t m, int low, int high, PrepWs &w, uint64_t **keys_out,
+                   uint32_t **vals_out, hipStream_t s)
 {
-    if (m <= 0) return SS_OK;
-    T *sums = (T *)sums_raw;
-    const int64_t nb = ceil_div(m, ST);
-    hipLaunchKernelGGL((k_scan_reduce<T, Op, REV>), dim3((unsigned)nb), dim3(SB), 0, s, in, m, sums);
-    SS_LAUNCH_CHECK();
-    hipLaunchKernelGGL((k_scan_spine<T, Op>), dim3(1), dim3(SB), 0, s, sums, nb);
-    SS_LAUNCH_CHECK();
-    hipLaunchKernelGGL((k_scan_down<T, Op, REV, EXCL>), dim3((unsigned)nb), dim3(SB), 0, s, in, out, m,
-                       (const T *)sums);
-    SS_LAUNCH_CHECK();
-    return SS_OK;
-}
-
-// Sorts (keyA, valA) by key bits [0, nbits); result in the returned buffers.
-int32_t radix_sort(int64_t m, int nbits, bool has_val, PrepWs &w, uint64_t **keys_out,
-                   uint64_t **vals_out, hipStream_t s)
-{
-    uint64_t *ka = w.keyA, *kb = w.keyB, *va = w.valA, *vb = w.valB;
+    uint64_t *ka = w.keyA, *kb = w.keyB;
+    uint32_t *va = w.valA, *vb = w.valB;
     const int64_t nb = ceil_div(m, RT);
-    for (int shift = 0; shift < nbits; shift += 8) {
-        if (m > 0) {
-            hipLaunchKernelGGL(k_radix_hist, dim3((unsigned)nb), dim3(RB), 0, s, ka, m, shift,
-                               w.hist, nb);
+    for (int shift = low; shift < high; shift += 8) {
+        const dim3 grid((unsigned)nb);
+        if (nb <= kOwnOffsets) {
+            if (nb > 1) {
+                hipLaunchKernelGGL(k_radix_hist<true>, grid, dim3(RB), 0, s, ka, m, shift, w.hist,
+                                   nb);
+                SS_LAUNCH_CHECK();
+            }
+            hipLaunchKernelGGL(k_radix_scatter<true>, grid, dim3(RB), 0, s, ka, va, m, shift,
+                               w.hist, nb, kb, vb, (uint32_t *)(w.vary + 1));
+        } else {
+            hipLaunchKernelGGL(k_radix_hist<false>, grid, dim3(RB), 0, s, ka, m, shift, w.hist,
+                               nb);
             SS_LAUNCH_CHECK();
-            int32_t rc = device_scan<uint32_t, OpAdd<uint32_t>, false, true>(
-                w.hist, w.hist, 256 * nb, w.sums, s);
+            const int32_t rc = scan_add_u32_excl(w.hist, w.hist, 256 * nb, w.sums, s);
             if (rc) return rc;
-            if (has_val)
-                hipLaunchKernelGGL(k_radix_scatter<true>, dim3((unsigned)nb), dim3(RB), 0, s, ka,
-                                   va, m, shift, w.hist, nb, kb, vb, w.err);
-            else
-                hipLaunchKernelGGL(k_radix_scatter<false>, dim3((unsigned)nb), dim3(RB), 0, s, ka,
-                                   va, m, shift, w.hist, nb, kb, vb, w.err);
-            SS_LAUNCH_CHECK();
+            hipLaunchKernelGGL(k_radix_scatter<false>, grid, dim3(RB), 0, s, ka, va, m, shift,
+                               w.hist, nb, kb, vb, (uint32_t *)(w.vary + 1));
         }
-        uint64_t *t = ka; ka = kb; kb = t;
-        t = va; va = vb; vb = t;
+        SS_LAUNCH_CHECK();
+        std::swap(ka, kb);
+        std::swap(va, vb);
     }
     *keys_out = ka;
     *vals_out = va;
@@ -380,72 +642,122 @@ int32_t run_prepare(int32_t model, int64_t n, int64_t p, int64_t nnz, const doub
     const bool fg = model == SS_FINE_GRAY;
     int32_t rc;
 
-    // ---- the column pointers, checked on the host
+    uint32_t *err = (uint32_t *)(w.vary + 1);
+    const bool packed = n <= (int64_t)1 << kIdxBits;
     std::vector<int64_t> cp_host((size_t)p + 1);
-    SS_HIP_CHECK(hipMemcpyAsync(cp_host.data(), col_ptr, sizeof(int64_t) * (size_t)(p + 1),
-                                hipMemcpyDeviceToHost, s));
-    SS_HIP_CHECK(hipStreamSynchronize(s));
-    if (cp_host[0] != 0 || cp_host[(size_t)p] != nnz) return SS_EINVAL;
-    for (int64_t j = 0; j < p; ++j) {
-        const int64_t a = cp_host[(size_t)j], b = cp_host[(size_t)j + 1];
-        if (b < a || a < 0 || b > nnz) return SS_EINVAL;
-    }
-
-    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, s, (int32_t *)w.err, (int64_t)1, 0);
-    SS_LAUNCH_CHECK();
-
-    // ---- ordering by decreasing time, stable in the subject index
-    hipLaunchKernelGGL(k_time_keys, dim3(grid_1d(n)), dim3(256), 0, s, y, n, w.keyA, w.valA);
-    SS_LAUNCH_CHECK();
-    uint64_t *ks, *vs;
-    rc = radix_sort(n, 64, true, w, &ks, &vs, s);
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_after_sort, dim3(grid_1d(n)), dim3(256), 0, s, n, (int)model, vs, y,
-                       status, perm, inv_perm, w.y_s, w.st_s, w.ev_s, w.ev_bits, w.err);
-    SS_LAUNCH_CHECK();
-
-    // ---- tie runs and event counts
-    hipLaunchKernelGGL(k_run_start, dim3(grid_1d(n)), dim3(256), 0, s, n, w.y_s, w.run_incl);
-    SS_LAUNCH_CHECK();
-    rc = device_scan<int32_t, OpAdd<int32_t>, false, false>(w.run_incl, w.run_incl, n, w.sums, s);
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_fill_i32, dim3(grid_1d(n)), dim3(256), 0, s, w.cnt_ev, n, 0);
-    SS_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_fill_i32, dim3(grid_1d(n)), dim3(256), 0, s, w.cnt_cens, n, 0);
-    SS_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_run_counts, dim3(grid_1d(n)), dim3(256), 0, s, n, w.run_incl, w.ev_s,
-                       w.st_s, w.cnt_ev, w.cnt_cens, w.err);
-    SS_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_run_finish, dim3(grid_1d(n)), dim3(256), 0, s, n, w.y_s, w.run_incl,
-                       w.cnt_ev, w.cnt_cens, d8, d32, fg ? w.fac : (double *)nullptr);
-    SS_LAUNCH_CHECK();
-
-    // ---- Fine-Gray: Kaplan-Meier G as an inclusive suffix product
-    if (fg) {
-        rc = device_scan<double, OpMul<double>, true, false>(w.fac, g_end, n, w.sums, s);
-        if (rc) return rc;
-        hipLaunchKernelGGL(k_fg_weights, dim3(grid_1d(n)), dim3(256), 0, s, n, w.st_s, g_end,
-                           w_comp);
-        SS_LAUNCH_CHECK();
-    }
-
-    // ---- design: re-labelled to sorted positions, ascending inside columns
     std::vector<int64_t> host_list;
-    rc = run_design(n, p, nnz, cp_host.data(), col_ptr, rows, vals, inv_perm, w.ev_bits,
-                    rows_sorted, vals_sorted, chunk_ptr, c, w.err, w.design, host_list, s);
-    if (rc) return rc;
+    for (bool all_bits = false;; all_bits = true) {
+        hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, s, (int32_t *)w.vary, (int64_t)4, 0);
+        SS_LAUNCH_CHECK();
+        if (packed)
+            hipLaunchKernelGGL(k_time_keys<true>, dim3(grid_1d(n, 1024)), dim3(256), 0, s, y,
+                               status, n, w.keyA, w.valA, (unsigned long long *)w.vary, err);
+        else
+            hipLaunchKernelGGL(k_time_keys<false>, dim3(grid_1d(n, 1024)), dim3(256), 0, s, y,
+                               status, n, w.keyA, w.valA, (unsigned long long *)w.vary, err);
+        SS_LAUNCH_CHECK();
+        // ---- on the host: the key bits that vary, and the column pointers,
+        // which are checked here
+        uint64_t vary = 0;
+        SS_HIP_CHECK(hipMemcpyAsync(&vary, w.vary, sizeof(vary), hipMemcpyDeviceToHost, s));
+        SS_HIP_CHECK(hipMemcpyAsync(cp_host.data(), col_ptr, sizeof(int64_t) * (size_t)(p + 1),
+                                    hipMemcpyDeviceToHost, s));
+        SS_HIP_CHECK(hipStreamSynchronize(s));
+        if (cp_host[0] != 0 || cp_host[(size_t)p] != nnz) return SS_EINVAL;
+        for (int64_t j = 0; j < p; ++j) {
+            const int64_t a = cp_host[(size_t)j], b = cp_host[(size_t)j + 1];
+            if (b < a || a < 0 || b > nnz) return SS_EINVAL;
+        }
 
-    // ---- data errors found on the device
-    uint32_t err = 0;
-    SS_HIP_CHECK(hipMemcpyAsync(&err, w.err, sizeof(err), hipMemcpyDeviceToHost, s));
-    SS_HIP_CHECK(hipStreamSynchronize(s));
-    return err ? SS_EINVAL : SS_OK;
+        // ---- ordering by decreasing time, stable in the subject index: the
+        // upper 32 (n > kFewBits: 40) of the bits that vary, the rest within
+        // the groups that agree in those, or, where one is not small, all
+        const int high = vary ? 64 - __builtin_clzll(vary) : 0;
+        const int bottom = vary ? __builtin_ctzll(vary) : 0;
+        int low = bottom;
+        const int bits = n <= kFewBits ? 32 : 40;
+        if (!all_bits && high - bits > bottom) low = high - bits;
+        uint64_t *ks;
+        uint32_t *vs;
+        rc = radix_sort(n, low, high, w, &ks, &vs, s);
+        if (rc) return rc;
+        uint64_t *key_s = ks == w.keyA ? w.keyB : w.keyA;
+        const int check = low > bottom ? low : 0;
+        if (packed)
+            hipLaunchKernelGGL(k_after_sort<true>, dim3(grid_1d(n)), dim3(256), 0, s, n,
+                               (int)model, check, ks, vs, status, perm, inv_perm, key_s, w.st_s,
+                               w.ev_bits, err);
+        else
+            hipLaunchKernelGGL(k_after_sort<false>, dim3(grid_1d(n)), dim3(256), 0, s, n,
+                               (int)model, check, ks, vs, status, perm, inv_perm, key_s, w.st_s,
+                               w.ev_bits, err);
+        SS_LAUNCH_CHECK();
+        uint32_t found = 0;
+        if (check) {
+            SS_HIP_CHECK(hipMemcpyAsync(&found, err + 1, sizeof(found), hipMemcpyDeviceToHost, s));
+            SS_HIP_CHECK(hipStreamSynchronize(s));
+            if (found) continue;
+        }
+
+        // ---- tie runs and event counts; Fine-Gray: Kaplan-Meier G and the
+        // weights
+        const int64_t tiles = ceil_div(n, (int64_t)ST);
+        const dim3 tg((unsigned)tiles);
+        hipLaunchKernelGGL(k_runs_reduce, tg, dim3(SB), 0, s, n, (int)model, key_s, w.st_s,
+                           w.sums);
+        SS_LAUNCH_CHECK();
+        if (tiles > ST) {
+            hipLaunchKernelGGL((k_scan_spine<uint64_t, OpRun>), dim3(1), dim3(SB), 0, s, w.sums,
+                               tiles);
+            SS_LAUNCH_CHECK();
+        }
+        double *fac = (double *)ks;  // the sorted records have been read
+        if (fg) {
+            hipLaunchKernelGGL(k_runs_finish<true>, tg, dim3(SB), 0, s, n, (int)model, tiles,
+                               key_s, w.st_s, w.sums, d8, d32, fac, w.prods);
+            SS_LAUNCH_CHECK();
+            if (tiles > ST) {
+                hipLaunchKernelGGL((k_scan_spine<double, OpMul<double>>), dim3(1), dim3(SB), 0, s,
+                                   w.prods, tiles);
+                SS_LAUNCH_CHECK();
+            }
+            hipLaunchKernelGGL(k_km_weights, tg, dim3(SB), 0, s, n, tiles, fac, w.prods, w.st_s,
+                               g_end, w_comp);
+        } else {
+            hipLaunchKernelGGL(k_runs_finish<false>, tg, dim3(SB), 0, s, n, (int)model, tiles,
+                               key_s, w.st_s, w.sums, d8, d32, fac, w.prods);
+        }
+        SS_LAUNCH_CHECK();
+
+        // ---- design: re-labelled to sorted positions, ascending inside columns
+        host_list.clear();
+        rc = run_design(n, p, nnz, cp_host.data(), col_ptr, rows, vals, inv_perm, w.ev_bits,
+                        rows_sorted, vals_sorted, chunk_ptr, c, err, w.design, host_list, s);
+        if (rc) return rc;
+
+        // ---- data errors found on the device
+        SS_HIP_CHECK(hipMemcpyAsync(&found, err, sizeof(found), hipMemcpyDeviceToHost, s));
+        SS_HIP_CHECK(hipStreamSynchronize(s));
+        return found ? SS_EINVAL : SS_OK;
+    }
 }
 
-int32_t scan_add_u32_excl(const uint32_t *in, uint32_t *out, int64_t m, void *sums, hipStream_t s)
+int32_t scan_add_u32_excl(const uint32_t *in, uint32_t *out, int64_t m, void *sums_raw,
+                          hipStream_t s)
 {
-    return device_scan<uint32_t, OpAdd<uint32_t>, false, true>(
-        in, out, m, reinterpret_cast<uint64_t *>(sums), s);
+    if (m <= 0) return SS_OK;
+    uint32_t *sums = (uint32_t *)sums_raw;
+    const int64_t tiles = ceil_div(m, (int64_t)ST);
+    hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)tiles), dim3(SB), 0, s, in, m, sums);
+    SS_LAUNCH_CHECK();
+    if (tiles > ST) {
+        hipLaunchKernelGGL((k_scan_spine<uint32_t, OpAdd<uint32_t>>), dim3(1), dim3(SB), 0, s,
+                           sums, tiles);
+        SS_LAUNCH_CHECK();
+    }
+    hipLaunchKernelGGL(k_scan_down, dim3((unsigned)tiles), dim3(SB), 0, s, in, out, m, tiles, sums);
+    SS_LAUNCH_CHECK();
+    return SS_OK;
 }
 
 }  // namespace ss

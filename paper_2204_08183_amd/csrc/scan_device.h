@@ -63,30 +63,21 @@ __device__ T block_scan(T (&it)[SI], T carry, T *s_w)
     return total;
 }
 
-template <typename T, bool REV>
-__device__ __forceinline__ int64_t phys(int64_t i, int64_t m)
+// A thread's SI items are consecutive in memory: a whole, 16-byte aligned run
+// moves as 16-byte vectors, anything else item by item.
+template <typename T>
+__device__ __forceinline__ bool whole_run(const T *p, int64_t base, int64_t m)
 {
-    return REV ? m - 1 - i : i;
+    return base + SI <= m && ((uintptr_t)(p + base) & 15u) == 0;
 }
 
-// A thread's SI items are consecutive in memory (descending addresses when
-// REV): a whole, 16-byte aligned run moves as 16-byte vectors, anything
-// else item by item.
-template <typename T, bool REV>
-__device__ __forceinline__ const T *item_run(const T *p, int64_t base, int64_t m)
-{
-    if (base + SI > m) return nullptr;
-    const T *r = p + (REV ? m - base - SI : base);
-    return ((uintptr_t)r & 15u) == 0 ? r : nullptr;
-}
-
-template <typename T, typename Op, bool REV>
+template <typename T, typename Op>
 __device__ __forceinline__ void load_items(const T *in, int64_t base, int64_t m, T (&it)[SI])
 {
     static_assert((SI * sizeof(T)) % 16 == 0, "a run of items is whole 16-byte vectors");
     constexpr int PV = 16 / sizeof(T);  // items per vector
-    if (const T *r = item_run<T, REV>(in, base, m)) {
-        const uint4 *v = reinterpret_cast<const uint4 *>(r);
+    if (whole_run(in, base, m)) {
+        const uint4 *v = reinterpret_cast<const uint4 *>(in + base);
 #pragma unroll
         for (int q = 0; q < SI / PV; ++q) {
             union {
@@ -95,26 +86,20 @@ __device__ __forceinline__ void load_items(const T *in, int64_t base, int64_t m,
             } x;
             x.u = v[q];
 #pragma unroll
-            for (int k = 0; k < PV; ++k) {
-                const int i = q * PV + k;  // memory order
-                it[REV ? SI - 1 - i : i] = x.t[k];
-            }
+            for (int k = 0; k < PV; ++k) it[q * PV + k] = x.t[k];
         }
         return;
     }
 #pragma unroll
-    for (int i = 0; i < SI; ++i) {
-        const int64_t l = base + i;
-        it[i] = l < m ? in[phys<T, REV>(l, m)] : Op::id();
-    }
+    for (int i = 0; i < SI; ++i) it[i] = base + i < m ? in[base + i] : Op::id();
 }
 
-template <typename T, bool REV>
+template <typename T>
 __device__ __forceinline__ void store_items(T *out, int64_t base, int64_t m, const T (&it)[SI])
 {
     constexpr int PV = 16 / sizeof(T);
-    if (T *r = const_cast<T *>(item_run<T, REV>(out, base, m))) {
-        uint4 *v = reinterpret_cast<uint4 *>(r);
+    if (whole_run(out, base, m)) {
+        uint4 *v = reinterpret_cast<uint4 *>(out + base);
 #pragma unroll
         for (int q = 0; q < SI / PV; ++q) {
             union {
@@ -122,19 +107,14 @@ __device__ __forceinline__ void store_items(T *out, int64_t base, int64_t m, con
                 T t[PV];
             } x;
 #pragma unroll
-            for (int k = 0; k < PV; ++k) {
-                const int i = q * PV + k;
-                x.t[k] = it[REV ? SI - 1 - i : i];
-            }
+            for (int k = 0; k < PV; ++k) x.t[k] = it[q * PV + k];
             v[q] = x.u;
         }
         return;
     }
 #pragma unroll
-    for (int i = 0; i < SI; ++i) {
-        const int64_t l = base + i;
-        if (l < m) out[phys<T, REV>(l, m)] = it[i];
-    }
+    for (int i = 0; i < SI; ++i)
+        if (base + i < m) out[base + i] = it[i];
 }
 
 // Turns the inclusive values left by block_scan into exclusive ones: the

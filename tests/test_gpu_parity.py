@@ -503,6 +503,91 @@ def test_design_ordering(n, counts, valued):
         assert abs(got_c[j] - want) <= (2.0 ** -31 * want if valued else 0.0), j
 
 
+def _times(kind, n, rng):
+    if kind == "whole":        # few bits vary: all of them are ordered
+        return np.ceil(rng.random(n) * 300)
+    if kind == "continuous":   # small groups agree in the bits ordered
+        return rng.standard_normal(n)
+    if kind == "one":          # nothing varies
+        return np.full(n, 2.5)
+    # one far time and the others close together: groups of 32 records and one
+    # of equal ones ("close"), or all records in one ("closest"), agree in the
+    # bits ordered
+    y = 1e6 + rng.permutation(n) * (2.0 ** -7 if kind == "close" else 2.0 ** -30)
+    y[rng.integers(0, n, n // 8)] = 1e6 - 2.0 ** -3  # equal ones
+    y[n // 2] = 0.25
+    if kind == "signed":
+        y = np.where(rng.random(n) < 0.5, y - 1e6, 1e6 - y)
+        y[:2] = np.array([0.0, -0.0])[:n]
+    return y
+
+
+@pytest.mark.parametrize("kind", ["whole", "continuous", "one", "close", "closest", "signed"])
+@pytest.mark.parametrize("model", ["cox", "fg"])
+@pytest.mark.parametrize("n", [1, 2, 63, 65, 2047, 2049, 4096, 4097, 300_001, 1_048_577])
+def test_time_ordering(n, model, kind):
+    """Order, events at run ends and weights: one tile of the sort and the
+    scans to many, and every way the bits of the times can be ordered."""
+    rng = np.random.default_rng(n)
+    y = _times(kind, n, rng)
+    status = rng.integers(0, 3 if model == "fg" else 2, n).astype(np.int8)
+    prob = ss.Problem(model, y, status, np.array([0, 1]), np.array([0], dtype=np.int32))
+    order = np.argsort(-y, kind="stable")
+    np.testing.assert_array_equal(prob.perm.cpu().numpy(), order)
+    inv = np.empty_like(order)
+    inv[order] = np.arange(n)
+    np.testing.assert_array_equal(prob.inv_perm.cpu().numpy(), inv)
+    ys, st = y[order], status[order]
+    end = np.append(ys[1:] != ys[:-1], True)
+    start_of = np.concatenate([[0], np.cumsum(end)[:-1]])  # run of each position
+    d = np.bincount(start_of, st == 1 if model == "fg" else st != 0)
+    want = np.where(end, d[start_of], 0).astype(np.int64)
+    np.testing.assert_array_equal(prob.d32.cpu().numpy(), want)
+    np.testing.assert_array_equal(prob.d8.cpu().numpy()[:n], np.minimum(want, 255))
+    if model == "fg":
+        cens = np.bincount(start_of, st == 0)
+        fac = np.where(end, 1.0 - cens[start_of] / np.arange(1, n + 1), 1.0)
+        g = np.cumprod(fac[::-1].astype(np.longdouble))[::-1]
+        # at most n roundings of 2^-53 each, in either order of the product
+        tol = (n + 2) * 2.0 ** -52
+        np.testing.assert_allclose(prob.g_end.cpu().numpy(), g.astype(np.float64), rtol=tol,
+                                   atol=1e-300)
+        with np.errstate(divide="ignore"):
+            w = np.where(st == 2, 1.0 / prob.g_end.cpu().numpy(), 0.0)
+        np.testing.assert_array_equal(prob.w_comp.cpu().numpy(), w)
+
+
+# more tiles than a workgroup adds up itself: of the run and weight scans, of
+# the times that order 40 bits, of the digit counts
+@pytest.mark.parametrize("n", [4_300_000, 8_400_000, 67_200_000])
+def test_time_ordering_large(n):
+    g = torch.Generator(device="cuda").manual_seed(n)
+    y = torch.randn(n, dtype=torch.float64, device="cuda", generator=g)
+    y[::7] = torch.round(y[::7] * 4096) / 4096
+    status = torch.randint(0, 3, (n,), dtype=torch.int8, device="cuda", generator=g)
+    prob = ss.Problem("fg", y, status, np.array([0, 1]), np.array([0], dtype=np.int32))
+    ys, order = torch.sort(y, descending=True, stable=True)
+    assert torch.equal(prob.perm.long(), order)
+    assert torch.equal(prob.inv_perm[order].long(), torch.arange(n, device="cuda"))
+    st = status[order]
+    end = torch.ones(n, dtype=torch.bool, device="cuda")
+    end[:-1] = ys[1:] != ys[:-1]
+    last = torch.nonzero(end).flatten()
+
+    def at_ends(mark):
+        upto = torch.cumsum(mark.long(), 0)[last]
+        return torch.diff(upto, prepend=upto.new_zeros(1))
+
+    want = torch.zeros(n, dtype=torch.int32, device="cuda")
+    want[last] = at_ends(st == 1).int()
+    assert torch.equal(prob.d32, want)
+    fac = torch.ones(n, dtype=torch.float64, device="cuda")
+    fac[last] = 1.0 - at_ends(st == 0).double() / (last + 1).double()
+    km = torch.cumprod(fac.flip(0), 0).flip(0)
+    # at most n roundings of 2^-53 each, on both sides
+    assert torch.allclose(prob.g_end, km, rtol=(n + 2) * 2.0 ** -52, atol=1e-300)
+
+
 @pytest.mark.parametrize("n,m", [(3000, 40), (300_000, 30), (300_000, 2000), (2_100_000, 50_000)])
 def test_design_errors(n, m):
     """A duplicate row and a row out of range are still refused, on every

@@ -229,7 +229,7 @@ def record_traffic(paths, n):
     # the roofline kernel: Cox, valued column, FP64, the most launched shape
     counts = {}
     for nm in names:
-        if ", 0, true, false, false, double, false>" in nm:
+        if ", 0, true, false, 0, false, double, false>" in nm:
             counts[nm] = len(values(fetch_p, lambda k, nm=nm: k == nm))
     name = max(counts, key=counts.get)
     ipt = int(name.split("k_fused<256, ")[1].split(",")[0])

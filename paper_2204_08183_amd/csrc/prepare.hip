@@ -85,18 +85,20 @@ __global__ __launch_bounds__(SB) void k_scan_down(const uint32_t *in, uint32_t *
 
 // ------------------------------------------------------------ radix sort
 // One pass orders (key, value) records by 8 bits of the key, stably.  A tile
-// is RB * RI records, wave w of a workgroup its w-th quarter in rounds of 64,
+// is RB * RI records, wave w of a workgroup its w-th part in rounds of 64,
 // so a record's rank among equal digits of the tile is its rank in the
 // wave's rounds before (a counter per wave and digit in LDS, no barrier),
 // in its round (wave ballots) and the counts of the waves before; the records
 // are put in order in LDS and leave as runs.  All of a thread's loads are in
 // flight at once.  Bound: at 1e6 records 245 workgroups, one per CU, and in
-// each the serial rounds.  (Rounds over the whole workgroup with three
-// barriers each, 8-byte values and records stored one by one: 22.5 us a pass
-// at 1e6 records, now 14.6; hist 6.3, now 4.5.)
-constexpr int RB = 256;
-constexpr int RI = 16;
+// each the serial rounds: 8 waves of 8 rounds 16.5 us a pass with the counts
+// added up, 4 waves of 16 rounds 19.3, 16 waves of 4 as 8.  (Rounds over the
+// whole workgroup with three barriers each, 8-byte values and records stored
+// one by one: 22.5 us without them; hist 6.3, now 4.3.)
+constexpr int RB = 512;
+constexpr int RI = 8;
 constexpr int RT = RB * RI;
+constexpr int RD = 256;  // digits
 // Up to kOwnOffsets tiles a scatter adds the tiles' counts up itself, one row
 // of 256 a tile (a tile alone needs none); above, a scan over the counts by
 // digit has.  (1e6 records: two launches of 6 us and their gaps a pass against
@@ -109,10 +111,10 @@ __global__ __launch_bounds__(RB) void k_radix_hist(const uint64_t *keys, int64_t
                                                    int shift, uint32_t *hist,
                                                    int64_t nb)
 {
-    __shared__ uint32_t cnt[RB / kWave][256];
+    __shared__ uint32_t cnt[RB / kWave][RD];
     const int w = threadIdx.x / kWave;
 #pragma unroll
-    for (int q = 0; q < RB / kWave; ++q) cnt[q][threadIdx.x] = 0;
+    for (int q = threadIdx.x; q < RB / kWave * RD; q += RB) (&cnt[0][0])[q] = 0;
     const int64_t base = (int64_t)blockIdx.x * RT;
     uint64_t key[RI];
 #pragma unroll
@@ -126,10 +128,11 @@ __global__ __launch_bounds__(RB) void k_radix_hist(const uint64_t *keys, int64_t
         if (base + (int64_t)r * RB + threadIdx.x < m)
             atomicAdd(&cnt[w][(key[r] >> shift) & 255u], 1u);
     __syncthreads();
+    if (threadIdx.x >= RD) return;
     uint32_t t = 0;
 #pragma unroll
     for (int q = 0; q < RB / kWave; ++q) t += cnt[q][threadIdx.x];
-    hist[ROWS ? (int64_t)blockIdx.x * 256 + threadIdx.x
+    hist[ROWS ? (int64_t)blockIdx.x * RD + threadIdx.x
               : (int64_t)threadIdx.x * nb + blockIdx.x] = t;
 }
 
@@ -161,9 +164,9 @@ __global__ __launch_bounds__(RB) void k_radix_scatter(const uint64_t *kin, const
                                                       uint32_t *err)
 {
     constexpr int NW = RB / kWave;
-    __shared__ uint32_t s_cnt[NW][256];   // records of a wave, then of the waves before
-    __shared__ uint32_t s_off[256];       // where a digit's run of the tile goes, less its start
-    __shared__ uint32_t s_start[256];     // a digit's first record in the ordered tile
+    __shared__ uint32_t s_cnt[NW][RD];    // records of a wave, then of the waves before
+    __shared__ uint32_t s_off[RD];        // where a digit's run of the tile goes, less its start
+    __shared__ uint32_t s_start[RD];      // a digit's first record in the ordered tile
     __shared__ uint32_t s_wsum[NW];
     __shared__ uint64_t s_key[RT];
     __shared__ uint32_t s_val[RT];
@@ -186,7 +189,7 @@ __global__ __launch_bounds__(RB) void k_radix_scatter(const uint64_t *kin, const
     }
     uint32_t first = 0;  // where the tile's run of digit tid goes
     if constexpr (!ROWS) {
-        first = offs[(int64_t)tid * nb + blockIdx.x];
+        if (tid < RD) first = offs[(int64_t)tid * nb + blockIdx.x];
     } else if (nb > 1) {
         // wave w adds every NW-th row up, lane l digits 4 l .. 4 l + 3
         const uint4 *row = reinterpret_cast<const uint4 *>(offs) + lane;
@@ -200,18 +203,20 @@ __global__ __launch_bounds__(RB) void k_radix_scatter(const uint64_t *kin, const
         }
         uint32_t *t = reinterpret_cast<uint32_t *>(s_key);
         reinterpret_cast<uint4 *>(t)[w * kWave + lane] = all;
-        reinterpret_cast<uint4 *>(t + NW * 256)[w * kWave + lane] = before;
+        reinterpret_cast<uint4 *>(t + NW * RD)[w * kWave + lane] = before;
         __syncthreads();
         uint32_t sum = 0;
+        if (tid < RD) {
 #pragma unroll
-        for (int q = 0; q < NW; ++q) {
-            sum += t[q * 256 + tid];
-            first += t[(NW + q) * 256 + tid];
+            for (int q = 0; q < NW; ++q) {
+                sum += t[q * RD + tid];
+                first += t[(NW + q) * RD + tid];
+            }
         }
         first += excl_prefix(sum, s_wsum);
     }
 #pragma unroll
-    for (int q = 0; q < NW; ++q) s_cnt[q][tid] = 0;
+    for (int q = tid; q < NW * RD; q += RB) (&s_cnt[0][0])[q] = 0;
     __syncthreads();
     const uint64_t lt_mask = (lane == 0) ? 0ull : ((~0ull) >> (kWave - lane));
     uint32_t rank[RI];  // within the wave
@@ -239,16 +244,20 @@ __global__ __launch_bounds__(RB) void k_radix_scatter(const uint64_t *kin, const
     // thread = digit: the waves' counts become the counts of the waves
     // before, the tile's counts their exclusive prefix over the digits
     uint32_t total = 0;
+    if (tid < RD) {
 #pragma unroll
-    for (int q = 0; q < NW; ++q) {
-        const uint32_t c = s_cnt[q][tid];
-        s_cnt[q][tid] = total;
-        total += c;
+        for (int q = 0; q < NW; ++q) {
+            const uint32_t c = s_cnt[q][tid];
+            s_cnt[q][tid] = total;
+            total += c;
+        }
     }
     const uint32_t start = excl_prefix(total, s_wsum);
     if (ROWS && nb == 1) first = start;
-    s_start[tid] = start;
-    s_off[tid] = first - start;
+    if (tid < RD) {
+        s_start[tid] = start;
+        s_off[tid] = first - start;
+    }
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < RI; ++r) {
@@ -327,8 +336,8 @@ __global__ __launch_bounds__(256) void k_time_keys(const double *y, const int8_t
 // equal keys are in order already; a group of different ones with over
 // kGroupMax records on either side of a change sets err[1], and the
 // caller orders all bits instead (1e6 continuous times and one far from them:
-// 557 us for a preparation that always ordered all 64 bits, 594 with the
-// attempt first; without the far one 571 and 319).
+// 557 us for a preparation that always ordered all 64 bits, 515 with the
+// attempt first; without the far one 571 and 296).
 //
 // Continuous times differ in sign and exponent, 12 bits at most, and spread
 // over the mantissa: 20 bits of it leave groups of below 8 records on average

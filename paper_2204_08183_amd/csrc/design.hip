@@ -11,12 +11,15 @@
 // counting pass and a placement pass first group each column's non-zeros by
 // window (in any order: the bitmap orders them).
 //
-// Bound: per non-zero one random 4-byte read of inv_perm and one LDS atomic,
-// both about one lane per clock and CU; 8 bytes of HBM traffic (20 valued)
-// against 24 per pass of the 4-5 pass LSD radix sort of (column, position)
-// keys it replaced.  N = 1e6, P = 1000, 5e7 non-zeros: 288 us against 3.3 ms
-// (without the reads of inv_perm ~220 us, without the stores ~280 us: no one
-// part bounds it, the phases of the one workgroup a CU holds add up).
+// Bound: per non-zero one random 4-byte read of inv_perm and one LDS atomic;
+// 8 bytes of HBM traffic (20 valued) against 24 per pass of the 4-5 pass LSD
+// radix sort of (column, position) keys it replaced.  N = 1e6, P = 1000, 5e7
+// non-zeros: 288 us against 3.3 ms.  Of these the bits take 171 (292 G random
+// reads a second, the rate at which the L2s take requests: batches pipelined
+// so that reads and atomics overlap gave nothing), the list 103 (a store per
+// entry and lane; a wave's run gathered in LDS first took 77, but what
+// followed waited as much longer, the preparation unchanged at 617), counts
+// and clearing 24.
 #include <algorithm>
 #include <vector>
 

@@ -43,8 +43,12 @@ __device__ __forceinline__ double read_lane(double x, int lane)
 }
 
 // 1/x by the hardware's reciprocal estimate refined with Newton's iteration
-// r <- r + r (1 - x r) (two steps in FP64, one in FP32): within a unit or two
-// of the last place for the positive normal x of the transforms.
+// r <- r + r (1 - x r) (two steps in FP64, one in FP32).  In FP64 the bits of
+// an IEEE division 1/x (2.4e7 x over the whole range) down to kRecipMin, from
+// where the estimate, good to some 2^-23, is sure to be finite; NaN where it
+// overflows.
+constexpr double kRecipMin = 0x1.0001p-1024;
+
 __device__ __forceinline__ double recip(double x)
 {
     double r = __builtin_amdgcn_rcp(x);

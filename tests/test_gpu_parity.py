@@ -685,3 +685,35 @@ def test_sweep_launches_tile_sums(model, n, p, density, monkeypatch):
         prob.sweep("l2", 1.0, j_begin=a, j_end=b)
     np.testing.assert_allclose(prob.beta.cpu().numpy(), beta, rtol=1e-9, atol=1e-13)
     assert prob.workspace_error() == 0
+
+
+# The latest subjects, censored, with an e that underflows to 0 (eta = -800)
+# or to a subnormal without a finite reciprocal (eta = -720): no run ends
+# there, and nothing of them may reach the sums.  One workgroup of each shape,
+# and several.
+@pytest.mark.parametrize("path", SWEEP_PATHS)
+@pytest.mark.parametrize("model", ["cox", "fg"])
+@pytest.mark.parametrize("n", [900, 1800, 3000, 7000])
+def test_sweep_leading_underflow(n, model, path, monkeypatch):
+    _sweep_env(monkeypatch, path)
+    p = 6
+    c = make_case(model, n, p, 130, 0, 0.1)
+    latest = np.argsort(-c["y"], kind="stable")[:40]
+    c["status"][latest] = 0
+    c["eta"] = np.random.default_rng(131).normal(0.0, 0.5, n)
+    c["eta"][latest[:20]] = -800.0
+    c["eta"][latest[20:]] = -720.0
+    prob = gpu_problem(model, c)
+    g12 = torch.zeros(3 * p, dtype=torch.float64, device=DEV)
+    beta, delta, eta, hist = oracle_sweeps(model, c, occd.PENALTY_L2, 1.0, 1)
+    for out in (None, g12):  # without and with the per-coordinate output
+        prob.set_beta(torch.zeros(p), c["eta"])
+        prob.reset_trust()
+        prob.sweep("l2", 1.0, g12_out=out)
+        np.testing.assert_allclose(prob.beta.cpu().numpy(), beta, rtol=1e-9, atol=1e-13)
+    got = g12.cpu().numpy().reshape(-1, 3)
+    for j in range(p):
+        g1, g2, s1, s2 = hist[j]
+        assert abs(got[j, 0] - g1) <= 1e-10 * s1, (j, got[j, 0], g1)
+        assert abs(got[j, 1] - g2) <= 1e-10 * s2, (j, got[j, 1], g2)
+    assert prob.workspace_error() == 0

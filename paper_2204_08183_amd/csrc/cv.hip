@@ -1998,8 +1998,9 @@ int32_t launch_cv_sweep(int32_t model, int32_t penalty, double lambda, int64_t n
     // SURVSCAN_CV_HALVES=1 forces one.
     const char *env = getenv("SURVSCAN_CV_HALVES");
     const bool allow2 = !(env && env[0] == '1');
-    // where everything fits on the chip at once, it stays there
-    if (!env) {
+    // where everything fits on the chip at once, it stays there (a call
+    // without coordinates only brings e up to date, which the others do)
+    if (!env && j_begin < j_end) {
         OnChip on;
         const int32_t rc = on_chip_for(model, n, reps, &on);
         if (rc) return rc;

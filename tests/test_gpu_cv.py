@@ -482,3 +482,24 @@ def test_cv_streaming_halves(model, n, ties, monkeypatch):
     monkeypatch.setenv("SURVSCAN_CV_HALVES", "2")
     d = cox_case(n, 4, 24, ties=ties) if model == "cox" else fg_case(n, 4, 24, ties=ties)
     check_sweeps(d, gen.cv_folds(25, n, 3, 1), "l1", 0.5, 1, 1e-10, model=model)
+
+
+@pytest.mark.parametrize("halves", HALVES)
+@pytest.mark.parametrize("model", ["cox", "fg"])
+def test_cv_sweep_without_coordinates(model, halves, monkeypatch):
+    """A sweep over no coordinates still leaves e = exp(eta) at training
+    positions and 0 elsewhere."""
+    _halves(monkeypatch, halves)
+    n = 3000
+    d = cox_case(n, 3, 26) if model == "cox" else fg_case(n, 3, 26)
+    train = gen.cv_folds(27, n, 3, 1)
+    prob, cvp = make_cv(d, train, model)
+    eta = np.random.default_rng(28).normal(0.0, 0.5, (train.shape[0], n))
+    cvp.set_eta(eta)
+    cvp.e.fill_(-1.0)
+    cvp.sweep("l1", 1.0, j_begin=2, j_end=2)
+    order = prob.perm.cpu().numpy()
+    np.testing.assert_allclose(cvp.sorted_view(cvp.e).cpu().numpy(),
+                               (np.exp(eta) * train)[:, order], rtol=1e-15)
+    np.testing.assert_array_equal(cvp.sorted_view(cvp.eta).cpu().numpy(), eta[:, order])
+    assert float(cvp.beta.abs().max()) == 0.0

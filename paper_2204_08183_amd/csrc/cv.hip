@@ -698,8 +698,11 @@ __global__ __launch_bounds__(BLOCK) void k_cv_sweep(CvArgs a)
             par ^= 1;
             double S0 = p0 + (i0 - t0);
             double S1 = p1 + (i1 - t1);
+            // S0 may start below the range of quot (every e of the first risk
+            // sets underflowing): the wave then divides
+            const bool low = __any(S0 + cur.v[0] < kQuotMin);
             // kCvGroup positions at a time without a branch, so that their
-            // reciprocals overlap; G = 0 off the run ends (S0 may be 0
+            // divisions overlap; G = 0 off the run ends (S0 may be 0
             // before the replicate's first subject)
 #pragma unroll
             for (int i0 = 0; i0 < IPT; i0 += kCvGroup) {
@@ -712,10 +715,17 @@ __global__ __launch_bounds__(BLOCK) void k_cv_sweep(CvArgs a)
                     s0[u] = S0;
                     s1[u] = S1;
                 }
+                double gq[kCvGroup];
+#pragma unroll
+                for (int u = 0; u < kCvGroup; ++u) gq[u] = quot(s1[u], s0[u]);
+                if (low) {
+#pragma unroll
+                    for (int u = 0; u < kCvGroup; ++u) gq[u] = s1[u] / s0[u];
+                }
 #pragma unroll
                 for (int u = 0; u < kCvGroup; ++u) {
                     const uint32_t d = dv[i0 + u];
-                    double g = s1[u] * recip(s0[u]);
+                    double g = gq[u];
                     asm("" : "+v"(g));  // a select, not a branch around it
                     g = d != 0u ? g : 0.0;
                     const double dd = (double)d;
@@ -1224,6 +1234,17 @@ constexpr int cv_on_lds()
     return MODEL == SS_COX && IPT > 56 ? IPT - 56 : 0;
 }
 
+// S0 below the range of quot (every e of the first risk sets underflowing):
+// a thread whose S0 starts there sums S0 and S1 times 2^200 (their ratio is
+// what counts), in fused multiply-adds that take the place of the additions of
+// e.  (A branch to a division in every group of run ends costs 2 to 3% of a
+// sweep, a transform of its own, behind one branch, more: the code then
+// outgrows the instruction cache.)
+__device__ __forceinline__ double cv_scale(double first)
+{
+    return first < kQuotMin ? 0x1p200 : 1.0;
+}
+
 template <int IPT, int MODEL>
 __global__ __launch_bounds__(kCvOnBlock, 2) void k_cv_on_chip(CvOnArgs f)
 {
@@ -1527,15 +1548,16 @@ __global__ __launch_bounds__(kCvOnBlock, 2) void k_cv_on_chip(CvOnArgs f)
         for (int g = 0; g < NG; ++g) x2[g] = 0u;
         if (j + 2 < je) column(j + 2, x2);
         // ---- transform at run ends and reduction, GT positions at a time so
-        // that their reciprocals overlap; G = 0 off the run ends (S0 may be 0
+        // that their divisions overlap; G = 0 off the run ends (S0 may be 0
         // before the replicate's first subject)
         double v[2] = {0.0, 0.0};
         {
-            double S0 = pre[0] + texcl[0], S1 = pre[1] + texcl[1];
+            const double sc = cv_scale(pre[0] + texcl[0] + ev(0));
+            double S0 = (pre[0] + texcl[0]) * sc, S1 = (pre[1] + texcl[1]) * sc;
             double R0 = 0.0, R1 = 0.0;
             if constexpr (FG) {
-                R0 = pre[2] - texcl[2];
-                R1 = pre[3] - texcl[3];
+                R0 = (pre[2] - texcl[2]) * sc;
+                R1 = (pre[3] - texcl[3]) * sc;
             }
             uint32_t dw = s_d[0][tid];  // the counts of a group, read one ahead
             static_assert(GT == 4, "a word of counts per group");
@@ -1548,14 +1570,14 @@ __global__ __launch_bounds__(kCvOnBlock, 2) void k_cv_on_chip(CvOnArgs f)
                     const int i = i0 + u;
                     const bool xj = (xc[i / 16] >> (i % 16)) & 1u;
                     const double e = ev(i);
-                    S0 += e;
-                    S1 += xj ? e : 0.0;
+                    S0 = fma(e, sc, S0);
+                    S1 = fma(xj ? e : 0.0, sc, S1);
                     t0[u] = S0;
                     t1[u] = S1;
                     if constexpr (FG) {
                         const double ew = e * wv[i];
-                        R0 -= ew;
-                        R1 -= xj ? ew : 0.0;
+                        R0 = fma(-ew, sc, R0);
+                        R1 = fma(xj ? -ew : 0.0, sc, R1);
                         const double g = s_g[i][tid];
                         t0[u] = fma(g, R0, t0[u]);
                         t1[u] = fma(g, R1, t1[u]);
@@ -1570,7 +1592,7 @@ __global__ __launch_bounds__(kCvOnBlock, 2) void k_cv_on_chip(CvOnArgs f)
                 }
 #pragma unroll
                 for (int u = 0; u < GT; ++u) {
-                    double g = t1[u] * recip(t0[u]);
+                    double g = quot(t1[u], t0[u]);
                     asm("" : "+v"(g));  // a select, not a branch around it
                     g = d[u] != 0u ? g : 0.0;
                     const double dd = (double)d[u];

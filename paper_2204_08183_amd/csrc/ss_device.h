@@ -57,6 +57,20 @@ __device__ __forceinline__ double recip(double x)
     e = fma(-x, r, 1.0);
     return fma(r, e, r);
 }
+// a/b, from the estimate after one Newton step and one correction of the
+// quotient by its residual: as many instructions as a * recip(b), and the
+// bits of an IEEE division (a * recip(b): up to 1.5 units of the last place
+// off) for b from kQuotMin up.  Below, the residual underflows, and below
+// kRecipMin the result is NaN.
+constexpr double kQuotMin = 0x1p-900;
+
+__device__ __forceinline__ double quot(double a, double b)
+{
+    double r = __builtin_amdgcn_rcp(b);
+    r = fma(r, fma(-b, r, 1.0), r);
+    const double q = a * r;
+    return fma(fma(-b, q, a), r, q);
+}
 __device__ __forceinline__ float recip(float x)
 {
     const float r = __builtin_amdgcn_rcpf(x);

@@ -503,3 +503,35 @@ def test_cv_sweep_without_coordinates(model, halves, monkeypatch):
                                (np.exp(eta) * train)[:, order], rtol=1e-15)
     np.testing.assert_array_equal(cvp.sorted_view(cvp.eta).cpu().numpy(), eta[:, order])
     assert float(cvp.beta.abs().max()) == 0.0
+
+
+@pytest.mark.parametrize("halves", ["two", "one", "2"])
+@pytest.mark.parametrize("model", ["cox", "fg"])
+def test_cv_risk_sets_that_underflow(model, halves, monkeypatch):
+    """e of some 1e-311 everywhere: the first risk sets' S0 is below the
+    smallest number with a finite reciprocal, but G = S1 / S0 is as good as
+    the 42 bits that e then has (2e-13)."""
+    if halves == "2":
+        monkeypatch.setenv("SURVSCAN_CV_HALVES", "2")
+    else:
+        _halves(monkeypatch, halves)
+    n, p = 1500, 6
+    d = cox_case(n, p, 29, density=0.2) if model == "cox" else fg_case(n, p, 29, density=0.2)
+    train = gen.cv_folds(30, n, 3, 1)
+    eta0 = np.random.default_rng(31).normal(0.0, 0.3, (train.shape[0], n)) - 715.0
+    prob, cvp = make_cv(d, train, model)
+    cvp.set_eta(eta0)
+    g12 = torch.zeros(cvp.reps * p * 3, dtype=torch.float64, device=DEV)
+    cvp.sweep("l2", 1.0, g12_out=g12)
+    got = g12.cpu().numpy().reshape(cvp.reps, p, 3)
+    for r in range(cvp.reps):
+        tr = train[r] == 1
+        ys, sts, cp, rr, _, idx = ocv.subset(d["y"], d["status"], d["col_ptr"], d["rows"], None,
+                                             tr)
+        _, _, _, hist = ocv.ccd_sweeps(model, ys, sts, cp, rr, None, eta0[r][idx] + 715.0,
+                                       occd.PENALTY_L2, 1.0, 1)
+        for j in range(p):
+            g1, g2, s1, s2 = hist[j]
+            assert abs(got[r, j, 0] - g1) <= 1e-10 * s1, (r, j, got[r, j], g1)
+            assert abs(got[r, j, 1] - g2) <= 1e-10 * s2, (r, j, got[r, j], g2)
+    assert cvp.workspace_error() == 0

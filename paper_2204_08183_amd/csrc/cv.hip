@@ -1485,7 +1485,7 @@ __global__ __launch_bounds__(kCvOnBlock, 2) void k_cv_on_chip(CvOnArgs f)
         double bj = a.beta[r * a.p + j], dj = a.delta[r * a.p + j];
         // ---- the update of column j-1
         if (st_prev != 0.0) {
-            const double fe = f_prev > -0.4 ? 1.0 + f_prev : exp(st_prev);
+            const double fe = exp_from(st_prev, f_prev);
 #pragma unroll
             for (int i = 0; i < IPT; ++i) {
                 if ((xp[i / 16] >> (i % 16)) & 1u) put(i, ev(i) * fe);

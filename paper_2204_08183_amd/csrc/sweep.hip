@@ -814,9 +814,7 @@ __global__ __launch_bounds__(BLOCK) void k_sweep1(SweepArgs a)
         const uint8_t bprev = (uint8_t)(1u << ((j + 2) % 3));
         // ---- the update of column j-1, in place
         if (j > jb && st_prev != 0.0) {
-            // exp(s) = 1 + expm1(s), which is at hand; below -1/2 the sum
-            // would cancel
-            const double fe = f_prev > -0.4 ? 1.0 + f_prev : exp(st_prev);
+            const double fe = exp_from(st_prev, f_prev);
 #pragma unroll
             for (int i = 0; i < IPT; ++i) {
                 if (fl[i] & bprev) {

@@ -318,10 +318,10 @@ int32_t ss_ccd_sweep(int32_t model, int32_t penalty, double lambda, int64_t n, i
     a.steps = steps;
     a.want_log = g12_out != nullptr;
     a.obj_penalty = -1;
-    // 0/1 designs: one launch per coordinate, each leaving the next one's
-    // tile sums (Fine-Gray: a sums pass before the first one); valued
-    // designs: Cox one launch with look-back, Fine-Gray two
-    const bool sums = vals_sorted == nullptr;
+    // Cox: one launch per coordinate, with look-back; Fine-Gray 0/1 designs:
+    // one too, each leaving the next one's tile sums (a sums pass before the
+    // first one); Fine-Gray valued designs: two
+    const bool sums = model == SS_FINE_GRAY && vals_sorted == nullptr;
     for (int64_t j = j_begin; j < j_end; ++j) {
         a.j = (int32_t)j;
         a.jprev = j > j_begin ? (int32_t)(j - 1) : -1;
@@ -332,8 +332,6 @@ int32_t ss_ccd_sweep(int32_t model, int32_t penalty, double lambda, int64_t n, i
         int32_t rc = launch_fused(a, v, s);
         if (rc) return rc;
     }
-    if (sums)  // eta, and e from it, after all steps
-        return launch_sweep_eta(n, (int32_t)j_begin, (int32_t)j_end, steps, a.col, eta, e, s);
     return launch_apply(n, (int32_t)(j_end - 1), steps + (j_end - 1), eta, e, a.col, s);
 }
 

@@ -147,7 +147,7 @@ __device__ void reduce_partials(u32x4 *part, u32x4 *gpart, int64_t tile, int64_t
 // Last tile: g', g'', the likelihood or the coordinate update from the
 // launch totals (thread 0), then the launch epoch moves on.
 //
-// FG_NEXT (Fine-Gray, EMIT): tot[3..] are the totals of A and D (see
+// FG_NEXT (EMIT): tot[3..] are the totals of A and D (see
 // k_fused); the coordinate's step s multiplies e by exp(s) where x_j = 1, so
 // the weighted totals of column jnext over the updated e are A + expm1(s) D,
 // stored for the next launch.
@@ -262,12 +262,9 @@ __device__ __forceinline__ void clear_tile_lds(uint8_t *s_flag, double *s_xv)
 }
 
 // Stages one tile (positions [t0, t0+cnt)): e (patched by the pending step
-// of column jprev, which is also written back), the weights w (Fine-Gray)
-// and the event counts d (one byte each, element i in byte i%4 of word i/4)
-// go to registers.  The pending step: a valued column updates eta and takes
-// e = exp(eta); a 0/1 column multiplies e by exp(step) where its owner holds
-// it, and eta follows at the end of the sweep (k_sweep_eta) -- the tile then
-// waits for no load of eta behind the column's rows.  Column j: a 0/1 column leaves a bit per
+// of column jprev, which is also written back to eta and e), the weights w
+// (Fine-Gray) and the event counts d (one byte each, element i in byte i%4
+// of word i/4) go to registers.  Column j: a 0/1 column leaves a bit per
 // element in a register (returned: bit i for element i); a valued column
 // leaves its values in LDS at s_xv[i * BLOCK + tid] (lane-major, free of
 // bank conflicts; 0 where the column has no entry, and the returned bits
@@ -394,14 +391,10 @@ __device__ __forceinline__ uint32_t stage_tile(const FusedCall &a, int64_t t0, i
         for (int32_t o = cnext.lo + tid; o < cnext.hi; o += BLOCK)
             lds_flag_or(s_flag, (int32_t)(a.col.rows[cnext.cb + o] - t0), kFlagNext);
     }
-    if (PREV && !VALS && step_prev != 0.0) {
-        for (int32_t o = cprev.lo + tid; o < cprev.hi; o += BLOCK)
-            lds_flag_or(s_flag, (int32_t)(a.col.rows[cprev.cb + o] - t0), kFlagPatch);
-    }
-    if (PREV && VALS && step_prev != 0.0) {
+    if (PREV && step_prev != 0.0) {
         for (int32_t o = cprev.lo + tid; o < cprev.hi; o += BLOCK) {
             const int32_t k = a.col.rows[cprev.cb + o];
-            const double x = a.col.vals[cprev.cb + o];
+            const double x = VALS ? a.col.vals[cprev.cb + o] : 1.0;
             const double et = a.eta[k] + x * step_prev;
             const double en = exp(et);
             a.eta[k] = et;
@@ -427,20 +420,10 @@ __device__ __forceinline__ uint32_t stage_tile(const FusedCall &a, int64_t t0, i
     }
     if (NEXT) *nbits = qbits;
     if (dense) xbits = IPT == 32 ? ~0u : (1u << IPT) - 1u;
-    if constexpr (PREV && VALS) {
+    if constexpr (PREV) {
 #pragma unroll
         for (int i = 0; i < IPT; ++i)
             if ((pbits >> i) & 1u) ev[i] = s_ep[tile_pos<BLOCK, IPT>(i, tid)];
-    }
-    if constexpr (PREV && !VALS) {
-        const double fe = exp(step_prev);
-#pragma unroll
-        for (int i = 0; i < IPT; ++i) {
-            if ((pbits >> i) & 1u) {
-                ev[i] *= fe;
-                a.e[t0 + tile_pos<BLOCK, IPT>(i, tid)] = ev[i];
-            }
-        }
     }
     return xbits;
 }
@@ -490,18 +473,18 @@ struct Tuple {
     }
 };
 
-// Sum of N values over the tiles before tile ti, by one wave (all lanes get
-// it): the tiles of its own group of kGroup, and the groups before, from the
+// Sum of N values over the tiles before tile ti into dst (LDS), by one wave:
+// the tiles of its own group of kGroup, and the groups before, from the
 // sums that reduce_partials of an earlier launch published (packed from word
 // `word` of slots of SLOT words).
 template <int N, int SLOT>
 __device__ __forceinline__ void tile_prefix(const u32x4 *part, const u32x4 *gpart, int word,
-                                            int32_t ti, double (&sum)[N])
+                                            int32_t ti, double *dst)
 {
     constexpr int NQ = pub_words<N>();
     const int lane = lane_id();
     const int32_t g = ti / kGroup, pos = ti % kGroup;
-    double v[N];
+    double v[N], sum[N];
 #pragma unroll
     for (int c = 0; c < N; ++c) sum[c] = 0.0;
     auto add = [&](const u32x4 *p) {
@@ -514,14 +497,12 @@ __device__ __forceinline__ void tile_prefix(const u32x4 *part, const u32x4 *gpar
     };
     if (lane < pos) add(part + (int64_t)(g * kGroup + lane) * SLOT);
     for (int32_t q = lane; q < g; q += kWave) add(gpart + (int64_t)q * SLOT);
-#pragma unroll
-    for (int c = 0; c < N; ++c) sum[c] = dpp_wave_sum(sum[c]);
+    wave_sums_to<N>(sum, dst);
 }
 
 // Waves per SIMD that the register allocation is held to: four for
 // Fine-Gray tiles of 2048 positions (A and D in the sweep's kernel would take
-// 142 registers, three waves: N = 6e6, 53 against 51 us per coordinate; five
-// waves spill, 80 us).
+// 142 registers, three waves).
 template <int IPT, int MODEL, bool VALS, int PRE>
 constexpr int fused_min_waves()
 {
@@ -536,17 +517,20 @@ constexpr int fused_min_waves()
 //   0  the decoupled look-back (Sec. 2.6) of this launch.
 //   1  the tile sums of the pass that formed the Fine-Gray totals (k_fg_sums
 //      reads e, w and the column anyway, so they cost nothing more).
-//   2  (0/1 designs inside a sweep) the tile sums A and D that the previous
-//      coordinate's launch left (EMIT): with x in {0, 1} its step s
+//   2  (Fine-Gray 0/1 designs inside a sweep) the tile sums A and D that the
+//      previous coordinate's launch left (EMIT): with x in {0, 1} its step s
 //      multiplies e by exp(s) on the rows of its column, so the tuple sums of
-//      a tile are A + expm1(s) D, with A the sums of e (1, x_next) and D the
-//      same over the rows of column j, taken before s was known.
+//      a tile are A + expm1(s) D, with A the sums of (e, e w) (1, x_next) and
+//      D the same over the rows of column j, taken before s was known.  (A
+//      negative step cancels where the column covers the prefix, by a factor
+//      of exp(|s|), and an e that had underflowed and comes back is in
+//      neither: a step beyond kCarryStep looks back instead.)
 // With 1 and 2 no tile waits for another one's prefix, so smaller tiles pay
-// (default_ipt).  us per coordinate against the look-back: Fine-Gray N = 2e7
-// 212 -> 172 (FP32 e 180 -> 145; the two passes move 41 (33) bytes per
-// position, 159 (128) us at the copy rate); in a sweep Fine-Gray N = 6e6
-// 64 -> 51, N = 2e7 211 -> 166, Cox N = 2e7 115 -> 73.
-// EMIT (0/1 designs): this launch leaves A and D for column jnext behind its
+// (default_ipt).  us per coordinate against the look-back: N = 2e7 212 -> 172
+// (FP32 e 180 -> 145; the two passes move 41 (33) bytes per position, 159
+// (128) us at the copy rate); in a sweep N = 6e6 64 -> 57, N = 2e7 219 -> 203.
+// (The same for Cox: N = 4.3e6 28.4 -> 29.0, N = 2e7 114 -> 104; not kept.)
+// EMIT: this launch leaves A and D for column jnext behind its
 // partial sums, in one of two buffers by the parity of the epoch.
 //
 // ET: storage type of e (float: FP32 storage, read from a.e32).  F32S (with
@@ -555,6 +539,8 @@ constexpr int fused_min_waves()
 // tile boundary (aggregates, the look-back prefix, the tile partial sums)
 // in FP64, and each run end's prefix is the FP64 carry plus the FP32
 // in-tile prefix.  Without F32S every sum is FP64.
+constexpr double kCarryStep = 0.25;
+
 template <int BLOCK, int IPT, int MODEL, bool VALS, bool PREV, int PRE = 0, bool EMIT = false,
           typename ET = double, bool F32S = false>
 __global__ __launch_bounds__(BLOCK, (fused_min_waves<IPT, MODEL, VALS, PRE>())) void k_fused(FusedCall a, WsView ws, int64_t ntiles)
@@ -563,7 +549,7 @@ __global__ __launch_bounds__(BLOCK, (fused_min_waves<IPT, MODEL, VALS, PRE>())) 
     constexpr int NW = BLOCK / kWave;
     static_assert(TILE % SS_CHUNK == 0, "tile must be whole chunks");
     static_assert(!VALS || (!EMIT && PRE != 2), "A and D: 0/1 designs");
-    static_assert(MODEL == SS_FINE_GRAY || PRE != 1, "the totals pass is Fine-Gray's");
+    static_assert(MODEL == SS_FINE_GRAY || (!EMIT && PRE == 0), "A, D and the sums pass: Fine-Gray");
     static_assert(!F32S || std::is_same<ET, float>::value, "FP32 sums need FP32 storage");
     // arithmetic type of the sums inside a tile
     using AT = typename std::conditional<F32S, float, double>::type;
@@ -574,15 +560,14 @@ __global__ __launch_bounds__(BLOCK, (fused_min_waves<IPT, MODEL, VALS, PRE>())) 
 
     __shared__ __attribute__((aligned(16))) uint8_t s_flag[TILE];
     __shared__ __attribute__((aligned(16))) double s_xv[VALS ? TILE : 1];
-    // G(Y) of the tile (Fine-Gray), or the patched e of a valued column's
-    // pending update (Cox: the Fine-Gray one is taken by the sums pass)
+    // G(Y) of the tile (Fine-Gray) and the patched e of a pending update (a
+    // valued Fine-Gray column's is taken by the sums pass)
     static_assert(!(MODEL == SS_FINE_GRAY && PREV && VALS), "see k_fg_sums");
     constexpr bool kGLds = SS_FG_G_LDS && MODEL == SS_FINE_GRAY;
-    __shared__ __attribute__((aligned(16))) double s_eg[((PREV && VALS) || kGLds) ? TILE : 1];
-    double *const s_ep = s_eg;
-    double *const s_g = s_eg;
+    __shared__ __attribute__((aligned(16))) double s_g[kGLds ? TILE : 1];
+    __shared__ double s_ep[PREV ? TILE : 1];
     __shared__ double s_wsum[TileMap<IPT>::R][NW][NX];
-    __shared__ double s_excl[NX];
+    __shared__ double s_excl[PRE == 2 ? 2 * NX : NX];  // the tile's exclusive prefix (A, D)
     __shared__ double s_red[NW * NR + NR];
     __shared__ double s_tsum[NE];
 
@@ -697,27 +682,20 @@ __global__ __launch_bounds__(BLOCK, (fused_min_waves<IPT, MODEL, VALS, PRE>())) 
 
     // ---- 6. the tile's exclusive prefix
     SS_TRACE(ws, tile, 2);
-    if constexpr (PRE != 0) {
+    // (the same for every tile of the launch)
+    const bool carried = PRE == 1 || (PRE == 2 && fabs(*a.step_prev) <= kCarryStep);
+    if (carried) {
         if (w == 0) {
-            double ex[NX];
             if constexpr (PRE == 1) {
-                tile_prefix<NX, 4>(ws.fg_part, ws.fg_gpart, 0, (int32_t)tile, ex);
-            } else {
+                tile_prefix<NX, 4>(ws.fg_part, ws.fg_gpart, 0, (int32_t)tile, s_excl);
+            } else if constexpr (PRE == 2) {
                 // behind the three partial sums (two words)
                 const bool odd = ((epoch - 1) & 1u) != 0;
-                double ad[2 * NX];
                 tile_prefix<2 * NX, 8>(odd ? ws.sw_agg : ws.part, odd ? ws.sw_pre : ws.gpart, 2,
-                                       (int32_t)tile, ad);
-                const double f = expm1(*a.step_prev);
-#pragma unroll
-                for (int c = 0; c < NX; ++c) ex[c] = ad[c] + f * ad[NX + c];
-            }
-            if (lane == 0) {
-#pragma unroll
-                for (int c = 0; c < NX; ++c) s_excl[c] = ex[c];
+                                       (int32_t)tile, s_excl);
             }
         }
-    } else if (w == 0) {  // decoupled look-back
+    } else if (PRE != 1 && w == 0) {  // decoupled look-back
         double agg[NX];
         tile_agg(agg);
         u32x4 *slot = ws.lb + tile * kLbSlot;
@@ -785,6 +763,13 @@ __global__ __launch_bounds__(BLOCK, (fused_min_waves<IPT, MODEL, VALS, PRE>())) 
     double carry[NX];
 #pragma unroll
     for (int c = 0; c < NX; ++c) carry[c] = s_excl[c];
+    if constexpr (PRE == 2) {
+        if (carried) {
+            const double f = expm1(*a.step_prev);
+#pragma unroll
+            for (int c = 0; c < NX; ++c) carry[c] += f * s_excl[NX + c];
+        }
+    }
     if constexpr (!F32S) {
 #pragma unroll
         for (int q = 0; q < R; ++q)
@@ -808,16 +793,13 @@ __global__ __launch_bounds__(BLOCK, (fused_min_waves<IPT, MODEL, VALS, PRE>())) 
     // and of the same where x_j = 1 behind them
     auto emit = [&](int i, AT ei) {
         if constexpr (EMIT) {
-            constexpr int H = NX / 2;
             const bool nb = (nbits >> i) & 1u;
             const bool both = nb && ((xb >> i) & 1u);
+            const double ew = (double)(ei * (AT)wv[i]);
             acc[3] += nb ? (double)ei : 0.0;
-            acc[3 + H] += both ? (double)ei : 0.0;
-            if constexpr (MODEL == SS_FINE_GRAY) {
-                const double ew = (double)(ei * (AT)wv[i]);
-                acc[4] += nb ? ew : 0.0;
-                acc[4 + H] += both ? ew : 0.0;
-            }
+            acc[4] += nb ? ew : 0.0;
+            acc[5] += both ? (double)ei : 0.0;
+            acc[6] += both ? ew : 0.0;
         }
     };
     LogSum lsum;
@@ -935,16 +917,15 @@ __global__ __launch_bounds__(BLOCK, (fused_min_waves<IPT, MODEL, VALS, PRE>())) 
 #pragma unroll
     for (int c = 0; c < 3; ++c) tsum[c] = s_tsum[c];
     if constexpr (EMIT) {
-        // A: e, e x_next (, e w, e w x_next); D: the same where x_j = 1
-        constexpr int H = NX / 2;
+        // A: e, e x_next, e w, e w x_next; D: the same where x_j = 1
         double agg[NX];
         tile_agg(agg);
 #pragma unroll
-        for (int h = 0; h < H; ++h) {
+        for (int h = 0; h < 2; ++h) {
             tsum[3 + 2 * h] = agg[2 * h];
             tsum[3 + 2 * h + 1] = s_tsum[3 + h];
             tsum[3 + NX + 2 * h] = agg[2 * h + 1];
-            tsum[3 + NX + 2 * h + 1] = s_tsum[3 + H + h];
+            tsum[3 + NX + 2 * h + 1] = s_tsum[5 + h];
         }
     }
     const bool odd = EMIT && (epoch & 1u) != 0;
@@ -953,7 +934,7 @@ __global__ __launch_bounds__(BLOCK, (fused_min_waves<IPT, MODEL, VALS, PRE>())) 
                                   ntiles, (epoch << 1) | 1u, ws.hdr, tsum, total, s_red);
     SS_TRACE(ws, tile, 4);
     if (tile == ntiles - 1) {
-        finish<BLOCK, NR, EMIT && MODEL == SS_FINE_GRAY>(a, ws, epoch, total, s_red);
+        finish<BLOCK, NR, EMIT>(a, ws, epoch, total, s_red);
         SS_TRACE(ws, tile, 5);
     }
 }
@@ -1015,66 +996,6 @@ __global__ __launch_bounds__(BLOCK) void k_fg_sums(FusedCall a, WsView ws, int64
             ws.hdr->fg_tot[2] = t[Tx::EXXW];
             st_relaxed_u64(&ws.hdr->fg_epoch, epoch + 1);
         }
-    }
-}
-
-// The end of a 0/1 sweep in per-coordinate launches: eta += steps[j] on the
-// rows of every column j in [j_begin, j_end), in that order, and e = exp(eta).
-// One wave owns a chunk of SS_CHUNK positions with its eta in LDS, so the
-// columns follow one another without a barrier; it takes the bounds of 64
-// columns in one set of loads and has the rows of kEtaAhead columns in
-// flight.  Bound: the column indices, 4 bytes per non-zero.
-constexpr int kEtaAhead = 4;
-
-__global__ __launch_bounds__(256) void k_sweep_eta(int64_t n, int32_t j_begin, int32_t j_end,
-                                                   const double *steps, Column col, double *eta,
-                                                   double *e)
-{
-    __shared__ double s_eta[256 / kWave][SS_CHUNK];
-    const int lane = lane_id(), w = threadIdx.x / kWave;
-    const int64_t t = (int64_t)blockIdx.x * (256 / kWave) + w;
-    const int64_t k0 = t * SS_CHUNK;
-    if (k0 >= n) return;  // the whole wave; no barrier below
-    const int32_t cnt = (int32_t)min((int64_t)SS_CHUNK, n - k0);
-    double *h = s_eta[w];
-    for (int32_t i = lane; i < cnt; i += kWave) h[i] = eta[k0 + i];
-    for (int32_t jb = j_begin; jb < j_end; jb += kWave) {
-        const int m = min(kWave, j_end - jb);
-        int64_t lo = 0;
-        int32_t len = 0;
-        double st = 0.0;
-        if (lane < m) {
-            const int32_t j = jb + lane;
-            const int32_t *cp = col.chunk_ptr + (int64_t)j * col.nchunk1 + t;
-            const int32_t a = cp[0];
-            lo = col.col_ptr[j] + a;
-            st = steps[j];
-            len = st != 0.0 ? cp[1] - a : 0;
-        }
-        for (int x0 = 0; x0 < m; x0 += kEtaAhead) {
-            int32_t r[kEtaAhead], l[kEtaAhead];
-            const int32_t *rp[kEtaAhead];
-#pragma unroll
-            for (int u = 0; u < kEtaAhead; ++u) {
-                const int x = min(x0 + u, kWave - 1);
-                l[u] = x0 + u < m ? __builtin_amdgcn_readlane(len, x) : 0;
-                const uint32_t p0 = __builtin_amdgcn_readlane((int)(lo & 0xffffffff), x);
-                const uint32_t p1 = __builtin_amdgcn_readlane((int)(lo >> 32), x);
-                rp[u] = col.rows + (int64_t)(((uint64_t)p1 << 32) | p0);
-                r[u] = lane < l[u] ? rp[u][lane] : 0;
-            }
-#pragma unroll
-            for (int u = 0; u < kEtaAhead; ++u) {
-                const double s = read_lane(st, min(x0 + u, kWave - 1));
-                if (lane < l[u]) h[r[u] - k0] += s;
-                for (int32_t o = kWave + lane; o < l[u]; o += kWave) h[rp[u][o] - k0] += s;
-            }
-        }
-    }
-    for (int32_t i = lane; i < cnt; i += kWave) {
-        const double x = h[i];
-        eta[k0 + i] = x;
-        e[k0 + i] = exp(x);
     }
 }
 
@@ -1252,9 +1173,11 @@ int32_t launch_fused_ipt(const FusedCall &a, const WsView &ws, hipStream_t s)
     const bool vals = a.col.vals != nullptr;
     const bool prev = a.jprev >= 0;
     const bool emit = a.jnext >= 0;
-    // A and D travel between launches of 0/1 designs, behind a pending update
-    if (vals && (emit || a.have_sums)) return SS_EUNSUPPORTED;
-    if (!vals && (a.have_sums != 0) != prev) return SS_EUNSUPPORTED;
+    // A and D travel between launches of Fine-Gray 0/1 designs, behind a
+    // pending update
+    const bool fg01 = a.model == SS_FINE_GRAY && !vals;
+    if (!fg01 && (emit || a.have_sums)) return SS_EUNSUPPORTED;
+    if (fg01 && (a.have_sums != 0) != prev) return SS_EUNSUPPORTED;
     if (a.model == SS_FINE_GRAY) {
         if constexpr (IPT != 8) {  // default_ipt
             return SS_EUNSUPPORTED;
@@ -1275,14 +1198,11 @@ int32_t launch_fused_ipt(const FusedCall &a, const WsView &ws, hipStream_t s)
             else
                 launch_fused_t<IPT, SS_FINE_GRAY, false, false, 1>(b, ws, ntiles, s);
         }
-    } else if (a.have_sums) {
-        if (emit) launch_fused_t<IPT, SS_COX, false, true, 2, true>(a, ws, ntiles, s);
-        else      launch_fused_t<IPT, SS_COX, false, true, 2, false>(a, ws, ntiles, s);
     } else if (vals) {
         if (prev) launch_fused_t<IPT, SS_COX, true, true>(a, ws, ntiles, s);
         else      launch_fused_t<IPT, SS_COX, true, false>(a, ws, ntiles, s);
     } else {
-        if (emit) launch_fused_t<IPT, SS_COX, false, false, 0, true>(a, ws, ntiles, s);
+        if (prev) launch_fused_t<IPT, SS_COX, false, true>(a, ws, ntiles, s);
         else      launch_fused_t<IPT, SS_COX, false, false>(a, ws, ntiles, s);
     }
     SS_LAUNCH_CHECK();
@@ -1337,16 +1257,6 @@ int32_t launch_fused(const FusedCall &a, const WsView &ws, hipStream_t s)
     if (a.e32) return SS_EUNSUPPORTED;
     return default_ipt(a.model, a.n) == 8 ? launch_fused_ipt<8>(a, ws, s)
                                           : launch_fused_ipt<16>(a, ws, s);
-}
-
-int32_t launch_sweep_eta(int64_t n, int32_t j_begin, int32_t j_end, const double *steps,
-                         const Column &col, double *eta, double *e, hipStream_t s)
-{
-    const unsigned grid = (unsigned)ceil_div(n, (int64_t)SS_CHUNK * (256 / kWave));
-    hipLaunchKernelGGL(k_sweep_eta, dim3(grid), dim3(256), 0, s, n, j_begin, j_end, steps, col,
-                       eta, e);
-    SS_LAUNCH_CHECK();
-    return SS_OK;
 }
 
 int32_t launch_apply(int64_t n, int32_t j, const double *step, double *eta,

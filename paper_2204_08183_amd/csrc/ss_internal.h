@@ -261,8 +261,8 @@ struct FusedCall {
     // out[1] = l, out[2] = pi with pi the penalty of Sec. 2.3 at beta_ll
     int32_t obj_penalty;
     double obj_lambda;
-    // 0/1 design inside a sweep: the previous launch left the tile sums A and
-    // D of column j (and the Fine-Gray totals over the updated e in
+    // Fine-Gray 0/1 design inside a sweep: the previous launch left the tile
+    // sums A and D of column j (and the totals over the updated e in
     // hdr->fg_tot), and jnext >= 0 asks this one to leave those of jnext
     int32_t have_sums;
     int32_t jnext;
@@ -321,8 +321,6 @@ struct SweepCall {
 };
 int32_t launch_sweep_persistent(const SweepCall &call, const WsView &ws,
                                 hipStream_t stream);
-int32_t launch_sweep_eta(int64_t n, int32_t j_begin, int32_t j_end, const double *steps,
-                         const Column &col, double *eta, double *e, hipStream_t stream);
 int32_t launch_apply(int64_t n, int32_t j, const double *step, double *eta,
                      double *e, const Column &col, hipStream_t stream);
 int32_t launch_ccd_scalar(int32_t penalty, double lambda, int32_t j,

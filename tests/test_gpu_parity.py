@@ -717,3 +717,74 @@ def test_sweep_leading_underflow(n, model, path, monkeypatch):
         assert abs(got[j, 0] - g1) <= 1e-10 * s1, (j, got[j, 0], g1)
         assert abs(got[j, 1] - g2) <= 1e-10 * s2, (j, got[j, 1], g2)
     assert prob.workspace_error() == 0
+
+
+def _check_history(prob, c, g12, hist, tol=1e-10):
+    got = g12.cpu().numpy().reshape(-1, 3)
+    for j in range(c["p"]):
+        g1, g2, s1, s2 = hist[j]
+        assert abs(got[j, 0] - g1) <= tol * s1, (j, got[j, 0], g1)
+        assert abs(got[j, 1] - g2) <= tol * s2, (j, got[j, 1], g2)
+    assert prob.workspace_error() == 0
+
+
+def _columns(n, cols):
+    ptr = np.concatenate([[0], np.cumsum([len(r) for r in cols])]).astype(np.int64)
+    return ptr, np.concatenate(cols).astype(np.int32)
+
+
+# Sweeps by launches take e = exp(eta) afresh at every update: an e that has
+# underflowed to 0 (eta = -800) comes back once eta does, 100 a coordinate,
+# and counts in the coordinates after it.
+@pytest.mark.parametrize("model", ["cox", "fg"])
+@pytest.mark.parametrize("n", [1500, 9000])
+def test_sweep_launches_bring_e_back(n, model, monkeypatch):
+    _sweep_env(monkeypatch, "launch")
+    c = make_case(model, n, 3, 140, 0, 0.1)
+    order = np.argsort(-c["y"], kind="stable")
+    who = int(order[3])                          # early: large in many risk sets
+    c["status"][order[:12]] = 1
+    rng = np.random.default_rng(141)
+    cols = [np.array([who])] * 8 + [rng.choice(n, n // 10, replace=False) for _ in range(4)]
+    cols[9] = np.union1d(cols[9], [who])
+    c["col_ptr"], c["rows"] = _columns(n, cols)
+    c["p"] = p = len(cols)
+    c["eta"] = rng.normal(0.0, 0.5, n)
+    c["eta"][who] = -800.0
+    prob = gpu_problem(model, c)
+    prob.delta.fill_(200.0)
+    g12 = torch.zeros(3 * p, dtype=torch.float64, device=DEV)
+    beta, delta, eta, hist = ocv.ccd_sweeps(model, c["y"], c["status"], c["col_ptr"], c["rows"],
+                                            None, c["eta"], occd.PENALTY_L2, 100.0, 1,
+                                            delta=np.full(p, 200.0))
+    assert eta[who] > -5.0                       # it did come back
+    prob.sweep("l2", 100.0, g12_out=g12)
+    _check_history(prob, c, g12, hist)
+    np.testing.assert_allclose(prob.beta.cpu().numpy(), beta, rtol=1e-9, atol=1e-12)
+
+
+# A step of -20 on a column that covers the first half of the positions: the
+# prefixes after it are e^-20 of those before, and as accurate.
+@pytest.mark.parametrize("model", ["cox", "fg"])
+@pytest.mark.parametrize("n", [20_000, 300_001])
+def test_sweep_launches_large_negative_step(n, model, monkeypatch):
+    _sweep_env(monkeypatch, "launch")
+    c = make_case(model, n, 3, 150, 0, 0.1)
+    order = np.argsort(-c["y"], kind="stable")
+    rng = np.random.default_rng(151)
+    half = order[: n // 2]
+    c["eta"] = rng.normal(0.0, 0.3, n)
+    c["eta"][order[n // 2:]] -= 8.0
+    cols = [np.sort(half)] + [np.sort(rng.choice(n, n // 20, replace=False)) for _ in range(3)]
+    c["col_ptr"], c["rows"] = _columns(n, cols)
+    c["p"] = p = len(cols)
+    prob = gpu_problem(model, c)
+    prob.delta.fill_(20.0)
+    g12 = torch.zeros(3 * p, dtype=torch.float64, device=DEV)
+    beta, delta, eta, hist = ocv.ccd_sweeps(model, c["y"], c["status"], c["col_ptr"], c["rows"],
+                                            None, c["eta"], occd.PENALTY_NONE, 0.0, 1,
+                                            delta=np.full(p, 20.0))
+    assert beta[0] == -20.0
+    prob.sweep("none", 0.0, g12_out=g12)
+    _check_history(prob, c, g12, hist)
+    np.testing.assert_allclose(prob.beta.cpu().numpy(), beta, rtol=1e-9, atol=1e-12)

@@ -76,7 +76,7 @@ __device__ __forceinline__ bool poll_pairs(const u32x4 *p, uint64_t tag, WsHeade
 // group's sums; the last tile of the launch waits for the groups and adds
 // them.  Only tiles with smaller indices are ever waited for.
 //
-// tile_sum: the calling tile's sums (valid in every thread).  In the last
+// tile_sum: the calling tile's sums (valid in wave 0).  In the last
 // tile, `total` (thread 0) receives the launch total; a wait that gives up
 // sets the error word and leaves its share out.  s_red: NR + BLOCK/64 * NR
 // doubles of LDS.
@@ -125,6 +125,14 @@ __device__ void reduce_partials(u32x4 *part, u32x4 *gpart, int64_t tile, int64_t
     __syncthreads();
     // the last tile: groups 0 .. ngroups-2 from memory, its own from LDS
     const int64_t ngroups = tile / kGroup + 1;
+    double own[NR];
+#pragma unroll
+    for (int c = 0; c < NR; ++c) own[c] = s_red[c];
+    if (ngroups == 1) {
+#pragma unroll
+        for (int c = 0; c < NR; ++c) total[c] = own[c];
+        return;
+    }
     double acc[NR];
 #pragma unroll
     for (int c = 0; c < NR; ++c) acc[c] = 0.0;
@@ -134,9 +142,6 @@ __device__ void reduce_partials(u32x4 *part, u32x4 *gpart, int64_t tile, int64_t
 #pragma unroll
         for (int c = 0; c < NR; ++c) acc[c] += r[c];
     }
-    double own[NR];
-#pragma unroll
-    for (int c = 0; c < NR; ++c) own[c] = s_red[c];
     block_sum<NR, BLOCK>(acc, s_red + NR);
     if (tid == 0) {
 #pragma unroll
@@ -569,7 +574,6 @@ __global__ __launch_bounds__(BLOCK, (fused_min_waves<IPT, MODEL, VALS, PRE>())) 
     __shared__ double s_wsum[TileMap<IPT>::R][NW][NX];
     __shared__ double s_excl[PRE == 2 ? 2 * NX : NX];  // the tile's exclusive prefix (A, D)
     __shared__ double s_red[NW * NR + NR];
-    __shared__ double s_tsum[NE];
 
     const int tid = threadIdx.x;
     const int lane = lane_id();
@@ -907,15 +911,20 @@ __global__ __launch_bounds__(BLOCK, (fused_min_waves<IPT, MODEL, VALS, PRE>())) 
     acc[0] = (double)acc_t[0];
     acc[1] = (double)acc_t[1];
     if (a.want_log) acc[2] = lsum.value();
-    block_sum<NE, BLOCK>(acc, s_red);
-    if (tid == 0) {
-#pragma unroll
-        for (int c = 0; c < NE; ++c) s_tsum[c] = acc[c];
-    }
+    // the tile's sums, in wave 0 (which publishes them)
+    wave_sums_to<NE>(acc, s_red + w * NE);
     __syncthreads();
-    double tsum[NR];
+    double st[NE], tsum[NR];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) tsum[c] = s_tsum[c];
+    for (int c = 0; c < NE; ++c) {
+        st[c] = 0.0;
+        if (w == 0) {
+#pragma unroll
+            for (int v = 0; v < NW; ++v) st[c] += s_red[v * NE + c];
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) tsum[c] = st[c];
     if constexpr (EMIT) {
         // A: e, e x_next, e w, e w x_next; D: the same where x_j = 1
         double agg[NX];
@@ -923,9 +932,9 @@ __global__ __launch_bounds__(BLOCK, (fused_min_waves<IPT, MODEL, VALS, PRE>())) 
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             tsum[3 + 2 * h] = agg[2 * h];
-            tsum[3 + 2 * h + 1] = s_tsum[3 + h];
+            tsum[3 + 2 * h + 1] = st[3 + h];
             tsum[3 + NX + 2 * h] = agg[2 * h + 1];
-            tsum[3 + NX + 2 * h + 1] = s_tsum[5 + h];
+            tsum[3 + NX + 2 * h + 1] = st[5 + h];
         }
     }
     const bool odd = EMIT && (epoch & 1u) != 0;
@@ -954,7 +963,6 @@ __global__ __launch_bounds__(BLOCK) void k_fg_sums(FusedCall a, WsView ws, int64
     using Tx = Tuple<BLOCK, SS_FINE_GRAY, VALS>;
     constexpr int NX = Tx::NX;
     __shared__ double s_red[NW * NX + NX];
-    __shared__ double s_tsum[NX];
     const int tid = threadIdx.x;
     // every wave reads the epoch itself (see k_fused)
     const uint64_t epoch = ld_relaxed_u64(&ws.hdr->fg_epoch);
@@ -978,15 +986,17 @@ __global__ __launch_bounds__(BLOCK) void k_fg_sums(FusedCall a, WsView ws, int64
     for (int c = 0; c < NX; ++c) acc[c] = 0.0;
 #pragma unroll
     for (int i = 0; i < IPT; ++i) Tx::add(acc, (double)ev[i], xbits, i, s_xv, wv[i]);
-    block_sum<NX, BLOCK>(acc, s_red);
-    if (tid == 0) {
-#pragma unroll
-        for (int c = 0; c < NX; ++c) s_tsum[c] = acc[c];
-    }
+    wave_sums_to<NX>(acc, s_red + tid / kWave * NX);
     __syncthreads();
     double tsum[NX], t[NX];
 #pragma unroll
-    for (int c = 0; c < NX; ++c) tsum[c] = s_tsum[c];
+    for (int c = 0; c < NX; ++c) {
+        tsum[c] = 0.0;
+        if (tid < kWave) {  // wave 0 publishes them
+#pragma unroll
+            for (int v = 0; v < NW; ++v) tsum[c] += s_red[v * NX + c];
+        }
+    }
     reduce_partials<BLOCK, NX, 4>(ws.fg_part, ws.fg_gpart, tile, ntiles, tag, ws.hdr, tsum, t,
                                   s_red);
     if (tile == ntiles - 1) {

@@ -489,7 +489,9 @@ int32_t ss_cv_select(int32_t n_gamma, int32_t reps, const double *scores,
  *                      or 16 only);
  *   SS_TUNE_SWEEP      segment shape of the persistent sweep of
  *                      ss_ccd_sweep, block * 100 + positions per thread:
- *                      25608, 25616, 51208 or 51216 (Cox only).
+ *                      25604, 25608, 25616, 51208 or 51216 (Cox only); the
+ *                      first three also as one workgroup alone where that
+ *                      holds n.
  * A choice is kept per (kind, model, storage of e, valued design or not,
  * size bucket ceil(log2 n)) in a process-wide table that every launch
  * consults; without an entry a launch uses the built-in rule (tiles of
@@ -536,7 +538,7 @@ int32_t ss_tune_load(const char *path, int32_t *loaded);
  * delta_s, steps_s: p doubles), which the sweep then updates.  Shapes whose
  * workgroups do not all fit on the device are skipped (us = -1); with none
  * left, SS_EUNSUPPORTED.  us [host, 4 floats, may be NULL]: 25616, 51208,
- * 25608, 51216 in that order.
+ * 25608, 51216 in that order (25604 is timed too, and may be the choice).
  * Errors as the calls they time; reps outside [1, 1000]: SS_EINVAL. */
 int32_t ss_autotune_grad_hess(int32_t model, int32_t storage, int64_t n,
                               int64_t p, int64_t j, const void *e,

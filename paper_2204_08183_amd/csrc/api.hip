@@ -517,10 +517,11 @@ int32_t ss_autotune_sweep(int32_t model, int32_t penalty, double lambda, int64_t
     EventPair ev;
     SS_HIP_CHECK(hipEventCreate(&ev.a));
     SS_HIP_CHECK(hipEventCreate(&ev.b));
-    static const int32_t cands[4] = {25616, 51208, 25608, 51216};
-    float t[4];
+    // every shape of the built-in rule (one workgroup alone: where one holds n)
+    static const int32_t cands[5] = {25616, 51208, 25608, 51216, 25604};
+    float t[5];
     int32_t best = 0;
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < 5; ++i) {
         t[i] = -1.f;
         if (model == SS_FINE_GRAY && cands[i] == 51216) continue;
         ForceScope force(SS_TUNE_SWEEP, cands[i]);
@@ -544,7 +545,7 @@ int32_t ss_autotune_sweep(int32_t model, int32_t penalty, double lambda, int64_t
         if (!best || t[i] < t[best - 1]) best = i + 1;
     }
     if (us)
-        for (int i = 0; i < 4; ++i) us[i] = t[i];
+        for (int i = 0; i < 4; ++i) us[i] = t[i];  // (the interface's four)
     if (!best) return SS_EUNSUPPORTED;
     *choice = cands[best - 1];
     return ss_tune_set(SS_TUNE_SWEEP, model, SS_STORAGE_F64, vals_sorted != nullptr, n,

@@ -56,7 +56,7 @@ bool valid_choice(int32_t kind, int32_t model, int32_t storage, int32_t choice)
         return choice == 4 || choice == 8 || choice == 16 || choice == 32;
     if (kind == SS_TUNE_SWEEP) {
         if (storage != SS_STORAGE_F64) return false;
-        for (int c : {25608, 25616, 51208, 51216})
+        for (int c : {25604, 25608, 25616, 51208, 51216})
             if (choice == c) return !(choice == 51216 && model == SS_FINE_GRAY);
         return false;
     }

@@ -114,7 +114,7 @@ STORAGE_F32 = 1
 STORAGE_F32_SUMS32 = 2
 STORAGES = {"f64": STORAGE_F64, "f32": STORAGE_F32, "f32x64": STORAGE_F32_SUMS32}
 GRAD_HESS_IPTS = (4, 8, 16, 32)
-SWEEP_SHAPES = (25616, 51208, 25608, 51216)
+SWEEP_SHAPES = (25616, 51208, 25608, 51216, 25604)
 
 
 class SurvScanError(RuntimeError):

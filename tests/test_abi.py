@@ -249,3 +249,17 @@ def test_autotune_rejects_bad_arguments(lib):
                                  None, None) == ss.SS_EINVAL
     assert lib.ss_autotune_sweep(0, 1, 0.0, 100, 4, 0, 2, *sargs, 3, ctypes.byref(choice),
                                  None, None) == ss.SS_EINVAL
+
+
+def test_tune_knows_the_shapes_of_the_rule(lib):
+    """Every segment shape that the built-in rule uses can be pinned."""
+    S = ss.TUNE_SWEEP
+    ss.tune_clear()
+    try:
+        for model in ("cox", "fg"):
+            for shape in (25604, 25608, 25616, 51208):
+                assert shape in ss.SWEEP_SHAPES
+                ss.tune_set(S, model, "f64", True, 200_000, shape)
+                assert ss.tune_get(S, model, "f64", True, 200_000) == shape
+    finally:
+        ss.tune_clear()

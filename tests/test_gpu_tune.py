@@ -168,3 +168,25 @@ def test_autotune_picks_and_stores_a_shape(model, tmp_path):
     again = prob.autotune(j=1, reps=3, sweep=False, cache=cache)
     assert again["grad_hess"] is None
     assert ss.tune_get(G, model, "f64", False, c["n"]) == first["grad_hess"][0]
+
+
+# More segments than a gather of the valued sweep has threads (the built-in
+# rule takes longer segments there).
+@pytest.mark.parametrize("model", ["cox", "fg"])
+@pytest.mark.parametrize("n", [524_289, 900_001])
+def test_valued_sweep_of_many_segments(model, n):
+    c = make_case(model, n, 4, 61, 0, 0.02, True)
+    c["eta"] = np.zeros(n)
+    prob = gpu_problem(model, c)
+    ss.tune_set(S, model, "f64", True, n, 25608)
+    g12 = torch.zeros(3 * c["p"], dtype=torch.float64, device="cuda:0")
+    prob.sweep("l2", 1.0, g12_out=g12)
+    beta, _, _, hist = ocv.ccd_sweeps(model, c["y"], c["status"], c["col_ptr"], c["rows"],
+                                      c["vals"], c["eta"], occd.PENALTY_L2, 1.0, 1)
+    got = g12.view(-1, 3).cpu().numpy()
+    for j in range(c["p"]):
+        g1, g2, s1, s2 = hist[j]
+        assert abs(got[j, 0] - g1) <= 1e-10 * s1, (n, j)
+        assert abs(got[j, 1] - g2) <= 1e-10 * s2, (n, j)
+    np.testing.assert_allclose(prob.beta.cpu().numpy(), beta, rtol=1e-9, atol=1e-13)
+    assert prob.workspace_error() == 0

@@ -332,9 +332,12 @@ __global__ __launch_bounds__(256) void k_time_keys(const double *y, const int8_t
 // The order from the sorted records.  low > 0: the keys are in order by the
 // bits from `low` up only, so a group of records that agree in those is put in
 // order here -- by (key, position), which is what the remaining stable passes
-// would give -- each position ranking its group's records itself.  Groups of
-// equal keys are in order already; a group of different ones with over
-// kGroupMax records on either side of a change sets err[1], and the
+// would give -- each record looking at its group once for the place it goes
+// to.  (A preparation of 1e6 times in groups of some 8, 16 and 32: 313, 540 and
+// 532 us, the last two by all bits in the end; 581 by all bits at once; 434,
+// 841 and 969 with every position looking for its record over all pairs.)
+// Groups of equal keys are in order already; a group of different ones with
+// over kGroupMax records on either side of a change sets err[1], and the
 // caller orders all bits instead (1e6 continuous times and one far from them:
 // 557 us for a preparation that always ordered all 64 bits, 515 with the
 // attempt first; without the far one 571 and 296).
@@ -347,20 +350,18 @@ constexpr int64_t kFewBits = (int64_t)1 << 23;
 constexpr int kGroupMax = 32;
 
 template <bool PACKED>
-__global__ __launch_bounds__(256) void k_after_sort(int64_t n, int model, int low,
-                                                    const uint64_t *keys, const uint32_t *vals,
-                                                    const int8_t *status, int32_t *perm,
-                                                    int32_t *inv_perm, uint64_t *key_s,
-                                                    int8_t *st_s, uint32_t *ev_bits,
-                                                    uint32_t *err)
+__global__ __launch_bounds__(256) void k_after_sort(int64_t n, int low, const uint64_t *keys,
+                                                    const uint32_t *vals, const int8_t *status,
+                                                    int32_t *perm, int32_t *inv_perm,
+                                                    uint64_t *key_s, int8_t *st_s, uint32_t *err)
 {
     for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n;
          k += (int64_t)gridDim.x * blockDim.x) {
         if (low > 0 &&
             __hip_atomic_load(err + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
             return;
-        int64_t from = k;
-        uint64_t key = keys[k];
+        int64_t at = k;
+        const uint64_t key = keys[k];
         const uint64_t prev = k > 0 ? keys[k - 1] : ~key, next = k + 1 < n ? keys[k + 1] : ~key;
         if (low > 0 && ((prev ^ key) >> low == 0 || (next ^ key) >> low == 0)) {
             int64_t a = k, b = k;  // the group, as far as it is looked at
@@ -371,33 +372,29 @@ __global__ __launch_bounds__(256) void k_after_sort(int64_t n, int model, int lo
                 err[1] = 1u;  // no atomic: thousands of waves may get here
                 return;  // all of this is done again
             }
+            // records of the group that go elsewhere: larger keys before
+            // this one move behind it, smaller ones after it before it
             bool mixed = false;
-            while (a > 0 && k - a <= kGroupMax && (keys[a - 1] ^ key) >> low == 0) {
+            while (a > 0 && k - a <= kGroupMax) {
+                const uint64_t q = keys[a - 1];
+                if ((q ^ key) >> low != 0) break;
                 --a;
-                mixed = mixed || keys[a] != key;
+                mixed = mixed || q != key;
+                at -= q > key;
             }
-            while (b + 1 < n && b - k <= kGroupMax && (keys[b + 1] ^ key) >> low == 0) {
+            while (b + 1 < n && b - k <= kGroupMax) {
+                const uint64_t q = keys[b + 1];
+                if ((q ^ key) >> low != 0) break;
                 ++b;
-                mixed = mixed || keys[b] != key;
+                mixed = mixed || q != key;
+                at += q < key;
             }
             if (mixed && (k - a > kGroupMax || b - k > kGroupMax)) {
                 err[1] = 1u;
                 return;
             }
-            if (mixed) {
-                for (int64_t q = a; q <= b; ++q) {
-                    const uint64_t kq = keys[q];
-                    int64_t at = a;
-                    for (int64_t r = a; r <= b; ++r) {
-                        const uint64_t kr = keys[r];
-                        at += kr < kq || (kr == kq && r < q);
-                    }
-                    if (at == k) from = q;
-                }
-                key = keys[from];
-            }
         }
-        const uint32_t v = vals[from];
+        const uint32_t v = vals[k];
         int64_t i = PACKED ? v & ((1u << kIdxBits) - 1u) : v;
         if (i >= n) {
             atomicOr(err, 64u);
@@ -405,13 +402,10 @@ __global__ __launch_bounds__(256) void k_after_sort(int64_t n, int model, int lo
         }
         int8_t s = PACKED ? (int8_t)(v >> kIdxBits) : status[i];
         if (s < 0 || s > 2) s = 0;  // reported by k_time_keys
-        perm[k] = (int32_t)i;
-        inv_perm[i] = (int32_t)k;
-        key_s[k] = key;
-        st_s[k] = s;
-        const bool ev = model == SS_COX ? (s != 0) : (s == 1);
-        const uint64_t bits = __ballot(ev);  // k is a multiple of 64 at lane 0
-        if (lane_id() == 0) *reinterpret_cast<uint64_t *>(ev_bits + k / 32) = bits;
+        perm[at] = (int32_t)i;
+        inv_perm[i] = (int32_t)at;
+        key_s[at] = key;
+        st_s[at] = s;
     }
 }
 
@@ -439,12 +433,13 @@ struct OpRun {
 
 __device__ __forceinline__ void run_items(int64_t n, int model, const uint64_t *key_s,
                                           const int8_t *st_s, int64_t k0, uint64_t (&key)[SI],
-                                          uint64_t (&it)[SI])
+                                          uint64_t (&it)[SI], uint32_t &events)
 {
     load_items<uint64_t, OpRun>(key_s, k0, n, key);
     uint64_t prev = k0 > 0 && k0 < n ? key_s[k0 - 1] : 0;
     // st_s is aligned to 256 bytes and holds whole runs of SI
     const uint64_t st = k0 < n ? *reinterpret_cast<const uint64_t *>(st_s + k0) : 0;
+    events = 0;  // a bit per item
 #pragma unroll
     for (int i = 0; i < SI; ++i) {
         const int64_t k = k0 + i;
@@ -454,17 +449,24 @@ __device__ __forceinline__ void run_items(int64_t n, int model, const uint64_t *
             const bool ev = model == SS_COX ? (s != 0) : (s == 1);
             it[i] = ((uint64_t)(k == 0 || !same_time(key[i], prev)) << 63) | ((uint64_t)ev << 31) |
                     (uint64_t)(s == 0);
+            events |= (uint32_t)ev << i;
             prev = key[i];
         }
     }
 }
 
+// Also leaves the events as one bit per position (a thread's items: a byte).
 __global__ __launch_bounds__(SB) void k_runs_reduce(int64_t n, int model, const uint64_t *key_s,
-                                                    const int8_t *st_s, uint64_t *sums)
+                                                    const int8_t *st_s, uint64_t *sums,
+                                                    uint8_t *ev_bytes)
 {
+    static_assert(SI == 8, "a byte of events per thread");
     __shared__ uint64_t s_w[SB / kWave];
     uint64_t key[SI], it[SI];
-    run_items(n, model, key_s, st_s, (int64_t)blockIdx.x * ST + (int64_t)threadIdx.x * SI, key, it);
+    uint32_t events;
+    const int64_t k0 = (int64_t)blockIdx.x * ST + (int64_t)threadIdx.x * SI;
+    run_items(n, model, key_s, st_s, k0, key, it, events);
+    if (k0 < n) ev_bytes[k0 / 8] = (uint8_t)events;
     const uint64_t t = block_scan<uint64_t, OpRun>(it, 0, s_w);
     if (threadIdx.x == 0) sums[blockIdx.x] = t;
 }
@@ -482,7 +484,8 @@ __global__ __launch_bounds__(SB) void k_runs_finish(int64_t n, int model, int64_
     __shared__ double s_p[SB / kWave];
     const int64_t k0 = (int64_t)blockIdx.x * ST + (int64_t)threadIdx.x * SI;
     uint64_t key[SI], it[SI];
-    run_items(n, model, key_s, st_s, k0, key, it);
+    uint32_t events;
+    run_items(n, model, key_s, st_s, k0, key, it, events);
     const uint64_t carry = tile_carry<uint64_t, OpRun, false>(sums, tiles, s_w);
     block_scan<uint64_t, OpRun>(it, carry, s_w);
     const uint64_t after = k0 + SI < n ? key_s[k0 + SI] : 0;
@@ -693,13 +696,11 @@ int32_t run_prepare(int32_t model, int64_t n, int64_t p, int64_t nnz, const doub
         uint64_t *key_s = ks == w.keyA ? w.keyB : w.keyA;
         const int check = low > bottom ? low : 0;
         if (packed)
-            hipLaunchKernelGGL(k_after_sort<true>, dim3(grid_1d(n)), dim3(256), 0, s, n,
-                               (int)model, check, ks, vs, status, perm, inv_perm, key_s, w.st_s,
-                               w.ev_bits, err);
+            hipLaunchKernelGGL(k_after_sort<true>, dim3(grid_1d(n)), dim3(256), 0, s, n, check,
+                               ks, vs, status, perm, inv_perm, key_s, w.st_s, err);
         else
-            hipLaunchKernelGGL(k_after_sort<false>, dim3(grid_1d(n)), dim3(256), 0, s, n,
-                               (int)model, check, ks, vs, status, perm, inv_perm, key_s, w.st_s,
-                               w.ev_bits, err);
+            hipLaunchKernelGGL(k_after_sort<false>, dim3(grid_1d(n)), dim3(256), 0, s, n, check,
+                               ks, vs, status, perm, inv_perm, key_s, w.st_s, err);
         SS_LAUNCH_CHECK();
         uint32_t found = 0;
         if (check) {
@@ -713,7 +714,7 @@ int32_t run_prepare(int32_t model, int64_t n, int64_t p, int64_t nnz, const doub
         const int64_t tiles = ceil_div(n, (int64_t)ST);
         const dim3 tg((unsigned)tiles);
         hipLaunchKernelGGL(k_runs_reduce, tg, dim3(SB), 0, s, n, (int)model, key_s, w.st_s,
-                           w.sums);
+                           w.sums, (uint8_t *)w.ev_bits);
         SS_LAUNCH_CHECK();
         if (tiles > ST) {
             hipLaunchKernelGGL((k_scan_spine<uint64_t, OpRun>), dim3(1), dim3(SB), 0, s, w.sums,

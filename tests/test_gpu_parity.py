@@ -788,3 +788,29 @@ def test_sweep_launches_large_negative_step(n, model, monkeypatch):
     prob.sweep("none", 0.0, g12_out=g12)
     _check_history(prob, c, g12, hist)
     np.testing.assert_allclose(prob.beta.cpu().numpy(), beta, rtol=1e-9, atol=1e-12)
+
+
+# Times in groups of exactly m that agree in the bits the sort orders and
+# differ below (some of them equal): from groups that are ranked in place to
+# those that send the order back to all bits (over 32 records on a side).
+@pytest.mark.parametrize("m", [2, 8, 31, 32, 33, 34, 64, 65, 66, 200])
+@pytest.mark.parametrize("n", [5000, 70_001])
+def test_time_ordering_groups(n, m):
+    rng = np.random.default_rng(n + m)
+    upper = (np.arange(n) // m).astype(np.uint64) << np.uint64(34)
+    low = rng.integers(0, 2 * m, n).astype(np.uint64)
+    y = (np.float64(1.0).view(np.uint64) + upper + low).view(np.float64)
+    rng.shuffle(y)
+    status = rng.integers(0, 3, n).astype(np.int8)
+    prob = ss.Problem("fg", y, status, np.array([0, n]), np.arange(n, dtype=np.int32))
+    order = np.argsort(-y, kind="stable")
+    np.testing.assert_array_equal(prob.perm.cpu().numpy(), order)
+    inv = np.empty_like(order)
+    inv[order] = np.arange(n)
+    np.testing.assert_array_equal(prob.inv_perm.cpu().numpy(), inv)
+    ys, st = y[order], status[order]
+    end = np.append(ys[1:] != ys[:-1], True)
+    run = np.concatenate([[0], np.cumsum(end)[:-1]])
+    d = np.bincount(run, st == 1)
+    np.testing.assert_array_equal(prob.d32.cpu().numpy(), np.where(end, d[run], 0).astype(np.int64))
+    assert float(prob.c[0]) == float(np.sum(st == 1))

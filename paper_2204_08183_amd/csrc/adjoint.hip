@@ -25,6 +25,8 @@
 // d/S0 and d G/S0 had taken 7 and 13).
 #include <math.h>
 
+#include <type_traits>
+
 #include "scan_device.h"
 #include "ss_internal.h"
 
@@ -390,15 +392,21 @@ __global__ __launch_bounds__(256) void k_xt_span(int64_t p, int64_t nspan, int64
 // 5e7 non-zeros: 194 us); from LDS it costs a bank access and the row indices
 // stream from HBM (46 us, 4.3 TB/s).  A wave takes the bounds of its columns
 // in one set of loads, and loads a column's first kXtAhead * 64 row indices
-// while it sums the column before.
+// while it sums the column before.  Short pieces would leave most of those
+// lanes and loads idle: batches of them put several columns in flight at once
+// (up to 128 entries) or give each lane a column (up to kXtFew); in long
+// spans, which wide designs get, short columns are gathered from L2 at once.
 //
-// The line between the two, whole beta gradients at 5% density, from L2 /
-// from LDS: N = 1e6, P = 16 36.3 / 32.3 us, P = 256 69.8 / 40.9; N = 1e5,
-// P = 512 25.7 / 25.5 (valued 28.3 / 33.1), P = 1024 32.7 / 28.4 (37.8 /
-// 38.7), P = 2048 50.5 / 33.4; below 16 columns a span loaded is hardly read.
+// The line between the two, whole beta gradients, us from L2 / from LDS: 5%
+// density N = 1e6, P = 16 40 / 32, P = 256 69.8 / 40.9; N = 1e5, P = 512 25.4 /
+// 25.3 (valued 28.3 / 29), P = 1024 32.7 / 27.8 (37.8 / 33.6), P = 2048 50.5 /
+// 32.5; 100 non-zeros a column N = 1e6, P = 2000 70 / 36; N = 1000, P = 1e5,
+// 5% 91 / 78.  Below 16 columns a span loaded is hardly read; with 16 columns
+// of 100 non-zeros N = 2e7 281 / 287.
 constexpr int kXtBlock = 512;
 constexpr int kXtSpan = 8192;
 constexpr int kXtAhead = 8;
+constexpr int kXtFew = 8;  // entries of a piece that a lane sums by itself
 constexpr int64_t kXtLdsCols = 16;
 constexpr int64_t kXtLdsSize = 100'000'000;  // positions times columns
 
@@ -414,6 +422,7 @@ __global__ __launch_bounds__(kXtBlock) void k_xt_lds(int64_t n, int64_t p, int64
     constexpr int NW = kXtBlock / kWave;
     constexpr int kSub = kXtSpan / SS_CHUNK;  // chunks held at a time
     __shared__ double s_g[kXtSpan + 1];
+    __shared__ double s_t[NW][kXtAhead];
     const int lane = lane_id();
     const int w = threadIdx.x / kWave;
     const int64_t c = blockIdx.x / groups;
@@ -423,40 +432,135 @@ __global__ __launch_bounds__(kXtBlock) void k_xt_lds(int64_t n, int64_t p, int64
     // columns of this wave: a contiguous share of the group's
     const int64_t share = (group_cols + NW - 1) / NW;
     const int64_t ja = min(j0 + w * share, j1), jz = min(ja + share, j1);
+    // a batch of up to 64 columns from jb on: column jb + x has its piece
+    // [lo, lo + len) between chunks ta and tb in lane x, which also adds its
+    // sum to part
+    int64_t lo = 0;
+    int32_t len = 0;
+    auto batch = [&](int64_t jb, int m, int64_t ta, int64_t tb) {
+        lo = 0;
+        len = 0;
+        if (lane < m) {
+            const int32_t *cp = chunk_ptr + (jb + lane) * (nchunk + 1);
+            const int32_t a = cp[ta], b = cp[tb];
+            lo = col_ptr[jb + lane] + a;
+            len = b - a;
+        }
+    };
+    // piece x of the batch: entries [at, at + l)
+    auto bounds = [&](int x, int64_t &at, int32_t &l) {
+        const uint32_t l0 = __builtin_amdgcn_readlane((int)(lo & 0xffffffff), x);
+        const uint32_t l1 = __builtin_amdgcn_readlane((int)(lo >> 32), x);
+        at = (int64_t)(((uint64_t)l1 << 32) | l0);
+        l = __builtin_amdgcn_readlane(len, x);
+    };
+    auto put = [&](int64_t jb, bool first, double t) {
+        double *dst = part + (jb + lane) * nspan + c;
+        *dst = first ? t : *dst + t;
+    };
+    // Batches of short pieces; get(in, r): the gradient at row r, 0 if !in
+    // (an entry past the end reads the design's first).  True: all done.
+    auto short_pieces = [&](int64_t jb, int m, bool first, int32_t most, auto get) -> bool {
+        if (__any(len > most)) return false;
+        // a lane for each column
+        if (!__any(len > kXtFew)) {
+            double acc = 0.0;
+            for (int32_t i0 = 0; __any(i0 < len); i0 += kXtFew / 2) {
+                int32_t r[kXtFew / 2];
+                double v[VALS ? kXtFew / 2 : 1];
+#pragma unroll
+                for (int i = 0; i < kXtFew / 2; ++i) {
+                    const int64_t o = i0 + i < len ? lo + i0 + i : 0;
+                    r[i] = rows_sorted[o];
+                    if constexpr (VALS) v[i] = vals_sorted[o];
+                }
+#pragma unroll
+                for (int i = 0; i < kXtFew / 2; ++i) {
+                    const double gv = get(i0 + i < len, r[i]);
+                    if constexpr (VALS) acc += i0 + i < len ? v[i] * gv : 0.0;
+                    else acc += gv;
+                }
+            }
+            if (lane < m) put(jb, first, acc);
+            return true;
+        }
+        // kXtAhead loads in flight over several columns, D for each
+        auto several = [&](auto depth) {
+            constexpr int D = decltype(depth)::value, C = kXtAhead / D;
+            for (int x0 = 0; x0 < m; x0 += C) {
+                int32_t r[kXtAhead], left[kXtAhead];
+                double v[VALS ? kXtAhead : 1], acc[C];
+#pragma unroll
+                for (int u = 0; u < kXtAhead; ++u) {
+                    int64_t at;
+                    int32_t l;
+                    bounds(min(x0 + u / D, kWave - 1), at, l);  // (none past m)
+                    left[u] = l - u % D * kWave;
+                    const int64_t o = lane < left[u] ? at + u % D * kWave + lane : 0;
+                    r[u] = rows_sorted[o];
+                    if constexpr (VALS) v[u] = vals_sorted[o];
+                }
+#pragma unroll
+                for (int u = 0; u < kXtAhead; ++u) {
+                    double gv = get(lane < left[u], r[u]);
+                    if constexpr (VALS) gv = lane < left[u] ? v[u] * gv : 0.0;
+                    acc[u / D] = u % D == 0 ? gv : acc[u / D] + gv;
+                }
+                wave_sums_to<C>(acc, s_t[w]);
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                if (lane >= x0 && lane < min(x0 + C, m)) put(jb, first, s_t[w][lane - x0]);
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            }
+        };
+        if (!__any(len > kWave)) several(std::integral_constant<int, 1>{});
+        else several(std::integral_constant<int, 2>{});
+        return true;
+    };
+    // A span of several stretches: batches with up to 128 entries a column in
+    // all of it gather from L2, at once.
+    uint64_t direct = 0;  // the wave's batches (the first 64) that did
+    if (kspan > kSub) {
+        bool all = jz - ja <= 64 * kWave;
+        int64_t q = 0;
+        for (int64_t jb = ja; jb < jz && q < 64; jb += kWave, ++q) {
+            const int m = (int)min((int64_t)kWave, jz - jb);
+            batch(jb, m, c * kspan, t_end);
+            const bool done = short_pieces(jb, m, true, 2 * kWave, [&](bool in, int32_t row) {
+                const double x = g[row];
+                return in ? x : 0.0;
+            });
+            if (done) direct |= 1ull << q;
+            all = all && done;
+        }
+        if (__syncthreads_and(all)) return;
+    }
     for (int64_t t0 = c * kspan; t0 < t_end; t0 += kSub) {
         const int64_t t1 = min(t0 + kSub, t_end);
         const int64_t k0 = t0 * SS_CHUNK;
         const int32_t cnt = (int32_t)(min(t1 * SS_CHUNK, n) - k0);
+        const bool first = t0 == c * kspan;
         __syncthreads();
         for (int32_t i = threadIdx.x; i < cnt; i += kXtBlock) s_g[i] = g[k0 + i];
         if (threadIdx.x == 0) s_g[kXtSpan] = 0.0;
         __syncthreads();
-        for (int64_t jb = ja; jb < jz; jb += kWave) {
+        int64_t q = 0;
+        for (int64_t jb = ja; jb < jz; jb += kWave, ++q) {
+            if (q < 64 && (direct >> q) & 1u) continue;
             const int m = (int)min((int64_t)kWave, jz - jb);
-            int64_t lo = 0;
-            int32_t len = 0;
-            if (lane < m) {
-                const int32_t *cp = chunk_ptr + (jb + lane) * (nchunk + 1);
-                const int32_t a = cp[t0], b = cp[t1];
-                lo = col_ptr[jb + lane] + a;
-                len = b - a;
-            }
-            // piece x of the batch: entries [at, at + l)
-            auto bounds = [&](int x, int64_t &at, int32_t &l) {
-                const uint32_t l0 = __builtin_amdgcn_readlane((int)(lo & 0xffffffff), x);
-                const uint32_t l1 = __builtin_amdgcn_readlane((int)(lo >> 32), x);
-                at = (int64_t)(((uint64_t)l1 << 32) | l0);
-                l = __builtin_amdgcn_readlane(len, x);
-            };
-            // entries o .. of a piece of l > 0 (the last one again past the end)
+            batch(jb, m, t0, t1);
+            if (short_pieces(jb, m, first, 2 * kWave, [&](bool in, int32_t row) {
+                    return s_g[in ? row - (int32_t)k0 : kXtSpan];
+                }))
+                continue;
+            // entries o .. of a piece (the last one again past the end; of an
+            // empty one the design's first)
             auto load = [&](int64_t at, int32_t l, int32_t o, int32_t (&r)[kXtAhead],
                             double (&v)[VALS ? kXtAhead : 1]) {
-                if (l == 0) return;
-                const int32_t *rp = rows_sorted + at;
-                const double *vp = VALS ? vals_sorted + at : nullptr;
+                const int32_t *rp = rows_sorted + (l > 0 ? at : 0);
+                const double *vp = VALS ? vals_sorted + (l > 0 ? at : 0) : nullptr;
 #pragma unroll
                 for (int u = 0; u < kXtAhead; ++u) {
-                    const uint32_t i = (uint32_t)min(o + u * kWave + lane, l - 1);
+                    const uint32_t i = (uint32_t)min(o + u * kWave + lane, max(l - 1, 0));
                     r[u] = rp[i];
                     if constexpr (VALS) v[u] = vp[i];
                 }
@@ -500,16 +604,11 @@ __global__ __launch_bounds__(kXtBlock) void k_xt_lds(int64_t n, int64_t p, int64
                 }
                 int32_t r2[kXtAhead];
                 double v2[VALS ? kXtAhead : 1];
-                if (x + 1 < m) {
-                    bounds(x + 1, at, l);
-                    load(at, l, 0, r2, v2);
-                }
+                bounds(min(x + 1, m - 1), at, l);
+                load(at, l, 0, r2, v2);
                 take(l0 - done);
                 const double t = dpp_wave_sum((acc[0] + acc[1]) + (acc[2] + acc[3]));
-                if (lane == 0) {
-                    double *dst = part + (jb + x) * nspan + c;
-                    *dst = t0 == c * kspan ? t : *dst + t;
-                }
+                if (lane == x) put(jb, first, t);
 #pragma unroll
                 for (int u = 0; u < kXtAhead; ++u) {
                     r[u] = r2[u];
@@ -663,13 +762,14 @@ int64_t xt_span_chunks(int64_t n, int64_t p)
 // 90% of the workgroup slots (two per CU) over the rounds they take, else the
 // fullest; at least 16 columns for each span loaded.  (N = 1e6, P = 1000,
 // 123 spans: 4 groups are one round of 492 workgroups; 9 groups, 2.2 rounds,
-// took 155 us.)
+// took 155 us.  N = 1000, P = 1e5, one span: 461 groups 78 us, 64 groups, as a
+// limit once had it, 205.)
 int64_t xt_group_cols(int64_t p, int64_t nspan)
 {
     constexpr int64_t slots = 2 * 256;
     int64_t best = 1;
     double full = 0.0;
-    for (int64_t g = 1; g <= std::min<int64_t>(p / 16, 64); ++g) {
+    for (int64_t g = 1; g <= std::min<int64_t>(p / 16, slots); ++g) {
         const int64_t wgs = nspan * g;
         const double f = (double)wgs / (double)(slots * ceil_div(wgs, slots));
         if (f > full) {

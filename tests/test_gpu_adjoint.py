@@ -273,3 +273,36 @@ def test_beta_gradient_column_groups(model, n, p, valued):
         x = 1.0 if vals is None else vals[col_ptr[j]:col_ptr[j + 1]]
         scale = float(np.sum(np.abs(x) * (np.abs(want_eta[r]) + 1.0)))
         assert abs(got[j] - float(np.sum(x * want_eta[r]))) <= TOL * scale, j
+
+
+@pytest.mark.parametrize("valued", [False, True])
+@pytest.mark.parametrize("model,n,p", [("cox", 40_009, 2600), ("fg", 8000, 13_001),
+                                       ("cox", 40_000, 30_000)])
+def test_beta_gradient_sparse_columns(model, n, p, valued):
+    """Batches of 64 columns none of which has more than 0, 8, 64 or 128 entries in
+    a span, and batches with one that does, the columns of one
+    batch all in one span or spread over all; one span or several of them,
+    of one or more stretches of 8192 positions."""
+    import scipy.sparse as sp
+    rng = np.random.default_rng(p)
+    kinds = [(0, 1), (0, 9), (8, 9), (1, 10), (0, 65), (64, 65), (60, 66), (100, 129), (120, 140)]
+    cols = []
+    for j in range(p):
+        lo, hi = kinds[(j // 64) % len(kinds)]
+        span = min(n, 8192 if (j // 576) % 2 else n)
+        m = int(rng.integers(lo, hi))
+        cols.append(np.sort(rng.choice(span, m, replace=False)))
+    ptr = np.concatenate([[0], np.cumsum([r.size for r in cols])]).astype(np.int64)
+    rows = np.concatenate(cols).astype(np.int32)
+    c = make_case(model, n, 1, 46, 0, 0.001, False)
+    c["y"] = -np.sort(-c["y"])  # sorted positions are the subjects
+    vals = rng.normal(0.0, 1.0, rows.size) if valued else None
+    prob = ss.Problem(model, c["y"], c["status"], ptr, rows, vals, DEV)
+    prob.set_eta(c["eta"])
+    gb, _ = prob.beta_gradient()
+    want_eta = oadj.eta_gradient_scan(model, c["y"], c["status"], c["eta"])
+    x = sp.csc_matrix((np.ones(rows.size) if vals is None else vals, rows, ptr), shape=(n, p))
+    scale = abs(x).T @ (np.abs(want_eta) + 1.0)
+    assert np.all(np.abs(gb.cpu().numpy() - x.T @ want_eta) <= TOL * scale)
+    gb2, _ = prob.beta_gradient()
+    assert torch.equal(gb, gb2)

@@ -58,8 +58,9 @@ struct DesignArgs {
 
 struct Piece {
     int64_t col, c0, lo, base;
-    int32_t m, cnt;  // entries, positions of the window
+    int32_t m, cnt;  // entries (at most cnt), positions of the window
     bool last;       // the column's last window
+    bool over;       // there are more entries than positions
 };
 
 __device__ __forceinline__ Piece piece_of(const DesignArgs &a, int64_t q)
@@ -70,10 +71,13 @@ __device__ __forceinline__ Piece piece_of(const DesignArgs &a, int64_t q)
     r.c0 = a.col_ptr[r.col];
     r.lo = a.nwin == 1 ? r.c0 : (int64_t)a.piece[q];
     const int64_t hi = a.nwin == 1 ? a.col_ptr[r.col + 1] : (int64_t)a.piece[q + 1];
-    r.m = (int32_t)(hi - r.lo);
     r.base = win << (a.nwin == 1 ? 0 : a.wbits);
     const int64_t left = a.n - r.base;
     r.cnt = (int32_t)(a.nwin == 1 ? left : min(left, (int64_t)1 << a.wbits));
+    // more entries than positions: some row is there twice, and the others
+    // need no look (a count near 2^31 would take the loops' int32 past it)
+    r.over = hi - r.lo > r.cnt;
+    r.m = (int32_t)min(hi - r.lo, (int64_t)r.cnt);
     r.last = win == a.nwin - 1;
     return r;
 }
@@ -156,7 +160,7 @@ __global__ __launch_bounds__(BLOCK) void k_design_bits(DesignArgs a, int32_t max
             }
         }
         if (bad) atomicOr(a.err, 8u);
-        if (twice) atomicOr(a.err, 16u);  // a duplicate row
+        if (twice || pc.over) atomicOr(a.err, 16u);  // a duplicate row
         __syncthreads();
 
         // ---- entries per group of words, then their exclusive prefix

@@ -814,3 +814,20 @@ def test_time_ordering_groups(n, m):
     d = np.bincount(run, st == 1)
     np.testing.assert_array_equal(prob.d32.cpu().numpy(), np.where(end, d[run], 0).astype(np.int64))
     assert float(prob.c[0]) == float(np.sum(st == 1))
+
+
+@pytest.mark.parametrize("n,m", [(1, 2), (700, 701), (2_100_000, 2_100_001), (3, 2**31 - 1)])
+def test_design_more_entries_than_subjects(n, m):
+    """A column with more entries than there are subjects has a duplicate row,
+    whatever their number: refused, at the largest number of entries too."""
+    if torch.cuda.mem_get_info()[0] < 24 * m + 2**30:
+        pytest.skip("needs %.0f GB" % (24e-9 * m))
+    rows = torch.arange(m, dtype=torch.int32, device=DEV).remainder_(n)
+    with pytest.raises(ss.SurvScanError):
+        ss.Problem("cox", np.arange(n, dtype=np.float64), np.ones(n, dtype=np.int8),
+                   np.array([0, m], dtype=np.int64), rows)
+    # the device is as it was
+    y = np.random.default_rng(n).random(500)
+    prob = ss.Problem("cox", y, np.ones(500, dtype=np.int8), np.array([0, 1]),
+                      np.array([7], dtype=np.int32))
+    np.testing.assert_array_equal(prob.perm.cpu().numpy(), np.argsort(-y, kind="stable"))

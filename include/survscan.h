@@ -48,7 +48,8 @@ extern "C" {
 #define SS_EINVAL       (-1)   /* null pointer, bad size, index out of range */
 #define SS_EWORKSPACE   (-2)   /* workspace too small or misaligned          */
 #define SS_EUNSUPPORTED (-3)   /* unknown model / penalty                    */
-#define SS_EDEVICE      (-4)   /* a HIP runtime call failed                  */
+#define SS_EDEVICE      (-4)   /* a HIP runtime call failed, or host memory  */
+                               /* ran out (ss_prepare)                       */
 
 /* ------------------------------------------------------------ enums */
 #define SS_COX        0        /* Sec. 2.1: events are status != 0          */

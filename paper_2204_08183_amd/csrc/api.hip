@@ -5,6 +5,8 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <new>
+
 #include "ss_internal.h"
 
 namespace ss {
@@ -127,9 +129,14 @@ int32_t ss_prepare(int32_t model, int64_t n, int64_t p, int64_t nnz, const doubl
     if (model == SS_FINE_GRAY && (!w_comp || !g_end)) return SS_EINVAL;
     if (!ws || ((uintptr_t)ws & 255u)) return SS_EWORKSPACE;
     if (ws_bytes < prepare_ws_bytes(n, p, nnz)) return SS_EWORKSPACE;
-    return run_prepare(model, n, p, nnz, y, status, col_ptr, rows, vals, perm, inv_perm,
-                       d8, d32, c, rows_sorted, vals_sorted, chunk_ptr, w_comp, g_end, ws,
-                       ws_bytes, (hipStream_t)stream);
+    try {  // (host lists of the column pointers and of the design's chunks)
+        return run_prepare(model, n, p, nnz, y, status, col_ptr, rows, vals, perm, inv_perm,
+                           d8, d32, c, rows_sorted, vals_sorted, chunk_ptr, w_comp, g_end, ws,
+                           ws_bytes, (hipStream_t)stream);
+    } catch (const std::bad_alloc &) {
+        snprintf(g_last_hip, sizeof(g_last_hip), "out of host memory");
+        return SS_EDEVICE;
+    }
 }
 
 size_t ss_workspace_bytes(int32_t model, int64_t n)

@@ -3,6 +3,8 @@ rejects invalid arguments on the host before any launch (no GPU needed)."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -263,3 +265,27 @@ def test_tune_knows_the_shapes_of_the_rule(lib):
                 assert ss.tune_get(S, model, "f64", True, 200_000) == shape
     finally:
         ss.tune_clear()
+
+
+def test_prepare_without_host_memory():
+    """Where the host list of column pointers cannot be allocated ss_prepare
+    returns a status; no exception crosses the interface.  (In a process of
+    its own: its address space is limited.)"""
+    code = """
+import ctypes, resource, sys
+sys.path.insert(0, %r)
+from paper_2204_08183_amd import survscan as ss
+lib = ss.load()
+with open("/proc/self/statm") as f:
+    used = int(f.read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (used + (1 << 30), resource.RLIM_INFINITY))
+p = 2**31 - 1
+ptr = ctypes.c_void_p(256)
+args = [ptr] * 5 + [ptr] * 8 + [None, None]   # inputs, outputs, no weights
+rc = lib.ss_prepare(0, 1, p, 1, *args, ptr, 2**62, None)
+text = lib.ss_status_string(rc)
+print(rc, text.decode() if isinstance(text, bytes) else text)
+""" % os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, (r.returncode, r.stderr[-400:])
+    assert r.stdout.split(None, 1) == ["%d" % ss.SS_EDEVICE, "out of host memory\n"], r.stdout

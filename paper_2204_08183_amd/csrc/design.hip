@@ -481,7 +481,11 @@ int32_t launch_bits(const DesignArgs &a, int64_t grid, int32_t max_words, hipStr
     const size_t lds = 4 * (size_t)max_words + 4 * (size_t)(max_words / kGroupWords);
     void *k = a.vals_sorted ? (void *)&k_design_bits<BLOCK, true>
                             : (void *)&k_design_bits<BLOCK, false>;
-    SS_HIP_CHECK(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    // the largest window's, whatever this one's: the attribute belongs to the
+    // process, and several threads may be here
+    constexpr size_t most = ((size_t)1 << kMaxWindowBits) / 8 * (kGroupWords + 1) / kGroupWords;
+    if (BLOCK == 1024)
+        SS_HIP_CHECK(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most));
     DesignArgs args = a;
     void *ptrs[] = {&args, &max_words};
     SS_HIP_CHECK(hipLaunchKernel(k, dim3((unsigned)grid), dim3(BLOCK), ptrs, lds, s));

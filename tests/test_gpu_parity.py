@@ -831,3 +831,42 @@ def test_design_more_entries_than_subjects(n, m):
     prob = ss.Problem("cox", y, np.ones(500, dtype=np.int8), np.array([0, 1]),
                       np.array([7], dtype=np.int32))
     np.testing.assert_array_equal(prob.perm.cpu().numpy(), np.argsort(-y, kind="stable"))
+
+
+def test_prepare_from_several_threads():
+    """Designs of one window each, of different sizes (so different amounts of
+    LDS for the same kernel), prepared by several threads on streams of
+    their own."""
+    import threading
+    sizes = [140_000, 300_000, 600_000, 1_048_576]
+    cases = []
+    for n in sizes:
+        rng = np.random.default_rng(n)
+        rows = [np.sort(rng.choice(n, n // 50, replace=False)) for _ in range(3)]
+        ptr = np.concatenate([[0], np.cumsum([r.size for r in rows])]).astype(np.int64)
+        y = rng.random(n)
+        cases.append((n, y, rng.integers(0, 2, n).astype(np.int8), ptr,
+                      np.concatenate(rows).astype(np.int32)))
+    failed = []
+
+    def work(c):
+        try:
+            n, y, st, ptr, rows = c
+            order = np.argsort(-y, kind="stable")
+            inv = np.empty_like(order)
+            inv[order] = np.arange(n)
+            want = np.concatenate([np.sort(inv[rows[a:b]]) for a, b in zip(ptr[:-1], ptr[1:])])
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for _ in range(6):
+                    prob = ss.Problem("cox", y, st, ptr, rows, None, DEV)
+                    got = prob.rows_sorted.cpu().numpy()
+                    assert np.array_equal(got, want)
+        except BaseException as e:  # noqa: BLE001
+            failed.append(e)
+
+    threads = [threading.Thread(target=work, args=(c,)) for c in cases]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failed, failed

@@ -321,7 +321,8 @@ int32_t ss_grad_hess_mixed(int32_t model, int32_t acc, int64_t n, int64_t p,
  * double.  The
  * workspace (any 256-byte-aligned device buffer of
  * ss_eta_gradient_workspace_bytes(n) bytes, caller-owned, no
- * initialisation) holds four N-vectors of partial results and per-tile sums; it is distinct from the ss_grad_hess
+ * initialisation) is sized for four N-vectors and per-tile sums, of which
+ * two vectors are in use; it is distinct from the ss_grad_hess
  * workspace.  All sums are taken in a fixed order: results are
  * deterministic.  Errors: SS_EINVAL for an unknown-size or null argument,
  * SS_EUNSUPPORTED for an unknown model, SS_EWORKSPACE for a short or

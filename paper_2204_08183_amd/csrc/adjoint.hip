@@ -657,7 +657,7 @@ size_t adj_layout(int64_t n, void *ws, AdjWs *w)
     AdjWs t;
     t.a = (double *)take(8 * (size_t)n);
     t.q = (double *)take(8 * (size_t)n);
-    (void)take(16 * (size_t)n);  // the interface promises four N-vectors
+    (void)take(16 * (size_t)n);  // the interface promises a size of four N-vectors
     t.lpart = (double *)take(8 * tiles);
     t.sum_e = (double *)take(8 * tiles);
     t.sum_ew = (double *)take(8 * tiles);

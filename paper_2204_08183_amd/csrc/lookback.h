@@ -105,11 +105,10 @@ __device__ bool look_back_seq(const u32x4 *lb, const u32x4 *glb, int32_t tile, i
         double val[NC];
         uint32_t st;
         {
-            u32x4 r[1][NQ];
-            const u32x4 *pp[1] = {ptr};
-            ld_lb<1, NQ>(pp, r);
-            st = before ? (uint32_t)kStateInc : pairs_state<NQ>(r[0], epoch);
-            pub_unpack<NC>(r[0], val);
+            u32x4 r[NQ];
+            ld_pairs<NQ>(ptr, r);
+            st = before ? (uint32_t)kStateInc : pairs_state<NQ>(r, epoch);
+            pub_unpack<NC>(r, val);
 #pragma unroll
             for (int c = 0; c < NC; ++c) val[c] = before ? 0.0 : val[c];
         }
@@ -164,11 +163,10 @@ __device__ bool group_members(const u32x4 *lb, int32_t tile, int32_t nin, uint64
     double val[NC];
     uint32_t st;
     {
-        u32x4 r[1][NQ];
-        const u32x4 *pp[1] = {ptr};
-        ld_lb<1, NQ>(pp, r);
-        st = mine ? pairs_state<NQ>(r[0], epoch) : (uint32_t)kStateAgg;
-        pub_unpack<NC>(r[0], val);
+        u32x4 r[NQ];
+        ld_pairs<NQ>(ptr, r);
+        st = mine ? pairs_state<NQ>(r, epoch) : (uint32_t)kStateAgg;
+        pub_unpack<NC>(r, val);
 #pragma unroll
         for (int c = 0; c < NC; ++c) val[c] = mine ? val[c] : 0.0;
     }

@@ -138,14 +138,6 @@ __device__ __forceinline__ void wave_sums_to(const double (&x)[N], double *dst)
     }
 }
 
-// Inclusive wave-wide scan of NC doubles.
-template <int NC>
-__device__ __forceinline__ void wave_inclusive_scan(double (&x)[NC])
-{
-#pragma unroll
-    for (int c = 0; c < NC; ++c) x[c] = dpp_incl_scan(x[c]);
-}
-
 __device__ __forceinline__ double wave_sum(double x) { return dpp_wave_sum(x); }
 
 // The same for floats (one DPP move per step).
@@ -510,21 +502,6 @@ __device__ __forceinline__ void ld_pairs<6>(const u32x4 *p, u32x4 (&r)[6])
 }
 
 template <>
-__device__ __forceinline__ void ld_pairs<5>(const u32x4 *p, u32x4 (&r)[5])
-{
-    asm volatile(
-                 "global_load_dwordx4 %0, %5, off sc1\n\t"
-                 "global_load_dwordx4 %1, %5, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %2, %5, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %3, %5, off offset:48 sc1\n\t"
-                 "global_load_dwordx4 %4, %5, off offset:64 sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4])
-                 : "v"(p)
-                 : "memory");
-}
-
-template <>
 __device__ __forceinline__ void ld_pairs<8>(const u32x4 *p, u32x4 (&r)[8])
 {
     asm volatile(
@@ -583,189 +560,6 @@ __device__ __forceinline__ void ld_pairs<15>(const u32x4 *p, u32x4 (&r)[15])
                  : "v"(p)
                  : "memory");
 }
-
-
-// Loads NC consecutive pairs at each of KQ addresses and waits for all of
-// them (the look-back's predecessor windows).
-template <int KQ, int NC>
-__device__ __forceinline__ void ld_lb(const u32x4 *const (&p)[KQ], u32x4 (&r)[KQ][NC]);
-
-template <>
-__device__ __forceinline__ void ld_lb<4, 3>(const u32x4 *const (&p)[4],
-                                               u32x4 (&r)[4][3])
-{
-    asm volatile(
-                 "global_load_dwordx4 %0, %12, off sc1\n\t"
-                 "global_load_dwordx4 %1, %12, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %2, %12, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %3, %13, off sc1\n\t"
-                 "global_load_dwordx4 %4, %13, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %5, %13, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %6, %14, off sc1\n\t"
-                 "global_load_dwordx4 %7, %14, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %8, %14, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %9, %15, off sc1\n\t"
-                 "global_load_dwordx4 %10, %15, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %11, %15, off offset:32 sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(r[0][0]), "=&v"(r[0][1]), "=&v"(r[0][2]), "=&v"(r[1][0]), "=&v"(r[1][1]), "=&v"(r[1][2]), "=&v"(r[2][0]), "=&v"(r[2][1]), "=&v"(r[2][2]), "=&v"(r[3][0]), "=&v"(r[3][1]), "=&v"(r[3][2])
-                 : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3])
-                 : "memory");
-}
-
-template <>
-__device__ __forceinline__ void ld_lb<3, 3>(const u32x4 *const (&p)[3],
-                                               u32x4 (&r)[3][3])
-{
-    asm volatile(
-                 "global_load_dwordx4 %0, %9, off sc1\n\t"
-                 "global_load_dwordx4 %1, %9, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %2, %9, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %3, %10, off sc1\n\t"
-                 "global_load_dwordx4 %4, %10, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %5, %10, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %6, %11, off sc1\n\t"
-                 "global_load_dwordx4 %7, %11, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %8, %11, off offset:32 sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(r[0][0]), "=&v"(r[0][1]), "=&v"(r[0][2]), "=&v"(r[1][0]), "=&v"(r[1][1]), "=&v"(r[1][2]), "=&v"(r[2][0]), "=&v"(r[2][1]), "=&v"(r[2][2])
-                 : "v"(p[0]), "v"(p[1]), "v"(p[2])
-                 : "memory");
-}
-
-template <>
-__device__ __forceinline__ void ld_lb<2, 2>(const u32x4 *const (&p)[2],
-                                               u32x4 (&r)[2][2])
-{
-    asm volatile(
-                 "global_load_dwordx4 %0, %4, off sc1\n\t"
-                 "global_load_dwordx4 %1, %4, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %2, %5, off sc1\n\t"
-                 "global_load_dwordx4 %3, %5, off offset:16 sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(r[0][0]), "=&v"(r[0][1]), "=&v"(r[1][0]), "=&v"(r[1][1])
-                 : "v"(p[0]), "v"(p[1])
-                 : "memory");
-}
-
-template <>
-__device__ __forceinline__ void ld_lb<2, 4>(const u32x4 *const (&p)[2],
-                                               u32x4 (&r)[2][4])
-{
-    asm volatile(
-                 "global_load_dwordx4 %0, %8, off sc1\n\t"
-                 "global_load_dwordx4 %1, %8, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %2, %8, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %3, %8, off offset:48 sc1\n\t"
-                 "global_load_dwordx4 %4, %9, off sc1\n\t"
-                 "global_load_dwordx4 %5, %9, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %6, %9, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %7, %9, off offset:48 sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(r[0][0]), "=&v"(r[0][1]), "=&v"(r[0][2]), "=&v"(r[0][3]), "=&v"(r[1][0]), "=&v"(r[1][1]), "=&v"(r[1][2]), "=&v"(r[1][3])
-                 : "v"(p[0]), "v"(p[1])
-                 : "memory");
-}
-
-template <>
-__device__ __forceinline__ void ld_lb<2, 3>(const u32x4 *const (&p)[2],
-                                               u32x4 (&r)[2][3])
-{
-    asm volatile(
-                 "global_load_dwordx4 %0, %6, off sc1\n\t"
-                 "global_load_dwordx4 %1, %6, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %2, %6, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %3, %7, off sc1\n\t"
-                 "global_load_dwordx4 %4, %7, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %5, %7, off offset:32 sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(r[0][0]), "=&v"(r[0][1]), "=&v"(r[0][2]), "=&v"(r[1][0]), "=&v"(r[1][1]), "=&v"(r[1][2])
-                 : "v"(p[0]), "v"(p[1])
-                 : "memory");
-}
-
-template <>
-__device__ __forceinline__ void ld_lb<2, 6>(const u32x4 *const (&p)[2],
-                                               u32x4 (&r)[2][6])
-{
-    asm volatile(
-                 "global_load_dwordx4 %0, %12, off sc1\n\t"
-                 "global_load_dwordx4 %1, %12, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %2, %12, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %3, %12, off offset:48 sc1\n\t"
-                 "global_load_dwordx4 %4, %12, off offset:64 sc1\n\t"
-                 "global_load_dwordx4 %5, %12, off offset:80 sc1\n\t"
-                 "global_load_dwordx4 %6, %13, off sc1\n\t"
-                 "global_load_dwordx4 %7, %13, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %8, %13, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %9, %13, off offset:48 sc1\n\t"
-                 "global_load_dwordx4 %10, %13, off offset:64 sc1\n\t"
-                 "global_load_dwordx4 %11, %13, off offset:80 sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(r[0][0]), "=&v"(r[0][1]), "=&v"(r[0][2]), "=&v"(r[0][3]), "=&v"(r[0][4]), "=&v"(r[0][5]), "=&v"(r[1][0]), "=&v"(r[1][1]), "=&v"(r[1][2]), "=&v"(r[1][3]), "=&v"(r[1][4]), "=&v"(r[1][5])
-                 : "v"(p[0]), "v"(p[1])
-                 : "memory");
-}
-
-template <>
-__device__ __forceinline__ void ld_lb<1, 2>(const u32x4 *const (&p)[1],
-                                               u32x4 (&r)[1][2])
-{
-    asm volatile(
-                 "global_load_dwordx4 %0, %2, off sc1\n\t"
-                 "global_load_dwordx4 %1, %2, off offset:16 sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(r[0][0]), "=&v"(r[0][1])
-                 : "v"(p[0])
-                 : "memory");
-}
-
-template <>
-__device__ __forceinline__ void ld_lb<1, 4>(const u32x4 *const (&p)[1],
-                                               u32x4 (&r)[1][4])
-{
-    asm volatile(
-                 "global_load_dwordx4 %0, %4, off sc1\n\t"
-                 "global_load_dwordx4 %1, %4, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %2, %4, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %3, %4, off offset:48 sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(r[0][0]), "=&v"(r[0][1]), "=&v"(r[0][2]), "=&v"(r[0][3])
-                 : "v"(p[0])
-                 : "memory");
-}
-
-template <>
-__device__ __forceinline__ void ld_lb<1, 3>(const u32x4 *const (&p)[1],
-                                               u32x4 (&r)[1][3])
-{
-    asm volatile(
-                 "global_load_dwordx4 %0, %3, off sc1\n\t"
-                 "global_load_dwordx4 %1, %3, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %2, %3, off offset:32 sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(r[0][0]), "=&v"(r[0][1]), "=&v"(r[0][2])
-                 : "v"(p[0])
-                 : "memory");
-}
-
-template <>
-__device__ __forceinline__ void ld_lb<1, 6>(const u32x4 *const (&p)[1],
-                                               u32x4 (&r)[1][6])
-{
-    asm volatile(
-                 "global_load_dwordx4 %0, %6, off sc1\n\t"
-                 "global_load_dwordx4 %1, %6, off offset:16 sc1\n\t"
-                 "global_load_dwordx4 %2, %6, off offset:32 sc1\n\t"
-                 "global_load_dwordx4 %3, %6, off offset:48 sc1\n\t"
-                 "global_load_dwordx4 %4, %6, off offset:64 sc1\n\t"
-                 "global_load_dwordx4 %5, %6, off offset:80 sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(r[0][0]), "=&v"(r[0][1]), "=&v"(r[0][2]), "=&v"(r[0][3]), "=&v"(r[0][4]), "=&v"(r[0][5])
-                 : "v"(p[0])
-                 : "memory");
-}
-
 
 // Polls NP pairs until all carry `tag`.  Returns false if the wait gave up
 // or another workgroup already did.

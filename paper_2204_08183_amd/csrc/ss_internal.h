@@ -32,38 +32,8 @@ constexpr int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // invalidates a whole L2, which costs microseconds and serialises every
 // workgroup of the XCD behind it.  So the values exchanged between
 // workgroups (look-back states, partial sums, counters) are only ever
-// written and read with agent-scope atomic stores and loads, which the
-// hardware performs at the device coherence point, and the two fences below
-// only order those accesses: all outstanding vector memory operations of the
-// wave complete (s_waitcnt vmcnt(0)), and a workgroup-scope fence keeps the
-// compiler from moving accesses across.
-__device__ __forceinline__ void order_release()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_s_waitcnt(0xF70);  // vmcnt(0); expcnt, lgkmcnt unchanged
-}
-__device__ __forceinline__ void order_acquire()
-{
-    __builtin_amdgcn_s_waitcnt(0xF70);
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
-
-__device__ __forceinline__ uint64_t ld_flag(const uint64_t *p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_flag(uint64_t *p, uint64_t v)
-{
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ double ld_relaxed(const double *p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_relaxed(double *p, double v)
-{
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
+// written and read with agent-scope stores and loads, which the hardware
+// performs at the device coherence point.
 __device__ __forceinline__ uint32_t ld_relaxed_u32(const uint32_t *p)
 {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -80,11 +50,6 @@ __device__ __forceinline__ void st_relaxed_u64(uint64_t *p, uint64_t v)
 {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ uint32_t fetch_add_relaxed(uint32_t *p, uint32_t v)
-{
-    return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 
 // ------------------------------------------------------------ workspace

@@ -686,6 +686,7 @@ __global__ __launch_bounds__(BLOCK, (fused_min_waves<IPT, MODEL, VALS, PRE>())) 
 
     // ---- 6. the tile's exclusive prefix
     SS_TRACE(ws, tile, 2);
+    const double em = PRE == 2 ? expm1(*a.step_prev) : 0.0;
     // (the same for every tile of the launch)
     const bool carried = PRE == 1 || (PRE == 2 && fabs(*a.step_prev) <= kCarryStep);
     if (carried) {
@@ -769,9 +770,8 @@ __global__ __launch_bounds__(BLOCK, (fused_min_waves<IPT, MODEL, VALS, PRE>())) 
     for (int c = 0; c < NX; ++c) carry[c] = s_excl[c];
     if constexpr (PRE == 2) {
         if (carried) {
-            const double f = expm1(*a.step_prev);
 #pragma unroll
-            for (int c = 0; c < NX; ++c) carry[c] += f * s_excl[NX + c];
+            for (int c = 0; c < NX; ++c) carry[c] += em * s_excl[NX + c];
         }
     }
     if constexpr (!F32S) {

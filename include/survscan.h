@@ -151,11 +151,13 @@ int32_t ss_workspace_error(const void *ws, int32_t *flag, void *stream);
  *   Cox:        S_m,k = sum_{r <= k} e_r x_rj^m
  *   Fine-Gray:  S_m,k = sum_{r <= k} e_r x_rj^m
  *                       + g_end_k * sum_{r after k's run} e_r x_rj^m w_comp_r
- * One fused pass: tuple scan with decoupled look-back, transform,
+ * Cox: one fused pass, tuple scan with decoupled look-back, transform,
  * reduction; the last tile finishes the reduction (Fig. 2).  The partial
  * sums are added in a fixed order, but a tile's prefix combines whichever
  * predecessor values the look-back finds visible first, so repeated calls
  * can differ in the last bits (far inside the 1e-10 parity bound).
+ * Fine-Gray: a pass for the tile sums, which the weighted totals need, and
+ * the same pass with its prefixes from them.
  * Inputs: e[n] in sorted order; the ss_prepare outputs; j in [0, p).
  * Output out[3] (device): g', g'', and sum_k d_k log S0_k. */
 int32_t ss_grad_hess(int32_t model, int64_t n, int64_t p, int64_t j,
@@ -209,13 +211,20 @@ int32_t ss_ccd_update(int32_t penalty, double lambda, int64_t n, int64_t p,
 
 /* ------------------------------------------------------------ fused sweep
  * Cyclic coordinate descent over coordinates j_begin..j_end-1 (Fig. 3)
- * without any host round trip: per coordinate one fused launch (Fine-Gray:
- * two) that applies the previous coordinate's update to eta and e (step
- * (1)), computes g', g'' (steps (2)-(4)) and, in its last tile, the update
- * of beta_j, delta_j and steps[j] (a3).  The last coordinate's update of
- * eta/e is applied before returning, so eta, e, beta and delta are
+ * without any host round trip: one cooperative launch where the problem fits
+ * on the device at once, else per coordinate one fused launch (Fine-Gray with
+ * a valued design: two) that applies the previous coordinate's update to eta
+ * and e (step (1)), computes g', g'' (steps (2)-(4)) and, in its last tile,
+ * the update of beta_j, delta_j and steps[j] (a3).  The last coordinate's
+ * update of eta/e is applied before returning, so eta, e, beta and delta are
  * consistent afterwards.  g12_out[3*p] (optional, may be NULL) receives
- * (g', g'', sum d log S0) of every visited coordinate. */
+ * (g', g'', sum d log S0) of every visited coordinate.
+ *
+ * e between the coordinates: the launches take exp(eta) anew wherever a step
+ * has moved eta, as the valued cooperative sweeps do.  The cooperative sweep
+ * of a 0/1 design multiplies e by exp(step) and takes exp(eta) when it ends:
+ * there an e that leaves the range of FP64 comes back with the end of the
+ * call, not with a later step of the same call. */
 int32_t ss_ccd_sweep(int32_t model, int32_t penalty, double lambda,
                      int64_t n, int64_t p, int64_t j_begin, int64_t j_end,
                      double *eta, double *e, const uint8_t *d8,

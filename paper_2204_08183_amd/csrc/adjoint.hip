@@ -390,7 +390,7 @@ __global__ __launch_bounds__(256) void k_xt_span(int64_t p, int64_t nspan, int64
 // of a group of columns from there.  A random 8-byte read takes a cache
 // line's worth of L2 bandwidth, which bounded the gather (N = 1e6, P = 1000,
 // 5e7 non-zeros: 194 us); from LDS it costs a bank access and the row indices
-// stream from HBM (46 us, 4.3 TB/s).  A wave takes the bounds of its columns
+// stream from HBM (43 us, 4.6 TB/s).  A wave takes the bounds of its columns
 // in one set of loads, and loads a column's first kXtAhead * 64 row indices
 // while it sums the column before.  Short pieces would leave most of those
 // lanes and loads idle: batches of them put several columns in flight at once

@@ -1206,7 +1206,7 @@ __global__ __launch_bounds__(BLOCK) void k_cv_sweep_fg(CvFgArgs f)
 // there is one scan and one barrier for a thread's IPT positions instead of
 // one per 8, and all CUs work (K follows the number of replicates).  ms per
 // 1000 coordinates, streaming / on chip, at N = 1e5: 100 replicates Cox 34.7 /
-// 18.6, 50 33.9 / 11.7, 10 31.3 / 5.0; 35 Fine-Gray replicates 58 / 16.5, 10
+// 18.6, 50 33.9 / 11.7, 10 31.3 / 5.0; 36 Fine-Gray replicates 59 / 14.5, 10
 // 54.2 / 6.0; 100 replicates at N = 5000 Cox 8.2 / 4.5, Fine-Gray 8.2 / 5.5.
 //
 // Bound: VALU issue (about 40 instructions per position and coordinate).

@@ -14,12 +14,12 @@
 // Bound: per non-zero one random 4-byte read of inv_perm and one LDS atomic;
 // 8 bytes of HBM traffic (20 valued) against 24 per pass of the 4-5 pass LSD
 // radix sort of (column, position) keys it replaced.  N = 1e6, P = 1000, 5e7
-// non-zeros: 288 us against 3.3 ms.  Of these the bits take 171 (292 G random
-// reads a second, the rate at which the L2s take requests: batches pipelined
-// so that reads and atomics overlap gave nothing), the list 103 (a store per
-// entry and lane; a wave's run gathered in LDS first took 77, but what
-// followed waited as much longer, the preparation unchanged at 617), counts
-// and clearing 24.
+// non-zeros: 288 us against 3.3 ms.  In a build that reads the clock between
+// its phases (298 us) the bits take 171 (5e7 random reads, 292 G a second, the
+// rate at which the L2s take requests: batches pipelined so that reads and
+// atomics overlap gave nothing), the list 103 (a store per entry and lane; a
+// wave's run gathered in LDS first took 77, but what followed waited as much
+// longer, the preparation unchanged at 617), counts and clearing 24.
 #include <algorithm>
 #include <vector>
 

@@ -1240,6 +1240,8 @@ constexpr int cv_on_lds()
 // e.  (A branch to a division in every group of run ends costs 2 to 3% of a
 // sweep, a transform of its own, behind one branch, more: the code then
 // outgrows the instruction cache.)
+// (In such a thread sums of 2^824 and more leave the range: an e of 1e248 next
+// to one of 1e-271.)
 __device__ __forceinline__ double cv_scale(double first)
 {
     return first < kQuotMin ? 0x1p200 : 1.0;
